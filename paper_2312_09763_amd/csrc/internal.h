@@ -196,6 +196,8 @@ struct HerkArgs {
     int32_t *nsplit;         // [n_inst] k-splits of each instance (built with work)
     int32_t *kcols;          // [n_inst] columns per k-split of each instance (a multiple of 64)
     int32_t balance_grid;    // > 0: add k-splits so the items fill whole waves of this many workgroups
+    int32_t n_bal;           // items per k-split of the launch that is balanced
+    int32_t min_cols;        // columns that a k-split keeps at least when splits are added
     int32_t grid;            // persistent grid size (multiple of 8)
 };
 int herk_super_tile(int prec);

@@ -74,13 +74,21 @@ __device__ inline int64_t inst_k(const int32_t *count, int64_t fixed_k, int n_ax
 
 // k-splits per instance and the item prefix.  nsplit_i starts at
 // ceil(K_i / ksplit); with balancing, extra splits are spread over the
-// instances until the total is a multiple of the persistent grid (capped by
-// max_splits and by 64 columns per split), and each instance's splits are made
-// equal: kcols_i = 64 ceil(K_i / (64 nsplit_i)).  Every workgroup then takes
-// the same number of items of nearly the same size.
+// instances until the items of the launch (n_bal per split) fill whole waves of
+// the persistent grid (capped by max_splits and by min_cols columns per split),
+// and each instance's splits are made equal:
+// kcols_i = 64 ceil(K_i / (64 nsplit_i)).  Every workgroup then takes the same
+// number of items of nearly the same size, and a call of few or small instances
+// still reaches every CU: 15 instances of 20 000 columns at 91 antennas made 75
+// items for 256 CUs and took 711 us on FP32, 255 items take 241 us; 8 instances
+// of 1000 columns on FP64 made 8 items of 63 serial stages, 134 us, and as 128
+// items take 29 us; 16 instances of 50 000 columns and 256 rows on FP64 filled
+// 2.2 of 3 waves of the grid, 6.26 ms, and fill 3 of 3 in 4.34 ms.  With several launches of different item counts
+// per split (unit mode, n_st = 1) the splits themselves are rounded once there
+// is a grid's worth of them, which suits every launch.
 __global__ void __launch_bounds__(1024) k_worklist(const int32_t *count, int64_t fixed_k, int n_ax, int nfb, int n_inst,
-                                                   int64_t ksplit, int n_st, int balance_grid, int max_splits,
-                                                   int32_t *work, int32_t *nsplit, int32_t *kcols) {
+                                                   int64_t ksplit, int n_st, int balance_grid, int n_bal, int min_cols,
+                                                   int max_splits, int32_t *work, int32_t *nsplit, int32_t *kcols) {
     __shared__ int wtot[1024 / kWave];
     __shared__ int carry_s, total_s;
     if (threadIdx.x == 0) {
@@ -99,7 +107,9 @@ __global__ void __launch_bounds__(1024) k_worklist(const int32_t *count, int64_t
         atomicAdd(&total_s, part);
         __syncthreads();
         const int t = total_s;
-        extra_all = (t + balance_grid - 1) / balance_grid * balance_grid - t;
+        const int64_t n = n_st == 1 && t >= balance_grid ? 1 : n_bal;
+        const int64_t waves = (t * n + balance_grid - 1) / balance_grid;
+        extra_all = (int)max<int64_t>(waves * balance_grid / n - t, 0);
     }
     for (int base = 0; base < n_inst; base += 1024) {
         int i = base + threadIdx.x;
@@ -110,7 +120,7 @@ __global__ void __launch_bounds__(1024) k_worklist(const int32_t *count, int64_t
             int64_t kc = ksplit;
             if (balance_grid > 0 && k > 0) {
                 const int extra = extra_all / n_inst + (i < extra_all % n_inst ? 1 : 0);
-                n = (int)min<int64_t>(min<int64_t>(n + extra, max_splits), (k + 63) / 64);
+                n = (int)max<int64_t>(min<int64_t>(min<int64_t>(n + extra, max_splits), (k + min_cols - 1) / min_cols), n);
                 kc = ((k + n - 1) / n + 63) / 64 * 64;
                 n = (int)((k + kc - 1) / kc);
             }
@@ -275,8 +285,9 @@ __global__ void __launch_bounds__(256, 2) k_herk(HerkArgs a) {
         const bool diag = (I == J);
         const int64_t K = inst_k(a.count, a.fixed_k, a.n_ax, a.nfb, inst);
         const int64_t Kr = ((K + KC - 1) / KC) * KC;
-        const int64_t kb = (int64_t)s * a.ksplit;
-        const int64_t ke = kb + a.ksplit < Kr ? kb + a.ksplit : Kr;
+        const int64_t kc = a.kcols[inst];
+        const int64_t kb = (int64_t)s * kc;
+        const int64_t ke = kb + kc < Kr ? kb + kc : Kr;
         const int64_t ioff = (int64_t)inst * a.inst_stride * D::EB;
 
         Acc acc_re[TI][TI], acc_im[TI][TI];
@@ -632,30 +643,46 @@ __global__ void __launch_bounds__(256) k_reduce_tiles(ReduceArgs a) {
         const int aa = r / nf, p = r % nf, b = c / nf, q = c % nf;
         return (((int64_t)aa * na + b) * nf + p) * nf + q;
     };
+    // The splits of this thread's four rows are summed together, so that the loads
+    // of four splits x four rows are in flight at once (the sums' order is the
+    // splits' either way): summed a row at a time, 128 splits cost more than the
+    // product of a small call.
+    const int c = 32 * C + tx;
+    double sr[4], si[4];
+    const PartT *pp[4];
+    bool on[4];
     for (int i = 0; i < 4; i++) {
-        const int rl = ty + 8 * i, r = 32 * R + rl, c = 32 * C + tx;
-        if (r >= N || c >= N || r < c) continue;
-        const PartT *pp = P + (int64_t)r * Np + c;
-        double sr = 0.0, si = 0.0;
-        for (int s = 0; s < ns; s++) {
-            const PartT v = pp[(int64_t)s * Np * Np];
-            sr += (double)v.x;
-            si += (double)v.y;
+        const int r = 32 * R + ty + 8 * i;
+        on[i] = r < N && c < N && r >= c;
+        pp[i] = P + (on[i] ? (int64_t)r * Np + c : 0);  // element 0 is readable for every split
+        sr[i] = si[i] = 0.0;
+    }
+#pragma unroll 4
+    for (int s = 0; s < ns; s++) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const PartT v = pp[i][(int64_t)s * Np * Np];
+            sr[i] += (double)v.x;
+            si[i] += (double)v.y;
         }
-        if (r == c) si = 0.0;
+    }
+    for (int i = 0; i < 4; i++) {
+        const int rl = ty + 8 * i, r = 32 * R + rl;
+        if (!on[i]) continue;
+        if (r == c) si[i] = 0.0;
         if (!a.first) {
             const double2 prev = acc[(int64_t)r * N + c];
-            sr += prev.x;
-            si += prev.y;
+            sr[i] += prev.x;
+            si[i] += prev.y;
         }
         if (!a.last) {
-            acc[(int64_t)r * N + c] = make_double2(sr, si);
+            acc[(int64_t)r * N + c] = make_double2(sr[i], si[i]);
             continue;
         }
-        sm[rl][tx] = make_double2(sr, si);
+        sm[rl][tx] = make_double2(sr[i], si[i]);
         OutT v;
-        v.x = sr;
-        v.y = si;
+        v.x = sr[i];
+        v.y = si[i];
         out[out_index(r, c)] = v;
     }
     if (!a.last) return;
@@ -737,7 +764,8 @@ hipError_t launch_worklist(int prec, const HerkArgs &a, int unit, hipStream_t s)
     const int nb = a.n_rows_pad / st;
     const int n_st = unit ? 1 : nb * (nb + 1) / 2;
     k_worklist<<<1, 1024, 0, s>>>(a.count, a.fixed_k, a.n_ax, a.nfb, a.n_inst, a.ksplit, n_st, a.balance_grid,
-                                  a.max_splits, a.work, a.nsplit, a.kcols);
+                                  a.n_bal < 1 ? 1 : a.n_bal, a.min_cols < 64 ? 64 : a.min_cols, a.max_splits, a.work,
+                                  a.nsplit, a.kcols);
     return hipGetLastError();
 }
 

@@ -48,6 +48,8 @@ struct matvis_ctx {
     int N = 0, Np = 0, st = 128;
     int64_t chunk = 0, ldz = 0, ksplit = 4096;
     int max_splits = 1, ntb = 1, nfb = 1, herk_grid = 512, fused_grid = 256;
+    int pair_splits = 1;  // k-splits of ksplit columns (the sub-matrix product, which is not balanced)
+    int n_bal = 1;        // items per k-split of the product launch that the splits are balanced for
     int64_t nblk_cap = 1;
     bool fused = false;  // Z formed inside the product (FP32 / BF16X3)
 
@@ -150,6 +152,10 @@ matvis_status dalloc(matvis_ctx *c, T **p, size_t bytes) {
     *p = (T *)q;
     return MATVIS_OK;
 }
+
+// Columns that a k-split keeps at least when k_worklist adds splits (four stages
+// of the product kernels; below that an item's fill and write-out outweigh it).
+constexpr int kMinSplitCols = 64;
 
 int64_t round_up(int64_t x, int64_t m) { return ((x + m - 1) / m) * m; }
 
@@ -293,7 +299,7 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
     const bool three_blocks =
         c->fused && fused_path(prec, cfg->n_feed, cfg->n_ax, cfg->n_beam, cfg->n_ant, c->Np) == MATVIS_PATH_FUSED_BLOCKS;
     c->ksplit = cfg->ksplit > 0 ? cfg->ksplit : default_ksplit(prec, over_sources, three_blocks);
-    c->max_splits = (int)((c->ldz + c->ksplit - 1) / c->ksplit);
+    c->max_splits = c->pair_splits = (int)((c->ldz + c->ksplit - 1) / c->ksplit);
     // batch: all channels of a few times, enough instances to fill the GPU with
     // work items while keeping Z within a fixed share of device memory
     c->nfb = cfg->batch_freq > 0 ? std::min(cfg->batch_freq, cfg->max_freq) : std::min(cfg->max_freq, 16);
@@ -310,6 +316,24 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
     int occ = std::max(1, herk_occupancy(prec));
     c->herk_grid = std::max(8, (c->n_cu * occ / 8) * 8);
     if (c->fused) c->fused_grid = std::max(8, (c->n_cu * std::max(1, herk_fused_occupancy(prec)) / 8) * 8);
+    // Room for the k-splits that k_worklist adds when a batch alone does not fill the
+    // grid: up to a grid's worth of items over the batch's instances, as long as the
+    // partials stay within 1 GiB (or what the plain splits need).
+    {
+        const int nb = c->Np / c->st;
+        const int grid = c->fused ? c->fused_grid : c->herk_grid;
+        c->n_bal = !c->fused ? nb * (nb + 1) / 2
+                   : over_sources ? c->Np / (2 * c->st)
+                   : three_blocks ? 3
+                   : prec == PB3 && nb == 2 ? 1  // one item holds both row blocks
+                                            : nb;
+        const int64_t per = std::max(1, grid / c->n_bal);
+        const size_t one = (size_t)B * c->Np * c->Np * cbytes(prec);
+        int64_t most = c->max_splits + (per + B - 1) / B;
+        most = std::min(most, (c->ldz + kMinSplitCols - 1) / kMinSplitCols);
+        most = std::min<int64_t>(most, (int64_t)(((size_t)1 << 30) / one));
+        c->max_splits = std::max<int64_t>(c->max_splits, most);
+    }
     // Z scratch: a whole batch when Z goes through device memory, else one
     // instance (used only by matvis_step_herk)
     const int zinst_n = c->fused ? 1 : B;
@@ -481,7 +505,9 @@ matvis_status enqueue_simulate(matvis_ctx *c, const double *antpos, const int32_
                 ha.work = c->work;
                 ha.nsplit = c->work + B_cap + 1;
                 ha.kcols = c->work + 2 * B_cap + 1;
-                ha.balance_grid = c->fused ? c->fused_grid : 0;
+                ha.balance_grid = c->fused ? c->fused_grid : c->herk_grid;
+                ha.n_bal = c->n_bal;
+                ha.min_cols = kMinSplitCols;
                 ha.grid = c->herk_grid;
                 if (!pairs) STEP(c, MATVIS_STEP_OTHER, s, launch_worklist(prec, ha, c->fused ? 1 : 0, s));
 
@@ -561,7 +587,7 @@ matvis_status enqueue_simulate(matvis_ctx *c, const double *antpos, const int32_
                     sa.nfb = nfb;
                     sa.n_inst = bt.n_inst;
                     sa.ksplit = c->ksplit;
-                    sa.max_splits = c->max_splits;
+                    sa.max_splits = c->pair_splits;
                     sa.part = c->pr_part;
                     if (c->fused && !c->pr_Z) {  // Z formed in the stages from B = sqrt(I) A and the fringe phase
                         sa.antc = c->antc;
@@ -580,7 +606,7 @@ matvis_status enqueue_simulate(matvis_ctx *c, const double *antpos, const int32_
                     SubmatReduceArgs sr{};
                     sr.part = c->pr_part;
                     sr.n_tiles = c->pr_tiles;
-                    sr.max_splits = c->max_splits;
+                    sr.max_splits = c->pair_splits;
                     sr.st = kSubmatTile;
                     sr.loc = c->pr_loc;
                     sr.n_pair = c->pr_n;
@@ -788,7 +814,7 @@ matvis_status matvis_set_pairs(matvis_ctx *c, const int32_t *pair_a, const int32
     matvis_status st;
     if ((st = dalloc(c, &c->pr_rows, sizeof(int32_t) * rows.size())) != MATVIS_OK) return st;
     if ((st = dalloc(c, &c->pr_loc, sizeof(int32_t) * loc.size())) != MATVIS_OK) return st;
-    if ((st = dalloc(c, &c->pr_part, cbytes(g.precision) * (size_t)B_cap * c->max_splits * n_tiles * ST * ST)) !=
+    if ((st = dalloc(c, &c->pr_part, cbytes(g.precision) * (size_t)B_cap * c->pair_splits * n_tiles * ST * ST)) !=
         MATVIS_OK)
         return st;
     if ((st = dalloc(c, &c->pr_vacc, sizeof(double) * 2 * (size_t)B_cap * n_pair * nf * nf)) != MATVIS_OK) return st;
