@@ -1,11 +1,10 @@
 // Kernels of the learned beam (layout and network in mlp.h).
 //
-// Training runs on small row-major FP32 tensors: Fourier features, a strided
-// MFMA GEMM with bias / SiLU epilogues (forward, and both backward products
-// through stride choices), SiLU backward, the squared-error gradient, column
-// sums for bias gradients, and Adam.  Products round their operands to bf16
-// and accumulate in FP32 (v_mfma_f32_16x16x32_bf16), or stay in FP32
-// (v_mfma_f32_16x16x4f32) in the FP32 check mode.
+// Training on bf16 products is in kernels_mlp_train.hip.  Its FP32 check mode
+// runs here on small row-major FP32 tensors: Fourier features, a strided MFMA
+// GEMM (v_mfma_f32_16x16x4f32) with bias / SiLU epilogues (forward, and both
+// backward products through stride choices), SiLU backward, the squared-error
+// gradient, column sums for bias gradients, and Adam.
 //
 // Inference (k_mlp_infer) is one persistent launch: every workgroup holds
 // the bf16 hidden weights in LDS and each wave runs the whole network on 64
@@ -17,22 +16,15 @@
 #include <algorithm>
 
 #include "beam_interp.h"
-#include "mlp.h"
+#include "mlp_math.h"
 
 namespace mv {
 
 namespace {
 
+using namespace mlp;
+
 __device__ inline int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
-
-__device__ inline float silu(float z) { return z / (1.0f + __expf(-z)); }
-
-// sin / cos of 2 pi r with the hardware units (argument in revolutions) after reduction
-__device__ inline void sincos_rev(float r, float &s, float &c) {
-    r -= rintf(r);
-    s = __builtin_amdgcn_sinf(r);
-    c = __builtin_amdgcn_cosf(r);
-}
 
 // ---------------------------------------------------------------- features
 __global__ void k_features(const float *__restrict__ x, int64_t n, const float *__restrict__ P,
@@ -72,14 +64,10 @@ struct GemmArgs {
     float *partial;
 };
 
-template <bool BF16>
 __global__ void __launch_bounds__(256) k_gemm(GemmArgs g) {
     constexpr int T = 64, KS = 32;
-    constexpr int RSB = KS + 8;  // bf16 row stride (elements): 80 B, keeps 16-byte lane reads aligned
     constexpr int RSF = KS + 1;  // float row stride
-    __shared__ __attribute__((aligned(16))) unsigned char smem[2 * T * (BF16 ? RSB * 2 : RSF * 4)];
-    __bf16 *Ab = (__bf16 *)smem, *Bb = Ab + T * RSB;
-    float *Af = (float *)smem, *Bf = Af + T * RSF;
+    __shared__ float Af[T * RSF], Bf[T * RSF];
     const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
     const int l16 = lane & 15, lk = lane >> 4;
     const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
@@ -94,33 +82,17 @@ __global__ void __launch_bounds__(256) k_gemm(GemmArgs g) {
             const int ra = a_kfast ? e / KS : e % T, ka = a_kfast ? e % KS : e / T;
             const int rb = b_kfast ? e / KS : e % T, kb = b_kfast ? e % KS : e / T;
             const int gm = m0 + ra, gka = k0 + ka, gn = n0 + rb, gkb = k0 + kb;
-            const float va = (gm < g.M && gka < kend) ? g.A[gm * g.sam + gka * g.sak] : 0.f;
-            const float vb = (gn < g.N && gkb < kend) ? g.B[gn * g.sbn + gkb * g.sbk] : 0.f;
-            if (BF16) {
-                Ab[ra * RSB + ka] = (__bf16)va;
-                Bb[rb * RSB + kb] = (__bf16)vb;
-            } else {
-                Af[ra * RSF + ka] = va;
-                Bf[rb * RSF + kb] = vb;
-            }
+            Af[ra * RSF + ka] = (gm < g.M && gka < kend) ? g.A[gm * g.sam + gka * g.sak] : 0.f;
+            Bf[rb * RSF + kb] = (gn < g.N && gkb < kend) ? g.B[gn * g.sbn + gkb * g.sbk] : 0.f;
         }
         __syncthreads();
-        if (BF16) {
-            bf16x8 a[2], b[2];
-            for (int i = 0; i < 2; i++) a[i] = *(const bf16x8 *)(Ab + (wr + 16 * i + l16) * RSB + lk * 8);
-            for (int j = 0; j < 2; j++) b[j] = *(const bf16x8 *)(Bb + (wc + 16 * j + l16) * RSB + lk * 8);
+        for (int kk = 0; kk < KS; kk += 4) {
+            float a[2], b[2];
+            for (int i = 0; i < 2; i++) a[i] = Af[(wr + 16 * i + l16) * RSF + kk + lk];
+            for (int j = 0; j < 2; j++) b[j] = Bf[(wc + 16 * j + l16) * RSF + kk + lk];
             for (int i = 0; i < 2; i++)
                 for (int j = 0; j < 2; j++)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-        } else {
-            for (int kk = 0; kk < KS; kk += 4) {
-                float a[2], b[2];
-                for (int i = 0; i < 2; i++) a[i] = Af[(wr + 16 * i + l16) * RSF + kk + lk];
-                for (int j = 0; j < 2; j++) b[j] = Bf[(wc + 16 * j + l16) * RSF + kk + lk];
-                for (int i = 0; i < 2; i++)
-                    for (int j = 0; j < 2; j++)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
-            }
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
         }
         __syncthreads();
     }
@@ -140,22 +112,10 @@ __global__ void __launch_bounds__(256) k_gemm(GemmArgs g) {
 }
 
 // ---------------------------------------------------------------- backward helpers
-// dZ = dH * d SiLU/dz = dH * s (1 + z (1 - s)),  s = 1 / (1 + exp(-z))
 __global__ void k_silu_bwd(const float *__restrict__ dH, const float *__restrict__ Z, float *__restrict__ dZ,
                            int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float z = Z[i];
-    const float s = 1.0f / (1.0f + __expf(-z));
-    dZ[i] = dH[i] * s * (1.0f + z * (1.0f - s));
-}
-
-// T_0..T_{kBasis-1} of the first kind at t (three-term recurrence)
-__device__ inline void chebyshev(float t, float (&T)[kBasis]) {
-    T[0] = 1.0f;
-    T[1] = t;
-#pragma unroll
-    for (int k = 2; k < kBasis; k++) T[k] = 2.0f * t * T[k - 1] - T[k - 2];
+    if (i < n) dZ[i] = silu_grad(dH[i], Z[i]);
 }
 
 // One thread per (row m, output o): out = sum_k T_k(2 w - 1) net[m][8 o + k]
@@ -226,19 +186,12 @@ __global__ void __launch_bounds__(256) k_colsum_part(const float *__restrict__ d
     if (rl == 0 && c < N) part[(int64_t)blockIdx.y * N + c] = (red[0][cl] + red[1][cl]) + (red[2][cl] + red[3][cl]);
 }
 
-// Adam (Kingma & Ba 2015) on the trainable parameters (the Fourier matrix is fixed).
+// Adam on the trainable parameters (the Fourier matrix is fixed).
 __global__ void k_adam(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m1,
                        float *__restrict__ m2, int64_t n, int64_t step, float lr, float b1, float b2, float eps) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n || i < kOffW1) return;
-    const float gi = g[i];
-    const float a = b1 * m1[i] + (1.0f - b1) * gi;
-    const float b = b2 * m2[i] + (1.0f - b2) * gi * gi;
-    m1[i] = a;
-    m2[i] = b;
-    const float ah = a / (1.0f - powf(b1, (float)step));
-    const float bh = b / (1.0f - powf(b2, (float)step));
-    p[i] -= lr * ah / (sqrtf(bh) + eps);
+    p[i] = adam_step(p[i], g[i], m1[i], m2[i], step, lr, b1, b2, eps);
 }
 
 // dst[i][:] = src[perm[i]][:] (mini-batch assembly)
@@ -254,11 +207,6 @@ __global__ void k_gather_rows(const float *__restrict__ src, int width, const in
 __global__ void k_fill(float *__restrict__ out, int64_t n, float v) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) out[i] = v;
-}
-
-__global__ void k_to_bf16(const float *__restrict__ in, __bf16 *__restrict__ out, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = (__bf16)in[i];
 }
 
 // ---------------------------------------------------------------- training samples
@@ -664,8 +612,8 @@ hipError_t features(const float *x, int64_t n, const float *P, float *phi, hipSt
     return hipGetLastError();
 }
 
-hipError_t gemm(bool bf16, const float *A, int64_t sam, int64_t sak, const float *B, int64_t sbn, int64_t sbk, int M,
-                int N, int K, const float *bias, float *Z, float *H, int act, float *ws, int64_t ws_elems, hipStream_t s) {
+hipError_t gemm(const float *A, int64_t sam, int64_t sak, const float *B, int64_t sbn, int64_t sbk, int M, int N, int K,
+                const float *bias, float *Z, float *H, int act, float *ws, int64_t ws_elems, hipStream_t s) {
     if (M <= 0 || N <= 0) return hipSuccess;
     GemmArgs g{A, sam, sak, B, sbn, sbk, M, N, K, bias, Z, H, act, K, nullptr};
     dim3 grid((N + 63) / 64, (M + 63) / 64, 1);
@@ -682,10 +630,7 @@ hipError_t gemm(bool bf16, const float *A, int64_t sam, int64_t sak, const float
         g.partial = ws;
         grid.z = nz;
     }
-    if (bf16)
-        k_gemm<true><<<grid, 256, 0, s>>>(g);
-    else
-        k_gemm<false><<<grid, 256, 0, s>>>(g);
+    k_gemm<<<grid, 256, 0, s>>>(g);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || nz == 1) return e;
     const int64_t n = (int64_t)M * N;
@@ -734,11 +679,6 @@ hipError_t gather_rows(const float *src, int width, const int32_t *perm, int64_t
 hipError_t fill(float *out, int64_t n, float v, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     k_fill<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(out, n, v);
-    return hipGetLastError();
-}
-
-hipError_t to_bf16(const float *in, __bf16 *out, int64_t n, hipStream_t s) {
-    k_to_bf16<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(in, out, n);
     return hipGetLastError();
 }
 

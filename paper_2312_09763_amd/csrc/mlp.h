@@ -50,12 +50,11 @@ constexpr int64_t kNParams = kOffB5 + kNet;   // 90944
 namespace mlp {
 hipError_t features(const float *x, int64_t n, const float *P, float *phi, hipStream_t s);
 // Z = A B^T + bias with A(m, k) = A[m sam + k sak], B(n, k) = B[n sbn + k sbk];
-// H = SiLU(Z) when act = 1.  bf16 rounds both operands to bf16 first.  A plain
+// H = SiLU(Z) when act = 1, in FP32 (the check mode of training).  A plain
 // product (no bias, no H) over a long k may split k through the workspace ws
 // (ws_elems floats; NULL disables the split).
-hipError_t gemm(bool bf16, const float *A, int64_t sam, int64_t sak, const float *B, int64_t sbn, int64_t sbk, int M,
-                int N, int K, const float *bias, float *Z, float *H, int act, float *ws, int64_t ws_elems,
-                hipStream_t s);
+hipError_t gemm(const float *A, int64_t sam, int64_t sak, const float *B, int64_t sbn, int64_t sbk, int M, int N, int K,
+                const float *bias, float *Z, float *H, int act, float *ws, int64_t ws_elems, hipStream_t s);
 hipError_t silu_bwd(const float *dH, const float *Z, float *dZ, int64_t n, hipStream_t s);
 // The basis sums and the squared error: out_o = sum_k T_k(2 x[m][2] - 1) net[m][8 o + k],
 // loss = sum (out - y)^2 / (8 n), dnet[m][8 o + k] = T_k 2 (out_o - y_o) / (8 n).
@@ -65,7 +64,6 @@ hipError_t loss_grad(const float *net, const float *x, const float *y, int64_t n
 hipError_t colsum(const float *dZ, int64_t M, int N, float *db, float *ws, int64_t ws_elems, hipStream_t s);
 hipError_t adam(float *p, const float *g, float *m1, float *m2, int64_t n, int64_t step, float lr, hipStream_t s);
 hipError_t fill(float *out, int64_t n, float v, hipStream_t s);
-hipError_t to_bf16(const float *in, __bf16 *out, int64_t n, hipStream_t s);
 // bf16 W1..W4 (kWbElems values, 160 KB) in the inference kernel's LDS image:
 // 1 KB MFMA A-operand blocks per (layer, 16-row tile, 32-deep k block), the
 // columns of W2..W4 permuted to the accumulator order of the layer before;
@@ -88,6 +86,31 @@ hipError_t infer_sim(const float *P, const __bf16 *Wb, double nu0, double nu1, c
                      int64_t stokes_stride, const double *freqs, int64_t ld_src, int64_t max_m, void *A, int n_feed,
                      int n_ax, int beam, int n_beam, const Batch &bt, hipStream_t s);
 hipError_t gather_rows(const float *src, int width, const int32_t *perm, int64_t n, float *dst, hipStream_t s);
+
+// Training on bf16 products (kernels_mlp_train.hip): activations and gradients of n
+// rows, the partial sums of the weight gradients, and the operand images of the
+// parameters.
+struct TrainBufs {
+    __bf16 *phi;    // [n][kFeat] features
+    __bf16 *h[3];   // [n][kHid] hidden layers 1..3
+    float *h4;      // [n][kHid] hidden layer 4
+    float *dz[4];   // [n][kHid] pre-activation gradients of layers 1..4
+    float *dnet;    // [n][kNet] gradients of the coefficients
+    float *part;    // [train_part_floats(n)]
+    double *sq;     // [train_sq_count(n)] partial sums of squares
+    float *images;  // [train_image_floats()]
+};
+int64_t train_part_floats(int64_t n);
+int64_t train_image_floats();
+int64_t train_sq_count(int64_t n);
+// the images of parameters P (before the first train_step on them)
+hipError_t train_pack(const float *P, float *images, hipStream_t s);
+// Loss (and gradient, where grad is set) of n rows of (x, y), row m being row
+// perm[m] where perm is set.  With update (= P), m1 and m2 set, also one Adam
+// step on them, which renews the images.
+hipError_t train_step(const TrainBufs &b, const float *P, const float *x, const float *y, const int32_t *perm,
+                      int64_t n, float *grad, float *loss, float *update, float *m1, float *m2, int64_t step, float lr,
+                      hipStream_t s);
 }  // namespace mlp
 
 }  // namespace mv

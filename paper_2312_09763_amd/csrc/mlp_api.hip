@@ -1,11 +1,13 @@
 // Host side of the learned beam (include/matvis.h, "Learned beam").
-// Forward and backward passes are chains of the kernels in kernels_mlp.hip;
-// the training loop is native and only synchronises once per epoch to read
-// the loss.
+// The loss and its gradient are the three launches of kernels_mlp_train.hip, or
+// in the FP32 check mode a chain of the kernels in kernels_mlp.hip; the training
+// loop is native, synchronises once per epoch, and draws the next epoch's order
+// while the GPU runs the current one.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <mutex>
+#include <new>
 #include <numeric>
 #include <random>
 #include <vector>
@@ -28,7 +30,7 @@ namespace {
         }                                              \
     } while (0)
 
-// Activation workspace for n rows: buffer sizes in floats, in the order the
+// Activation workspace of the FP32 check mode for n rows: buffer sizes in floats, in the order the
 // workspace holds them.  alloc() gives each its own device allocation; bind()
 // carves them, 256-byte aligned, out of one caller-provided block of
 // Work::floats_for(rows) floats.
@@ -95,8 +97,45 @@ struct Work {
     }
 };
 
-// Forward + backward of the squared error for w.n rows of (x, y).
-hipError_t loss_grad_impl(const float *P, const float *x, const float *y, bool bf16, float *grad, float *loss, Work &w,
+// Workspace of the bf16 mode for n rows: train_bind() carves the buffers, 256-byte
+// aligned, out of one block of train_floats(n) floats.
+mlp::TrainBufs train_bind(float *base, int64_t n, int64_t *total = nullptr) {
+    int64_t off = 0;
+    auto piece = [&](int64_t floats) {
+        float *p = base ? base + off : nullptr;
+        off += Work::round_a(floats);
+        return p;
+    };
+    mlp::TrainBufs b{};
+    b.phi = (__bf16 *)piece(n * kFeat / 2);
+    for (int l = 0; l < 3; l++) b.h[l] = (__bf16 *)piece(n * kHid / 2);
+    b.h4 = piece(n * kHid);
+    for (int l = 0; l < 4; l++) b.dz[l] = piece(n * kHid);
+    b.dnet = piece(n * kNet);
+    b.part = piece(mlp::train_part_floats(n));
+    b.sq = (double *)piece(2 * mlp::train_sq_count(n));
+    b.images = piece(mlp::train_image_floats());
+    if (total) *total = off;
+    return b;
+}
+int64_t train_floats(int64_t n) {
+    int64_t total = 0;
+    (void)train_bind(nullptr, n, &total);
+    return total;
+}
+
+// Loss and gradient of n rows on bf16 products in a block of train_floats(n) floats.
+hipError_t loss_grad_bf16(const float *P, const float *x, const float *y, int64_t n, float *grad, float *loss,
+                          float *base, hipStream_t s) {
+    const mlp::TrainBufs b = train_bind(base, n);
+    hipError_t e = mlp::train_pack(P, b.images, s);
+    if (e == hipSuccess)
+        e = mlp::train_step(b, P, x, y, nullptr, n, grad, loss, nullptr, nullptr, nullptr, 0, 0.f, s);
+    return e;
+}
+
+// FP32 forward + backward of the squared error for w.n rows of (x, y).
+hipError_t loss_grad_impl(const float *P, const float *x, const float *y, float *grad, float *loss, Work &w,
                           hipStream_t s) {
     const int64_t n = w.n;
     const int ni = (int)n;
@@ -104,36 +143,36 @@ hipError_t loss_grad_impl(const float *P, const float *x, const float *y, bool b
 #define RET(expr)                      \
     if ((e = (expr)) != hipSuccess) return e
     RET(mlp::features(x, n, P, w.phi, s));
-    RET(mlp::gemm(bf16, w.phi, kFeat, 1, P + kOffW1, kFeat, 1, ni, kHid, kFeat, P + kOffB1, w.Z[0], w.H[0], 1,
+    RET(mlp::gemm(w.phi, kFeat, 1, P + kOffW1, kFeat, 1, ni, kHid, kFeat, P + kOffB1, w.Z[0], w.H[0], 1,
                   w.ws, w.ws_elems, s));
     const int64_t offW[3] = {kOffW2, kOffW3, kOffW4}, offB[3] = {kOffB2, kOffB3, kOffB4};
     for (int l = 1; l < 4; l++)
-        RET(mlp::gemm(bf16, w.H[l - 1], kHid, 1, P + offW[l - 1], kHid, 1, ni, kHid, kHid, P + offB[l - 1], w.Z[l],
+        RET(mlp::gemm(w.H[l - 1], kHid, 1, P + offW[l - 1], kHid, 1, ni, kHid, kHid, P + offB[l - 1], w.Z[l],
                       w.H[l], 1, w.ws, w.ws_elems, s));
-    // the linear head in FP32 (inference splits it hi / lo), then the Chebyshev
+    // the linear head, then the Chebyshev
     // sums of the frequency head and the squared error
-    RET(mlp::gemm(false, w.H[3], kHid, 1, P + kOffW5, kHid, 1, ni, kNet, kHid, P + kOffB5, w.out, nullptr, 0,
+    RET(mlp::gemm(w.H[3], kHid, 1, P + kOffW5, kHid, 1, ni, kNet, kHid, P + kOffB5, w.out, nullptr, 0,
                   w.ws, w.ws_elems, s));
     RET(mlp::loss_grad(w.out, x, y, n, w.dout, w.part, loss, s));
     RET(mlp::fill(grad, kOffW1, 0.f, s));  // the Fourier matrix is not trained
     // output layer
-    RET(mlp::gemm(false, w.dout, 1, kNet, w.H[3], 1, kHid, kNet, kHid, ni, nullptr, grad + kOffW5, nullptr, 0,
+    RET(mlp::gemm(w.dout, 1, kNet, w.H[3], 1, kHid, kNet, kHid, ni, nullptr, grad + kOffW5, nullptr, 0,
                   w.ws, w.ws_elems, s));
     RET(mlp::colsum(w.dout, n, kNet, grad + kOffB5, w.ws, w.ws_elems, s));
-    RET(mlp::gemm(false, w.dout, kNet, 1, P + kOffW5, 1, kHid, ni, kHid, kNet, nullptr, w.dH, nullptr, 0,
+    RET(mlp::gemm(w.dout, kNet, 1, P + kOffW5, 1, kHid, ni, kHid, kNet, nullptr, w.dH, nullptr, 0,
                   w.ws, w.ws_elems, s));
     // hidden layers 4..2
     const int64_t gW[4] = {kOffW1, kOffW2, kOffW3, kOffW4}, gB[4] = {kOffB1, kOffB2, kOffB3, kOffB4};
     for (int l = 3; l >= 1; l--) {
         RET(mlp::silu_bwd(w.dH, w.Z[l], w.dZ, n * kHid, s));
-        RET(mlp::gemm(bf16, w.dZ, 1, kHid, w.H[l - 1], 1, kHid, kHid, kHid, ni, nullptr, grad + gW[l], nullptr, 0,
+        RET(mlp::gemm(w.dZ, 1, kHid, w.H[l - 1], 1, kHid, kHid, kHid, ni, nullptr, grad + gW[l], nullptr, 0,
                       w.ws, w.ws_elems, s));
         RET(mlp::colsum(w.dZ, n, kHid, grad + gB[l], w.ws, w.ws_elems, s));
-        RET(mlp::gemm(bf16, w.dZ, kHid, 1, P + gW[l], 1, kHid, ni, kHid, kHid, nullptr, w.dH, nullptr, 0,
+        RET(mlp::gemm(w.dZ, kHid, 1, P + gW[l], 1, kHid, ni, kHid, kHid, nullptr, w.dH, nullptr, 0,
                       w.ws, w.ws_elems, s));
     }
     RET(mlp::silu_bwd(w.dH, w.Z[0], w.dZ, n * kHid, s));
-    RET(mlp::gemm(bf16, w.dZ, 1, kHid, w.phi, 1, kFeat, kHid, kFeat, ni, nullptr, grad + kOffW1, nullptr, 0,
+    RET(mlp::gemm(w.dZ, 1, kHid, w.phi, 1, kFeat, kHid, kFeat, ni, nullptr, grad + kOffW1, nullptr, 0,
                   w.ws, w.ws_elems, s));
     RET(mlp::colsum(w.dZ, n, kHid, grad + kOffB1, w.ws, w.ws_elems, s));
 #undef RET
@@ -193,9 +232,18 @@ matvis_status matvis_mlp_loss_grad(const float *params, const float *x, const fl
                                    float *grad, float *loss, void *stream) {
     if (!params || !x || !y || !grad || !loss || n <= 0 || n > (1 << 24)) return MATVIS_EINVAL;
     hipStream_t s = (hipStream_t)stream;
+    if (!fp32_math) {
+        float *base = nullptr;
+        CK(hipMalloc(&base, sizeof(float) * train_floats(n)));
+        hipError_t e = loss_grad_bf16(params, x, y, n, grad, loss, base, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        (void)hipFree(base);
+        CK(e);
+        return MATVIS_OK;
+    }
     Work w;
     CK(w.alloc(n));
-    CK(loss_grad_impl(params, x, y, !fp32_math, grad, loss, w, s));
+    CK(loss_grad_impl(params, x, y, grad, loss, w, s));
     CK(hipStreamSynchronize(s));
     return MATVIS_OK;
 }
@@ -210,16 +258,20 @@ matvis_status matvis_mlp_loss_grad_noalloc(const float *params, const float *x, 
                 (long long)n, (long long)kNoAllocRows);
         return MATVIS_EINVAL;
     }
-    if (Work::floats_for(kNoAllocRows) != kNoAllocFloats) {  // layout and array size out of step
+    if (Work::floats_for(kNoAllocRows) != kNoAllocFloats || train_floats(n) > kNoAllocFloats) {  // layout and array size out of step
         fprintf(stderr, "matvis_mlp_loss_grad_noalloc: workspace layout needs %lld floats, array holds %lld\n",
                 (long long)Work::floats_for(kNoAllocRows), (long long)kNoAllocFloats);
         return MATVIS_EUNSUPPORTED;
     }
     float *base = nullptr;
     CK(noalloc_scratch(&base));
+    if (!fp32_math) {
+        CK(loss_grad_bf16(params, x, y, n, grad, loss, base, (hipStream_t)stream));
+        return MATVIS_OK;
+    }
     Work w;
     w.bind(base, n);
-    CK(loss_grad_impl(params, x, y, !fp32_math, grad, loss, w, (hipStream_t)stream));
+    CK(loss_grad_impl(params, x, y, grad, loss, w, (hipStream_t)stream));
     return MATVIS_OK;
 }
 
@@ -258,42 +310,56 @@ matvis_status matvis_train_surrogate(float *params, const float *x, const float 
         return MATVIS_EINVAL;
     hipStream_t s = (hipStream_t)stream;
     const int64_t bsz = std::min<int64_t>(batch, n);
-    Work w;
-    CK(w.alloc(bsz));
-    float *grad = nullptr, *m1 = nullptr, *m2 = nullptr, *xb = nullptr, *yb = nullptr, *lossd = nullptr;
-    int32_t *perm_d = nullptr;
-    std::vector<void *> allocs;
-    auto al = [&](void **p, size_t bytes) {
-        hipError_t e = hipMalloc(p, bytes);
-        if (e == hipSuccess) allocs.push_back(*p);
-        return e;
-    };
-    hipError_t e = al((void **)&grad, sizeof(float) * kNParams);
-    if (e == hipSuccess) e = al((void **)&m1, sizeof(float) * kNParams);
-    if (e == hipSuccess) e = al((void **)&m2, sizeof(float) * kNParams);
-    if (e == hipSuccess) e = al((void **)&xb, sizeof(float) * bsz * 3);
-    if (e == hipSuccess) e = al((void **)&yb, sizeof(float) * bsz * kOut);
-    if (e == hipSuccess) e = al((void **)&lossd, sizeof(float) * 4096);
-    if (e == hipSuccess) e = al((void **)&perm_d, sizeof(int32_t) * n);
-    if (e == hipSuccess) e = hipMemsetAsync(m1, 0, sizeof(float) * kNParams, s);
-    if (e == hipSuccess) e = hipMemsetAsync(m2, 0, sizeof(float) * kNParams, s);
-    std::vector<int32_t> perm((size_t)n);
-    std::iota(perm.begin(), perm.end(), 0);
-    std::mt19937_64 rng(seed);
     const int64_t nb = n / bsz;  // whole batches only
+    std::vector<int32_t> order[2];  // this epoch's and the next one's
+    std::vector<float> lh;
+    try {
+        order[0].resize((size_t)n);
+        if (epochs > 1) order[1].resize((size_t)n);
+        lh.resize((size_t)std::min<int64_t>(nb, 4096));
+    } catch (const std::bad_alloc &) {
+        return MATVIS_ENOMEM;
+    }
+    std::iota(order[0].begin(), order[0].end(), 0);
+    std::mt19937_64 rng(seed);
+    std::shuffle(order[0].begin(), order[0].end(), rng);
+    Work w;
+    if (fp32_math) CK(w.alloc(bsz));
+    // one block: the row buffers (bf16 mode) or a batch's gradient and samples (check
+    // mode), then the moments, the losses and the order
+    const int64_t head = fp32_math ? Work::round_a(kNParams) + Work::round_a(bsz * 3) + Work::round_a(bsz * kOut)
+                                   : train_floats(bsz);
+    const int64_t moments = Work::round_a(kNParams);
+    float *base = nullptr;
+    CK(hipMalloc(&base, sizeof(float) * (head + 2 * moments + 4096 + n)));
+    float *grad = base, *xb = grad + Work::round_a(kNParams), *yb = xb + Work::round_a(bsz * 3);  // check mode
+    float *m1 = base + head, *m2 = m1 + moments, *lossd = m2 + moments;
+    int32_t *perm_d = (int32_t *)(lossd + 4096);
+    const mlp::TrainBufs tb = fp32_math ? mlp::TrainBufs{} : train_bind(base, bsz);
+    hipError_t e = hipMemsetAsync(m1, 0, sizeof(float) * 2 * moments, s);
+    if (e == hipSuccess && !fp32_math) e = mlp::train_pack(params, tb.images, s);
     int64_t step = 0;
-    std::vector<float> lh((size_t)std::min<int64_t>(nb, 4096));
     for (int ep = 0; ep < epochs && e == hipSuccess; ep++) {
         if (ep > 0) e = hipStreamSynchronize(s);  // the previous epoch's order has been uploaded
         if (e != hipSuccess) break;
-        std::shuffle(perm.begin(), perm.end(), rng);
+        const std::vector<int32_t> &perm = order[ep & 1];
         e = hipMemcpyAsync(perm_d, perm.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, s);
         const float lr = epochs > 1 ? lr0 * std::pow(lr1 / lr0, (float)ep / (float)(epochs - 1)) : lr0;
         for (int64_t b = 0; b < nb && e == hipSuccess; b++) {
+            if (!fp32_math) {
+                e = mlp::train_step(tb, params, x, y, perm_d + b * bsz, bsz, nullptr, lossd + (b % 4096), params, m1,
+                                    m2, ++step, lr, s);
+                continue;
+            }
             e = mlp::gather_rows(x, 3, perm_d + b * bsz, bsz, xb, s);
             if (e == hipSuccess) e = mlp::gather_rows(y, kOut, perm_d + b * bsz, bsz, yb, s);
-            if (e == hipSuccess) e = loss_grad_impl(params, xb, yb, !fp32_math, grad, lossd + (b % 4096), w, s);
+            if (e == hipSuccess) e = loss_grad_impl(params, xb, yb, grad, lossd + (b % 4096), w, s);
             if (e == hipSuccess) e = mlp::adam(params, grad, m1, m2, kNParams, ++step, lr, s);
+        }
+        if (ep + 1 < epochs) {  // the next epoch's order, while the GPU works
+            std::vector<int32_t> &next = order[(ep + 1) & 1];
+            std::copy(perm.begin(), perm.end(), next.begin());
+            std::shuffle(next.begin(), next.end(), rng);
         }
         if (e == hipSuccess && loss_history) {
             const int64_t k = std::min<int64_t>(nb, 4096);
@@ -304,8 +370,9 @@ matvis_status matvis_train_surrogate(float *params, const float *x, const float 
             loss_history[ep] = (float)(sum / (double)k);
         }
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    for (void *p : allocs) (void)hipFree(p);
+    const hipError_t done = hipStreamSynchronize(s);  // also after an error: the block is in use until then
+    if (e == hipSuccess) e = done;
+    (void)hipFree(base);
     CK(e);
     return MATVIS_OK;
 }
