@@ -374,7 +374,7 @@ def cpu_baseline(wl, grid):
 
 def side_by_side(args, wl, vis, stream, tuned):
     """The headline's sample through the FP64 interpolated path, FP32 and BF16X3 with the
-    bicubic-interpolated beam (Z in device memory on FP64; formed in the product otherwise).
+    bicubic-interpolated beam (Z formed in the product).
     BF16X3 takes the headline's tuned product configuration, FP32 and FP64 the defaults."""
     import torch
     from paper_2312_09763_amd import matvis as mv
@@ -391,7 +391,10 @@ def side_by_side(args, wl, vis, stream, tuned):
             _, count, _, _ = vctx.step_sky(vd["lsts"], vd["src_radec"])
             counts = count.cpu().numpy().astype(np.int64)
             vpath = vctx.product_path
-            tot, _, _ = product_flops(vpath, wl.n_ant, wl.n_feed, wl.n_ax, counts, wl.n_freq)
+            # FP64 with a shared 2 x 2 beam also takes the axis sum per source first (product_path
+            # reports z_in_hbm for every FP64 context)
+            tot, _, _ = product_flops("sources" if vprec == "fp64" else vpath, wl.n_ant, wl.n_feed, wl.n_ax, counts,
+                                      wl.n_freq)
             pms = vprof["herk"][0] + vprof["herk_pairs"][0]
             vtf = tot * PRODUCTS[vprec] / (pms / 1e3) / 1e12 if pms > 0 else None
             vsteps = {k: round(v[0], 4) for k, v in vprof.items()}

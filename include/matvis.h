@@ -109,7 +109,7 @@ typedef struct {
 } matvis_config;
 
 #define MATVIS_FLAG_NO_GRAPH 1 /* launch kernels directly instead of replaying a captured hipGraph */
-#define MATVIS_FLAG_UNFUSED 2  /* FP32 / BF16X3: write Z to device memory in a separate step
+#define MATVIS_FLAG_UNFUSED 2  /* write Z to device memory in a separate step
                                   (Alg. 2 step (iv)) instead of forming it inside the product */
 #define MATVIS_FLAG_POLARISED_SKY 4 /* src_flux holds all four Stokes parameters per source and
                                        channel: the brightness matrix of Sec. 2.1,
@@ -363,7 +363,11 @@ matvis_status matvis_profile_read(matvis_ctx *ctx, double *ms, int64_t *launches
 
 /* Which kernel forms the product of Eq. zz for this context (fixed at init):
  *   MATVIS_PATH_Z_IN_HBM   Z is written to device memory by its own step and
- *                          V = Z Z^H reads it (FP64, or MATVIS_FLAG_UNFUSED);
+ *                          V = Z Z^H reads it (FP64, or MATVIS_FLAG_UNFUSED).
+ *                          Reported for every FP64 context, also where matvis_simulate
+ *                          takes the axis sum per source first and forms Z inside the
+ *                          product (2 feeds x 2 axes, one shared beam, without
+ *                          MATVIS_FLAG_UNFUSED);
  *   MATVIS_PATH_FUSED      Z formed in LDS per 128-row super-tile pair;
  *   MATVIS_PATH_FUSED_ROWS Z formed once per (instance, k-split) for all of
  *                          129..256 rows (BF16X3);

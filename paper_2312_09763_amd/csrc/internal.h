@@ -209,13 +209,14 @@ int herk_occupancy(int prec);  // resident workgroups per CU
 hipError_t launch_worklist(int prec, const HerkArgs &a, int unit, hipStream_t s);
 hipError_t launch_herk(int prec, const HerkArgs &a, hipStream_t s);
 
-// Product with Z formed in LDS (kernels_herk_fused.hip); FP32 and BF16X3 only.
+// Product with Z formed in LDS (kernels_herk_fused.hip on FP32 and BF16X3,
+// kernels_herk_f64.hip on FP64).
 struct FusedArgs {
     const double *antc;      // [n_ant][3] centred ENU
     const int32_t *bidx;     // [n_ant]
     const double *freqs;     // [n_freq]
     const double *s_hat;     // [nslots][3][ld_src]
-    const void *B;           // sqrt(I) A, complex64 [n_inst][n_beam][n_feed][n_ax][ld_src]
+    const void *B;           // sqrt(I) A, complex64 (FP64: complex128) [n_inst][n_beam][n_feed][n_ax][ld_src]
     const int32_t *count;    // [nslots]
     int64_t ld_src;
     int32_t n_ant, n_feed, n_ax, n_beam;
@@ -236,6 +237,11 @@ hipError_t launch_herk_fused(int prec, const FusedArgs &a, hipStream_t s, int wh
 // whether the path of these arguments has a second (block-pair) launch
 bool fused_has_pairs(int prec, const FusedArgs &a);
 int herk_fused_occupancy(int prec);
+// FP64 product over sources (kernels_herk_f64.hip): whether a context takes it, its
+// items per (instance, k-split), and its launch (one workgroup per CU).
+bool f64_over_sources(int n_feed, int n_ax, int n_beam);
+int f64_items(int n_ant);
+hipError_t launch_herk_f64(const FusedArgs &a, hipStream_t s);
 // the library's k-split for a precision and product path (matvis_config.ksplit = 0)
 int64_t default_ksplit(int prec, bool over_sources, bool three_blocks);
 // product kernel launch_herk_fused picks (a matvis_product_path value, never Z_IN_HBM)

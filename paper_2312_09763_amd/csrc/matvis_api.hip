@@ -51,7 +51,7 @@ struct matvis_ctx {
     int pair_splits = 1;  // k-splits of ksplit columns (the sub-matrix product, which is not balanced)
     int n_bal = 1;        // items per k-split of the product launch that the splits are balanced for
     int64_t nblk_cap = 1;
-    bool fused = false;  // Z formed inside the product (FP32 / BF16X3)
+    bool fused = false;  // Z formed inside the product (FP32, BF16X3, or FP64 over sources)
 
     // device scratch
     double *xeq = nullptr, *rot = nullptr, *antc = nullptr, *s_hat = nullptr, *za_az = nullptr, *vacc = nullptr;
@@ -273,9 +273,12 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
     // the load imbalance at the end of each product launch and a pass of the
     // reduction (on the 3.1M-pixel polarised sky one chunk instead of twelve was
     // 79.5 -> 71.7 ms per call of 8 instances).
-    c->fused = prec != P64 && !(cfg->flags & MATVIS_FLAG_UNFUSED);
+    const bool over64 = prec == P64 && f64_over_sources(cfg->n_feed, cfg->n_ax, cfg->n_beam);
+    c->fused = (prec != P64 || over64) && !(cfg->flags & MATVIS_FLAG_UNFUSED);
+    // (FP64 keeps the chunk and the batch of a Z in device memory, which its
+    // sub-matrix product still writes.)
     c->chunk = cfg->src_chunk > 0 ? std::min<int64_t>(cfg->src_chunk, cfg->max_src)
-                                  : std::min<int64_t>(cfg->max_src, (int64_t)1 << (c->fused ? 22 : 18));
+                                  : std::min<int64_t>(cfg->max_src, (int64_t)1 << (c->fused && prec != P64 ? 22 : 18));
     c->ldz = round_up((int64_t)cfg->n_ax * c->chunk, kColPad);
     // Columns per work item.  FP32 accumulators see ksplit / 2 sequential MFMA
     // updates per item; 2048 keeps that rounding near 2e-6 of the Cauchy-Schwarz
@@ -289,7 +292,8 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
     // benchmark's ~50 000 visible columns it gives three splits per instance
     // instead of four (fewer items and partials: 1.4 % of its step).
     const bool over_sources =
-        c->fused && fused_path(prec, cfg->n_feed, cfg->n_ax, cfg->n_beam, cfg->n_ant, c->Np) == MATVIS_PATH_SOURCES;
+        c->fused && prec != P64 &&
+        fused_path(prec, cfg->n_feed, cfg->n_ax, cfg->n_beam, cfg->n_ant, c->Np) == MATVIS_PATH_SOURCES;
     if (over_sources) c->Np = (int)round_up(c->N, 2 * c->st);  // whole blocks of 128 antennas x 2 feeds
     // FP32 product over sources: 8192 (err_CS 2.9e-6 on the benchmark instance,
     // against 0.8e-6 at 2048 and 1.5e-6 at 4096; the step 28.7 -> 27.3 ms).
@@ -297,14 +301,15 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
     // against 2.8e-6 at 4096 on the 350-antenna diffuse sky, with half the partials:
     // its reduction went from 0.82 to 0.46 ms per two instances)
     const bool three_blocks =
-        c->fused && fused_path(prec, cfg->n_feed, cfg->n_ax, cfg->n_beam, cfg->n_ant, c->Np) == MATVIS_PATH_FUSED_BLOCKS;
+        c->fused && prec != P64 &&
+        fused_path(prec, cfg->n_feed, cfg->n_ax, cfg->n_beam, cfg->n_ant, c->Np) == MATVIS_PATH_FUSED_BLOCKS;
     c->ksplit = cfg->ksplit > 0 ? cfg->ksplit : default_ksplit(prec, over_sources, three_blocks);
     c->max_splits = c->pair_splits = (int)((c->ldz + c->ksplit - 1) / c->ksplit);
     // batch: all channels of a few times, enough instances to fill the GPU with
     // work items while keeping Z within a fixed share of device memory
     c->nfb = cfg->batch_freq > 0 ? std::min(cfg->batch_freq, cfg->max_freq) : std::min(cfg->max_freq, 16);
     // per-instance scratch that scales with the batch: Z (unfused only) and the k-split partials
-    size_t zinst = (c->fused ? 0 : (size_t)c->Np * c->ldz * cbytes(prec)) +
+    size_t zinst = (c->fused && prec != P64 ? 0 : (size_t)c->Np * c->ldz * cbytes(prec)) +
                    (size_t)c->max_splits * c->Np * c->Np * cbytes(prec);
     size_t budget = (size_t)12 << 30;
     int ntb_auto = (int)std::max<size_t>(1, budget / std::max<size_t>(1, zinst * c->nfb));
@@ -315,7 +320,8 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
     int64_t nblk_total = std::max<int64_t>(c->nblk_cap * c->ntb, (cfg->max_src + 255) / 256);
     int occ = std::max(1, herk_occupancy(prec));
     c->herk_grid = std::max(8, (c->n_cu * occ / 8) * 8);
-    if (c->fused) c->fused_grid = std::max(8, (c->n_cu * std::max(1, herk_fused_occupancy(prec)) / 8) * 8);
+    if (c->fused)
+        c->fused_grid = std::max(8, (c->n_cu * (prec == P64 ? 1 : std::max(1, herk_fused_occupancy(prec))) / 8) * 8);
     // Room for the k-splits that k_worklist adds when a batch alone does not fill the
     // grid: up to a grid's worth of items over the batch's instances, as long as the
     // partials stay within 1 GiB (or what the plain splits need).
@@ -323,6 +329,7 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
         const int nb = c->Np / c->st;
         const int grid = c->fused ? c->fused_grid : c->herk_grid;
         c->n_bal = !c->fused ? nb * (nb + 1) / 2
+                   : prec == P64 ? f64_items(cfg->n_ant)
                    : over_sources ? c->Np / (2 * c->st)
                    : three_blocks ? 3
                    : prec == PB3 && nb == 2 ? 1  // one item holds both row blocks
@@ -534,7 +541,9 @@ matvis_status enqueue_simulate(matvis_ctx *c, const double *antpos, const int32_
                     fa.work = c->work;
                     fa.grid = c->fused_grid;
                     fa.tile = g.tile;
-                    if (c->profiling && fused_has_pairs(prec, fa)) {  // time the two launches apart
+                    if (prec == P64) {
+                        STEP(c, MATVIS_STEP_HERK, s, launch_herk_f64(fa, s));
+                    } else if (c->profiling && fused_has_pairs(prec, fa)) {  // time the two launches apart
                         STEP(c, MATVIS_STEP_HERK, s, launch_herk_fused(prec, fa, s, FUSED_FIRST));
                         STEP(c, MATVIS_STEP_HERK_PAIRS, s, launch_herk_fused(prec, fa, s, FUSED_PAIRS));
                     } else {
@@ -820,10 +829,11 @@ matvis_status matvis_set_pairs(matvis_ctx *c, const int32_t *pair_a, const int32
     if ((st = dalloc(c, &c->pr_vacc, sizeof(double) * 2 * (size_t)B_cap * n_pair * nf * nf)) != MATVIS_OK) return st;
     // Fused contexts: a sub-matrix tile reuses a formed Z row only within its 32
     // rows, so forming Z once per batch in device memory is faster whenever it
-    // fits a fixed budget; otherwise the tiles form their rows in the stages.
+    // fits a fixed budget; otherwise the tiles form their rows in the stages (FP64
+    // always has it: its batch is sized for one).
     if (c->fused) {
         const size_t zplane = (g.precision == PB3 ? (size_t)4 : cbytes(g.precision)) * B_cap * c->Np * c->ldz;
-        if (zplane * (g.precision == PB3 ? 2 : 1) <= ((size_t)8 << 30)) {
+        if (g.precision == P64 || zplane * (g.precision == PB3 ? 2 : 1) <= ((size_t)8 << 30)) {
             if ((st = dalloc(c, &c->pr_Z, zplane)) != MATVIS_OK) return st;
             if (g.precision == PB3 && (st = dalloc(c, &c->pr_Z_lo, zplane)) != MATVIS_OK) return st;
         }
@@ -864,9 +874,9 @@ matvis_status matvis_set_surrogate(matvis_ctx *c, const float *params, double nu
 
 int32_t matvis_product_path_of(const matvis_ctx *c) {
     if (!c) return MATVIS_EINVAL;
-    if (!c->fused) return MATVIS_PATH_Z_IN_HBM;
+    if (!c->fused || c->cfg.precision == MATVIS_FP64) return MATVIS_PATH_Z_IN_HBM;
     const matvis_config &g = c->cfg;
-    return fused_path(g.precision == MATVIS_FP32 ? P32 : g.precision == MATVIS_BF16X3 ? PB3 : P64, g.n_feed, g.n_ax,
+    return fused_path(g.precision == MATVIS_FP32 ? P32 : PB3, g.n_feed, g.n_ax,
                       g.n_beam, g.n_ant, c->Np);
 }
 

@@ -24,8 +24,9 @@ def test_few_sources_over_many_splits(precision, workload, n_ant, n_src):
     say(f"splits: {precision}, workload {workload}, {n_ant} antennas, {n_src} sources")
     # capacities above the call's own sizes: the splits are planned from the visible counts
     cfg = mv.config_for(wl, precision, max_time=5, max_freq=3, max_src=n_src + 700)
+    d = mv.device_inputs(wl, precision)
     with mv.Context(cfg) as ctx:
-        V = ctx.simulate(**mv.device_inputs(wl, precision)).cpu().numpy().astype(np.complex128)
+        V = ctx.simulate(**d).cpu().numpy().astype(np.complex128)
         ctx.finish()
     V = V.reshape((-1,) + V.shape[2:])
     assert np.array_equal(V, np.conj(np.transpose(V, (0, 2, 1, 4, 3))))
