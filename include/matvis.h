@@ -52,8 +52,11 @@ typedef enum {
 
 /* Arithmetic of step (v), V = Z Z^H.
  *   FP64  : complex128 beams, Z, products and output;
- *   FP32  : complex64 beams and Z, FP32 MFMA products accumulated in FP32
- *           over bounded source chunks, chunks combined in FP64, complex64 out;
+ *   FP32  : complex64 beams and Z, FP32 products accumulated in FP32 over bounded
+ *           source chunks, chunks combined in FP64, complex64 out (on
+ *           MATVIS_PATH_SOURCES and _FUSED_BLOCKS every FP32 operand is split
+ *           exactly into three bf16 terms and multiplied on bf16 MFMA, with
+ *           smaller error than FP32 MFMA; elsewhere FP32 MFMA);
  *   BF16X3: Z in FP32 split into bf16 hi + lo parts, V ~ hi hi^T + hi lo^T +
  *           lo hi^T on bf16 MFMA with FP32 accumulation, complex64 out.
  * In every mode the rotation and the phase range reduction are FP64. */
@@ -101,7 +104,7 @@ typedef struct {
                              MATVIS_PATH_SOURCES with BF16X3: 0 puts each source's
                              coherency weight on the rows only (the plain fringe rows
                              of the other block as columns), 1 splits it as square
-                             roots over both sides (FP32 always uses the latter).
+                             roots over both sides (FP32 always uses the former).
                              Bit 6: 16 sources per stage instead of 32 on
                              MATVIS_PATH_FUSED_BLOCKS with BF16X3.
                              Bits 0-3 and 6 only reschedule work; bit 4 changes

@@ -237,6 +237,11 @@ hipError_t launch_herk_fused(int prec, const FusedArgs &a, hipStream_t s, int wh
 // whether the path of these arguments has a second (block-pair) launch
 bool fused_has_pairs(int prec, const FusedArgs &a);
 int herk_fused_occupancy(int prec);
+// FP32 products on bf16 matrix cores (kernels_herk_x6.hip): the launches of
+// launch_herk_fused for FP32.
+hipError_t launch_coh_x6(const FusedArgs &a, hipStream_t s);    // diagonal blocks, product over sources
+hipError_t launch_pairs_x6(const FusedArgs &a, hipStream_t s);  // its block pairs
+hipError_t launch_blk3_x6(const FusedArgs &a, hipStream_t s);   // scalar rows in three blocks
 // FP64 product over sources (kernels_herk_f64.hip): whether a context takes it, its
 // items per (instance, k-split), and its launch (one workgroup per CU).
 bool f64_over_sources(int n_feed, int n_ax, int n_beam);

@@ -24,35 +24,16 @@
 // Per source the item reads 24 B of direction and 8 n_feed n_ax B of beam;
 // everything else is arithmetic.  Partials go to the same slots as the
 // unfused product and are summed by k_reduce.
-#include "matvis.h"
-#include "internal.h"
 #include <type_traits>
+
+#include "herk_tiles.h"
+#include "matvis.h"
 
 namespace mv {
 
 namespace {
 
-constexpr int kST = 128, kWT = 64, kKC = 32, kTI = 4;
-
-__device__ inline int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
-
-// Row of a forming thread (8 threads per row, two sources each): a wave's 8 rows
-// in the order 0, 4, 1, 5, 2, 6, 3, 7, so the two rows that 16 consecutive
-// lanes write are 4 rows (576 bytes) apart and fall in disjoint LDS banks.
-__device__ inline int wrow(int t) {
-    const int g = (t >> 3) & 7;
-    return ((t >> 6) << 3) + (((g & 1) << 2) | (g >> 1));
-}
-
-// The same for 160-byte rows: rows 0, 2, 1, 3, 4, 6, 5, 7 (two rows 320 bytes, 16
-// banks, apart)
-__device__ inline int wrow160(int t) {
-    const int g = (t >> 3) & 7;
-    return ((t >> 6) << 3) + (g & 4) + ((g & 1) << 1) + ((g >> 1) & 1);
-}
-
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
+constexpr int kWT = 64, kKC = 32;
 
 // packed (hi, lo) bf16 words of one complex64 value: hi = bf16(z), lo = bf16(z - hi),
 // both round-to-nearest-even (v_cvt_pk_bf16_f32 on gfx950)
@@ -79,12 +60,6 @@ struct FL {
     static constexpr int RS = kKC * EBP * PLANES + 16;    // LDS row stride
     static constexpr int BUF = 2 * kST * RS;              // one stage buffer (rows of I and J)
     static constexpr int TAB = 2 * kST;                   // antenna table entries (rows of I and J, n_feed = 1)
-};
-
-struct AntEntry {
-    double ux, uy, uz;  // (nu / c) x_a
-    int b;              // beam index, -1 for padding rows
-    int pad;
 };
 
 // ---------------------------------------------------------------------------
@@ -517,29 +492,11 @@ __global__ void __launch_bounds__(512, 1) k_herk_fused(FusedArgs a) {
 // The column operand carries the rotation here: im += a . (-b_im, b_re).
 // ---------------------------------------------------------------------------
 
-// the column fragment rotated for the imaginary part: (re, im) -> (-im, re) per bf16 pair
-__device__ inline u32x4 bf16_rot_col(u32x4 v) {
-    u32x4 r;
-    for (int q = 0; q < 4; q++) r[q] = __builtin_amdgcn_alignbit(v[q], v[q], 16) ^ 0x00008000u;
-    return r;
-}
-
-__device__ __forceinline__ void mfma_pair(const u32x4 &a, const u32x4 &b, const u32x4 &w, f32x4 &re, f32x4 &im) {
-    re = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), re, 0, 0,
-                                                 0);
-    im = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, w), im, 0, 0,
-                                                 0);
-}
-
 // Staged-row geometry of the two-block kernels: RS bytes per row, hi plane
 // then lo plane of PLANEB bytes each, NKS k-steps of 16 complex per stage.
 // Operand reads are 16 bytes per lane from 16 rows at once; measured on the
 // LDS, 160-byte rows serve them without bank conflicts and 144-byte rows with
 // half of their cycles in conflicts, so 160 bytes where the stage buffers fit.
-template <int RS_, int PLANEB_, int NKS_>
-struct RowGeom {
-    static constexpr int RS = RS_, PLANEB = PLANEB_, NKS = NKS_;
-};
 typedef RowGeom<FL<PB3>::RS, FL<PB3>::PLANEB, kKC / 16> GeomPair;  // 32 complex per stage
 typedef RowGeom<16 * 4 * 2 + 16, 16 * 4, 1> GeomCoh;               // 16 complex per stage
 typedef RowGeom<16 * 4 * 2 + 32, 16 * 4, 1> GeomCoh3;              // the same in 160-byte rows
@@ -584,89 +541,6 @@ __device__ __forceinline__ void consume_sq_b3(const unsigned char *buf, int rb, 
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-}
-
-// Row sets of the triangle waves and the first accumulator slot of each row
-// (row r of a set holds columns 0..r in consecutive slots).  On a diagonal
-// block the column operand of column c is the row operand of row c (same
-// rows, same lane layout), so a wave loads only the columns that are not its
-// own rows, and none right of its last row.  order[] interleaves loaded and
-// reused columns so every load has at least one column of products to hide in.
-template <int S>
-struct TriSet {
-    static constexpr int NR = 4;
-    static constexpr int r[4] = {S == 0 ? 0 : 2, S == 0 ? 7 : 5, S == 0 ? 1 : 3, S == 0 ? 6 : 4};
-    static constexpr int base[4] = {0, r[0] + 1, r[0] + r[1] + 2, r[0] + r[1] + r[2] + 3};
-    static constexpr int ncol = S == 0 ? 8 : 6;
-    static constexpr int order[8] = {S == 0 ? 0 : 2, S == 0 ? 2 : 0, S == 0 ? 1 : 3, S == 0 ? 3 : 1,
-                                     S == 0 ? 6 : 4, S == 0 ? 4 : 5, S == 0 ? 7 : -1, S == 0 ? 5 : -1};
-    // row slot holding column c, or -1 when the column is loaded
-    static constexpr int slot(int c) { return r[0] == c ? 0 : r[1] == c ? 1 : r[2] == c ? 2 : r[3] == c ? 3 : -1; }
-    // first position at or after p whose column is loaded, or -1
-    static constexpr int next_loaded(int p) {
-        return p >= ncol ? -1 : slot(order[p]) < 0 ? p : next_loaded(p + 1);
-    }
-};
-
-// Two-row sets {S, 7 - S} of a 128-row triangle (nine tiles each), columns in
-// natural order; rows S and 7 - S double as columns S and 7 - S.
-template <int S>
-struct TriPair {
-    static constexpr int NR = 2;
-    static constexpr int r[2] = {S, 7 - S};
-    static constexpr int base[2] = {0, S + 1};
-    static constexpr int ncol = 8 - S;
-    static constexpr int order[8] = {0, 1, 2, 3, 4, 5, 6, 7};
-    static constexpr int slot(int c) { return c == r[0] ? 0 : c == r[1] ? 1 : -1; }
-    static constexpr int next_loaded(int p) {
-        return p >= ncol ? -1 : slot(order[p]) < 0 ? p : next_loaded(p + 1);
-    }
-};
-
-// A tile set passed as a value (to pick a set at run time among instantiations)
-template <typename T>
-struct SetTag {
-    typedef T type;
-};
-
-// Row S alone of a two-row set, when row 7 - S lies wholly past the antennas of
-// a short last block (its tiles are neither multiplied nor stored).
-template <int S>
-struct TriSingle {
-    static constexpr int NR = 1;
-    static constexpr int r[1] = {S};
-    static constexpr int base[1] = {0};
-    static constexpr int ncol = S + 1;
-    static constexpr int order[8] = {0, 1, 2, 3, 4, 5, 6, 7};
-    static constexpr int slot(int c) { return c == r[0] ? 0 : -1; }
-    static constexpr int next_loaded(int p) {
-        return p >= ncol ? -1 : slot(order[p]) < 0 ? p : next_loaded(p + 1);
-    }
-};
-
-// Row sets of the triangle waves on a short diagonal block of at most 96
-// antennas (six tile rows): {5, 0, 3} (eleven tiles) and {4, 1, 2} (ten).
-template <int S>
-struct TriSet6 {
-    static constexpr int NR = 3;
-    static constexpr int r[3] = {S == 0 ? 5 : 4, S == 0 ? 0 : 1, S == 0 ? 3 : 2};
-    static constexpr int base[3] = {0, r[0] + 1, r[0] + r[1] + 2};
-    static constexpr int ncol = S == 0 ? 6 : 5;
-    static constexpr int order[6] = {S == 0 ? 0 : 1, S == 0 ? 1 : 0, S == 0 ? 3 : 2,
-                                     S == 0 ? 2 : 3, S == 0 ? 5 : 4, S == 0 ? 4 : -1};
-    static constexpr int slot(int c) { return r[0] == c ? 0 : r[1] == c ? 1 : r[2] == c ? 2 : -1; }
-    static constexpr int next_loaded(int p) {
-        return p >= ncol ? -1 : slot(order[p]) < 0 ? p : next_loaded(p + 1);
-    }
-};
-
-// Calls f(slot, row, column) for every tile of a triangle row set.
-template <typename T, typename F>
-__device__ __forceinline__ void for_tri_tiles(F f) {
-#pragma unroll
-    for (int k = 0; k < T::NR; k++)
-#pragma unroll
-        for (int c = 0; c <= T::r[k]; c++) f(T::base[k] + c, T::r[k], c);
 }
 
 // One 128-row diagonal triangle starting at LDS row o: tiles (r, c), c <= r, r in the set.
@@ -721,66 +595,6 @@ __device__ __forceinline__ void consume_tri_b3(const unsigned char *buf, int o, 
             for (int k = 0; k < NR; k++)
                 if (T::r[k] == c) mfma_pair(al[k], bl, wl, re[T::base[k] + c], im[T::base[k] + c]);
             __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-}
-
-// FP32 forms of the two wave shapes on a stage of 16 complex columns (one
-// complex64 per element, re/im interleaved): per 4-deep k group,
-// re += a.re b.re + a.im b.im and im += a.im b.re - a.re b.im on
-// v_mfma_f32_16x16x4f32, one complex element per lane.
-template <typename L, int NACC, int NR = kTI, int NC = kTI>
-__device__ __forceinline__ void consume_sq_f32(const unsigned char *buf, int rb, int cb, int l16, int lk,
-                                               f32x4 (&re)[NACC], f32x4 (&im)[NACC]) {
-#pragma unroll
-    for (int kk = 0; kk < 16; kk += 4) {
-        float2 av[NR], bv[NC];
-#pragma unroll
-        for (int i = 0; i < NR; i++) av[i] = *(const float2 *)(buf + (16 * (rb + i) + l16) * L::RS + (kk + lk) * 8);
-#pragma unroll
-        for (int j = 0; j < NC; j++) bv[j] = *(const float2 *)(buf + (16 * (cb + j) + l16) * L::RS + (kk + lk) * 8);
-#pragma unroll
-        for (int i = 0; i < NR; i++) {
-            const float nre = -av[i].x;
-#pragma unroll
-            for (int j = 0; j < NC; j++) {
-                re[i * kTI + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i].x, bv[j].x, re[i * kTI + j], 0, 0, 0);
-                im[i * kTI + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i].y, bv[j].x, im[i * kTI + j], 0, 0, 0);
-            }
-#pragma unroll
-            for (int j = 0; j < NC; j++) {
-                re[i * kTI + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i].y, bv[j].y, re[i * kTI + j], 0, 0, 0);
-                im[i * kTI + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(nre, bv[j].y, im[i * kTI + j], 0, 0, 0);
-            }
-        }
-    }
-}
-
-template <typename L, typename T, int NACC>
-__device__ __forceinline__ void consume_tri_f32(const unsigned char *buf, int o, int l16, int lk, f32x4 (&re)[NACC],
-                                                f32x4 (&im)[NACC]) {
-    constexpr int NR = T::NR;
-#pragma unroll
-    for (int kk = 0; kk < 16; kk += 4) {
-        const unsigned char *p0 = buf + (o + l16) * L::RS + (kk + lk) * 8;
-        float2 av[NR];
-#pragma unroll
-        for (int k = 0; k < NR; k++) av[k] = *(const float2 *)(p0 + 16 * T::r[k] * L::RS);
-#pragma unroll
-        for (int q = 0; q < T::ncol; q++) {
-            const int c = T::order[q];
-            const int kc = T::slot(c);
-            // a column that is one of the wave's rows is already in registers
-            const float2 b = kc >= 0 ? av[kc] : *(const float2 *)(p0 + 16 * c * L::RS);
-#pragma unroll
-            for (int k = 0; k < NR; k++)
-                if (T::r[k] >= c) {
-                    f32x4 &r = re[T::base[k] + c], &m = im[T::base[k] + c];
-                    r = __builtin_amdgcn_mfma_f32_16x16x4f32(av[k].x, b.x, r, 0, 0, 0);
-                    m = __builtin_amdgcn_mfma_f32_16x16x4f32(av[k].y, b.x, m, 0, 0, 0);
-                    r = __builtin_amdgcn_mfma_f32_16x16x4f32(av[k].y, b.y, r, 0, 0, 0);
-                    m = __builtin_amdgcn_mfma_f32_16x16x4f32(-av[k].x, b.y, m, 0, 0, 0);
-                }
         }
     }
 }
@@ -1003,8 +817,8 @@ __global__ void __launch_bounds__(512, 1) k_herk_b3_pair(FusedArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Polarised products with one shared beam (BF16X3 or FP32, 2 feeds x 2 axes,
-// more than 64 antennas).  With Z[(a,p),(m,k)] = B_pk(m) F_a(m) (F the fringe factor of
+// Polarised products with one shared beam (BF16X3 here, FP32 in kernels_herk_x6.hip;
+// 2 feeds x 2 axes, more than 64 antennas).  With Z[(a,p),(m,k)] = B_pk(m) F_a(m) (F the fringe factor of
 // antenna a, B = sqrt(I) A the same for every antenna), the sum over the
 // axis index k can be taken per source first:
 //   V[(a,p),(b,q)] = sum_m F_a(m) conj(F_b(m)) C_pq(m),
@@ -1035,11 +849,10 @@ struct CohSrc {
     float lx, ly;    // C10 / sqrt C00 (all four 0 past the split)
 };
 
-template <int PREC, bool OFF, int SQ_ANT = 96, bool SHORT = false>
+template <bool OFF, int SQ_ANT = 96, bool SHORT = false>
 __global__ void __launch_bounds__(512, 1) k_herk_coh(FusedArgs a) {
-    // 144-byte rows: hi + lo bf16 planes, or one complex64 plane (FP32); 160 bytes
-    // on the three-plane diagonal items of BF16X3
-    constexpr bool R160 = !OFF && PREC == PB3;
+    // rows of hi + lo bf16 planes: 144 bytes, 160 on the three-plane diagonal items
+    constexpr bool R160 = !OFF;
     typedef typename std::conditional<R160, GeomCoh3, GeomCoh>::type L;
     constexpr int RS = L::RS;
     constexpr int SPS = 16;                 // sources per stage
@@ -1198,29 +1011,15 @@ __global__ void __launch_bounds__(512, 1) k_herk_coh(FusedArgs a) {
                     const float r = (float)__builtin_amdgcn_fract(p);
                     const float fi = __builtin_amdgcn_sinf(-r);
                     const float fr = __builtin_amdgcn_cosf(-r);
-                    if constexpr (PREC == PB3) {
-                        split2(w[q].s0 * fr, w[q].s0 * fi, h[0][q], l[0][q]);
-                        split2(w[q].s1 * fr, w[q].s1 * fi, h[1][q], l[1][q]);
-                        split2(w[q].lx * fr - w[q].ly * fi, w[q].lx * fi + w[q].ly * fr, h[2][q], l[2][q]);
-                    } else {  // FP32: (re, im) words of each plane
-                        h[0][q] = __float_as_uint(w[q].s0 * fr);
-                        l[0][q] = __float_as_uint(w[q].s0 * fi);
-                        h[1][q] = __float_as_uint(w[q].s1 * fr);
-                        l[1][q] = __float_as_uint(w[q].s1 * fi);
-                        h[2][q] = __float_as_uint(w[q].lx * fr - w[q].ly * fi);
-                        l[2][q] = __float_as_uint(w[q].lx * fi + w[q].ly * fr);
-                    }
+                    split2(w[q].s0 * fr, w[q].s0 * fi, h[0][q], l[0][q]);
+                    split2(w[q].s1 * fr, w[q].s1 * fi, h[1][q], l[1][q]);
+                    split2(w[q].lx * fr - w[q].ly * fi, w[q].lx * fi + w[q].ly * fr, h[2][q], l[2][q]);
                 }
 #pragma unroll
                 for (int pl = 0; pl < 3; pl++) {
-                    if constexpr (PREC == PB3) {
-                        unsigned char *row = buf + (pl * kST + as) * RS + mp * 8;
-                        *(uint2 *)row = make_uint2(h[pl][0], h[pl][1]);
-                        *(uint2 *)(row + L::PLANEB) = make_uint2(l[pl][0], l[pl][1]);
-                    } else {  // two complex64 of sources 2 mp, 2 mp + 1
-                        unsigned char *row = buf + (pl * kST + as) * RS + mp * 16;
-                        *(u32x4 *)row = u32x4{h[pl][0], l[pl][0], h[pl][1], l[pl][1]};
-                    }
+                    unsigned char *row = buf + (pl * kST + as) * RS + mp * 8;
+                    *(uint2 *)row = make_uint2(h[pl][0], h[pl][1]);
+                    *(uint2 *)(row + L::PLANEB) = make_uint2(l[pl][0], l[pl][1]);
                 }
             }
         };
@@ -1258,18 +1057,12 @@ __global__ void __launch_bounds__(512, 1) k_herk_coh(FusedArgs a) {
                 }
 #pragma unroll
                 for (int v = 0; v < 2; v++) {
-                    if constexpr (PREC == PB3) {
-                        uint32_t h0, l0, h1, l1;
-                        split2(vr[v][0], vi[v][0], h0, l0);
-                        split2(vr[v][1], vi[v][1], h1, l1);
-                        unsigned char *rp = buf + ((pl0 + v) * kST + row) * RS + mp * 8;
-                        *(uint2 *)rp = make_uint2(h0, h1);
-                        *(uint2 *)(rp + L::PLANEB) = make_uint2(l0, l1);
-                    } else {
-                        unsigned char *rp = buf + ((pl0 + v) * kST + row) * RS + mp * 16;
-                        *(u32x4 *)rp = u32x4{__float_as_uint(vr[v][0]), __float_as_uint(vi[v][0]),
-                                             __float_as_uint(vr[v][1]), __float_as_uint(vi[v][1])};
-                    }
+                    uint32_t h0, l0, h1, l1;
+                    split2(vr[v][0], vi[v][0], h0, l0);
+                    split2(vr[v][1], vi[v][1], h1, l1);
+                    unsigned char *rp = buf + ((pl0 + v) * kST + row) * RS + mp * 8;
+                    *(uint2 *)rp = make_uint2(h0, h1);
+                    *(uint2 *)(rp + L::PLANEB) = make_uint2(l0, l1);
                 }
             }
         };
@@ -1299,11 +1092,8 @@ __global__ void __launch_bounds__(512, 1) k_herk_coh(FusedArgs a) {
         const int o_rb = o_rp * 8 + 4 * ((wave & 3) >> 1), o_cb = o_cp * 8 + 4 * (wave & 1);
         auto consume = [&](const unsigned char *buf) {
             if constexpr (OFF) {
-                if constexpr (PREC == PB3)
-                    consume_sq_b3<L>(buf, o_rb, o_cb, l16, lk, acc_re, acc_im);
-                else
-                    consume_sq_f32<L>(buf, o_rb, o_cb, l16, lk, acc_re, acc_im);
-            } else if constexpr (PREC == PB3) {
+                consume_sq_b3<L>(buf, o_rb, o_cb, l16, lk, acc_re, acc_im);
+            } else {
                 if (short_blk && sq)
                     consume_sq_b3<L, NACC, 3, 3>(buf, 16 + sh_r0, sh_c0, l16, lk, acc_re, acc_im);
                 else if (short_blk && tri_s == 0)
@@ -1316,19 +1106,6 @@ __global__ void __launch_bounds__(512, 1) k_herk_coh(FusedArgs a) {
                     consume_tri_b3<L, TriSet<0>>(buf, tri_o, l16, lk, acc_re, acc_im);
                 else
                     consume_tri_b3<L, TriSet<1>>(buf, tri_o, l16, lk, acc_re, acc_im);
-            } else {
-                if (short_blk && sq)
-                    consume_sq_f32<L, NACC, 3, 3>(buf, 16 + sh_r0, sh_c0, l16, lk, acc_re, acc_im);
-                else if (short_blk && tri_s == 0)
-                    consume_tri_f32<L, TriSet6<0>>(buf, tri_o, l16, lk, acc_re, acc_im);
-                else if (short_blk)
-                    consume_tri_f32<L, TriSet6<1>>(buf, tri_o, l16, lk, acc_re, acc_im);
-                else if (sq)
-                    consume_sq_f32<L>(buf, sq_rb, sq_cb, l16, lk, acc_re, acc_im);
-                else if (tri_s == 0)
-                    consume_tri_f32<L, TriSet<0>>(buf, tri_o, l16, lk, acc_re, acc_im);
-                else
-                    consume_tri_f32<L, TriSet<1>>(buf, tri_o, l16, lk, acc_re, acc_im);
             }
         };
 
@@ -1434,7 +1211,7 @@ __global__ void __launch_bounds__(512, 1) k_herk_coh(FusedArgs a) {
 // Rows are 160 bytes (conflict-free 16-byte operand reads), so two stages fill
 // the 160 KB of LDS; the antenna table and the per-source weights live in the
 // 32 unused bytes at the end of rows, which the forming never writes and the
-// multiply never reads.  Against k_herk_coh<PREC, true> (both operands weighted
+// multiply never reads.  Against k_herk_coh<true> (both operands weighted
 // by square roots of the coherency) that is a quarter fewer rows to scale and
 // split per stage.
 //
@@ -1750,16 +1527,15 @@ struct SclSrc {
     float g, pad;    // |B| (0 past the split)
 };
 
-// SPS_: sources per stage, 16 or (BF16X3, the default there) 32: a deeper
+// SPS_: sources per stage, 16 or (the default) 32: a deeper
 // stage halves the barriers and the per-stage operand loads per source (3-5 %
 // on the 350-antenna diffuse sky), the LDS holds 147 KB; the MFMAs accumulate
 // in the same source order either way.
-template <int PREC, int SQ_ROWS = 96, int SPS_ = 16>
+template <int SQ_ROWS = 96, int SPS_ = 16>
 __global__ void __launch_bounds__(512, 1) k_herk_blk3(FusedArgs a) {
-    static_assert(SPS_ == 16 || (SPS_ == 32 && PREC == PB3), "16 sources per stage, or 32 on BF16X3");
-    // 288- and 160-byte rows on BF16X3 (conflict-free operand reads), 144 on FP32
-    typedef typename std::conditional<SPS_ == 32, GeomPair3,
-                                      typename std::conditional<PREC == PB3, GeomCoh3, GeomCoh>::type>::type L;
+    static_assert(SPS_ == 16 || SPS_ == 32, "16 or 32 sources per stage");
+    // 288- and 160-byte rows (conflict-free operand reads)
+    typedef typename std::conditional<SPS_ == 32, GeomPair3, GeomCoh3>::type L;
     constexpr int RS = L::RS;
     constexpr int SPS = SPS_;
     constexpr int RSTEP = 512 / SPS;  // rows between a thread's rows
@@ -1786,8 +1562,7 @@ __global__ void __launch_bounds__(512, 1) k_herk_blk3(FusedArgs a) {
     const int mp = tid % (SPS / 2);
     // 16-source stages: 8 threads per row, rows permuted as in the two-block kernels
     const int a0 = SPS == 32    ? (sq ? tid / (SPS / 2) : SQ_ROWS + (tid - 256) / (SPS / 2))
-                   : PREC == PB3 ? (sq ? wrow160(tid) : SQ_ROWS + wrow160(tid - 256))
-                                 : (sq ? wrow(tid) : SQ_ROWS + wrow(tid - 256));
+                                : (sq ? wrow160(tid) : SQ_ROWS + wrow160(tid - 256));
     const int sq_c0 = 4 * (wave & 1);
     const int tri_s = (wave - 4) & 3;
 
@@ -1888,17 +1663,12 @@ __global__ void __launch_bounds__(512, 1) k_herk_blk3(FusedArgs a) {
                     vi[q] = w[q].g * __builtin_amdgcn_sinf(-r);
                     vr[q] = w[q].g * __builtin_amdgcn_cosf(-r);
                 }
-                if constexpr (PREC == PB3) {
-                    uint32_t h0, l0, h1, l1;
-                    split2(vr[0], vi[0], h0, l0);
-                    split2(vr[1], vi[1], h1, l1);
-                    unsigned char *rp = buf + as * RS + mp * 8;
-                    *(uint2 *)rp = make_uint2(h0, h1);
-                    *(uint2 *)(rp + L::PLANEB) = make_uint2(l0, l1);
-                } else {
-                    *(u32x4 *)(buf + as * RS + mp * 16) =
-                        u32x4{__float_as_uint(vr[0]), __float_as_uint(vi[0]), __float_as_uint(vr[1]), __float_as_uint(vi[1])};
-                }
+                uint32_t h0, l0, h1, l1;
+                split2(vr[0], vi[0], h0, l0);
+                split2(vr[1], vi[1], h1, l1);
+                unsigned char *rp = buf + as * RS + mp * 8;
+                *(uint2 *)rp = make_uint2(h0, h1);
+                *(uint2 *)(rp + L::PLANEB) = make_uint2(l0, l1);
             }
         };
         auto produce = [&](unsigned char *buf, int stage) __attribute__((always_inline)) {
@@ -1916,17 +1686,11 @@ __global__ void __launch_bounds__(512, 1) k_herk_blk3(FusedArgs a) {
             }
         auto sq_n = [&](const unsigned char *buf, auto nr) __attribute__((always_inline)) {
             constexpr int NR = decltype(nr)::value;
-            if constexpr (PREC == PB3)
-                consume_sq_b3<L, 16, NR, kTI>(buf, 8 + sq_r0, sq_c0, l16, lk, acc_re, acc_im);
-            else
-                consume_sq_f32<L, 16, NR, kTI>(buf, 8 + sq_r0, sq_c0, l16, lk, acc_re, acc_im);
+            consume_sq_b3<L, 16, NR, kTI>(buf, 8 + sq_r0, sq_c0, l16, lk, acc_re, acc_im);
         };
         auto tri_n = [&](const unsigned char *buf, auto set) __attribute__((always_inline)) {
             typedef typename decltype(set)::type TS;
-            if constexpr (PREC == PB3)
-                consume_tri_b3<L, TS>(buf, tri_o, l16, lk, acc_re, acc_im);
-            else
-                consume_tri_f32<L, TS>(buf, tri_o, l16, lk, acc_re, acc_im);
+            consume_tri_b3<L, TS>(buf, tri_o, l16, lk, acc_re, acc_im);
         };
         auto consume = [&](const unsigned char *buf) __attribute__((always_inline)) {
             if (sq) {
@@ -2070,30 +1834,25 @@ hipError_t launch_herk_fused(int prec, const FusedArgs &a, hipStream_t s, int wh
             if (prec == PB3) {
                 if (nb > 1 || !has_short) {
                     if (split == 2)
-                        k_herk_coh<PB3, false, 64><<<a.grid, 512, 0, s>>>(a);
+                        k_herk_coh<false, 64><<<a.grid, 512, 0, s>>>(a);
                     else
-                        k_herk_coh<PB3, false, 96><<<a.grid, 512, 0, s>>>(a);
+                        k_herk_coh<false, 96><<<a.grid, 512, 0, s>>>(a);
                 }
-                if (has_short) k_herk_coh<PB3, false, 96, true><<<a.grid, 512, 0, s>>>(a);
+                if (has_short) k_herk_coh<false, 96, true><<<a.grid, 512, 0, s>>>(a);
             } else {
-                if (nb > 1 || !has_short) {
-                    if (split == 2)
-                        k_herk_coh<P32, false, 64><<<a.grid, 512, 0, s>>>(a);
-                    else
-                        k_herk_coh<P32, false, 96><<<a.grid, 512, 0, s>>>(a);
-                }
-                if (has_short) k_herk_coh<P32, false, 96, true><<<a.grid, 512, 0, s>>>(a);
+                const hipError_t e = launch_coh_x6(a, s);
+                if (e != hipSuccess) return e;
             }
         }
         if (pairs && a.n_rows_pad > 2 * kST) {  // pairs of antenna blocks
-            // bits 4-5 of the variant: 0 the one-sided-weight pair kernel (BF16X3), 1 the
-            // two-sided one; FP32 always takes the latter
+            // bits 4-5 of the variant: 0 the one-sided-weight pair kernel, 1 the two-sided
+            // one (FP32 has the former only)
             if (prec == PB3 && ((a.tile >> 4) & 3) == 0)
                 k_herk_pairs<<<a.grid, 512, 0, s>>>(a);
             else if (prec == PB3)
-                k_herk_coh<PB3, true><<<a.grid, 512, 0, s>>>(a);
+                k_herk_coh<true><<<a.grid, 512, 0, s>>>(a);
             else
-                k_herk_coh<P32, true><<<a.grid, 512, 0, s>>>(a);
+                return launch_pairs_x6(a, s);
         }
         return hipGetLastError();
     }
@@ -2102,25 +1861,20 @@ hipError_t launch_herk_fused(int prec, const FusedArgs &a, hipStream_t s, int wh
         if (!first) return hipSuccess;
         if (prec == PB3 && !(a.tile & 64)) {  // 32 sources per stage unless bit 6 asks for 16
             if (split == 2)
-                k_herk_blk3<PB3, 64, 32><<<a.grid, 512, 0, s>>>(a);
+                k_herk_blk3<64, 32><<<a.grid, 512, 0, s>>>(a);
             else if (split == 4)
-                k_herk_blk3<PB3, 128, 32><<<a.grid, 512, 0, s>>>(a);
+                k_herk_blk3<128, 32><<<a.grid, 512, 0, s>>>(a);
             else
-                k_herk_blk3<PB3, 96, 32><<<a.grid, 512, 0, s>>>(a);
+                k_herk_blk3<96, 32><<<a.grid, 512, 0, s>>>(a);
         } else if (prec == PB3) {
             if (split == 2)
-                k_herk_blk3<PB3, 64><<<a.grid, 512, 0, s>>>(a);
+                k_herk_blk3<64><<<a.grid, 512, 0, s>>>(a);
             else if (split == 4)
-                k_herk_blk3<PB3, 128><<<a.grid, 512, 0, s>>>(a);
+                k_herk_blk3<128><<<a.grid, 512, 0, s>>>(a);
             else
-                k_herk_blk3<PB3, 96><<<a.grid, 512, 0, s>>>(a);
+                k_herk_blk3<96><<<a.grid, 512, 0, s>>>(a);
         } else {
-            if (split == 2)
-                k_herk_blk3<P32, 64><<<a.grid, 512, 0, s>>>(a);
-            else if (split == 4)
-                k_herk_blk3<P32, 128><<<a.grid, 512, 0, s>>>(a);
-            else
-                k_herk_blk3<P32, 96><<<a.grid, 512, 0, s>>>(a);
+            return launch_blk3_x6(a, s);
         }
         return hipGetLastError();
     }

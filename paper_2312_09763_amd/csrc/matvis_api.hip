@@ -295,8 +295,9 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
         c->fused && prec != P64 &&
         fused_path(prec, cfg->n_feed, cfg->n_ax, cfg->n_beam, cfg->n_ant, c->Np) == MATVIS_PATH_SOURCES;
     if (over_sources) c->Np = (int)round_up(c->N, 2 * c->st);  // whole blocks of 128 antennas x 2 feeds
-    // FP32 product over sources: 8192 (err_CS 2.9e-6 on the benchmark instance,
-    // against 0.8e-6 at 2048 and 1.5e-6 at 4096; the step 28.7 -> 27.3 ms).
+    // FP32 product over sources: 8192.  Its accumulators round once per 16 sources, so
+    // the error hardly depends on it (2.3e-7 at 8192 and at 20480); 20480 would take 0.2 ms
+    // off the 32.5 ms of 128 antennas, 200 000 sources, 256 instances.
     // scalar rows in three blocks (BF16X3): 8192 columns per split (err_CS 3.5e-6
     // against 2.8e-6 at 4096 on the 350-antenna diffuse sky, with half the partials:
     // its reduction went from 0.82 to 0.46 ms per two instances)
