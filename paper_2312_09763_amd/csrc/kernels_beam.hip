@@ -49,28 +49,49 @@ __global__ void __launch_bounds__(256) k_interp(InterpArgs a, Batch bt) {
 }
 
 // [b][F][P] -> [b][P][Fs] with F = n_freq * ncomp, P = n_za * n_az and the run
-// stride Fs = F rounded up to even (16-byte aligned runs), 64 x 64 tiles through LDS.
-template <typename C>
+// stride Fs = F rounded up to even (16-byte aligned runs), in tiles of TF values by
+// 4096 / TF points through LDS.  Bound by HBM (read and write once); TF is the
+// smallest of 8, 16, 32, 64 that holds F, so that short runs fill the lanes of a
+// store too: 128 beams of 8 values on 130 320 points took 1.03 ms in 64 x 64
+// tiles and take 0.47 (2.1 GB at 4.5 TB/s).
+// Rows of the tile are padded to spread the TF values of a point over the banks.
+template <typename C, int TF>
 __global__ void __launch_bounds__(256) k_grid_interleave(const C *__restrict__ in, int F, int64_t P, C *__restrict__ out) {
+    constexpr int TP = 4096 / TF, PAD = TF < 32 ? 32 / TF : 1;
     const int Fs = (F + 1) & ~1;
-    __shared__ C tile[64][65];
+    __shared__ C tile[TF][TP + PAD];
     const int b = blockIdx.z;
-    const int64_t p0 = (int64_t)blockIdx.x * 64;
-    const int f0 = blockIdx.y * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    const C *src = in + (int64_t)b * F * P;
-    C *dst = out + (int64_t)b * Fs * P;
-    for (int r = ty; r < 64; r += 4) {
-        const int f = f0 + r;
-        const int64_t p = p0 + tx;
-        if (f < F && p < P) tile[r][tx] = src[(int64_t)f * P + p];
+    const int64_t p0 = (int64_t)blockIdx.x * TP;
+    const int f0 = blockIdx.y * TF;
+    const int nf = F - f0 < TF ? F - f0 : TF;
+    const int np = P - p0 < TP ? (int)(P - p0) : TP;
+    const C *src = in + ((int64_t)b * F + f0) * P + p0;
+    C *dst = out + ((int64_t)b * P + p0) * Fs + f0;
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        const int e = i * 256 + threadIdx.x, f = e / TP, p = e % TP;
+        if (f < nf && p < np) tile[f][p] = src[(int64_t)f * P + p];
     }
     __syncthreads();
-    for (int r = ty; r < 64; r += 4) {
-        const int64_t p = p0 + r;
-        const int f = f0 + tx;
-        if (f < F && p < P) dst[p * Fs + f] = tile[tx][r];
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        const int e = i * 256 + threadIdx.x, f = e % TF, p = e / TF;
+        if (f < nf && p < np) dst[(int64_t)p * Fs + f] = tile[f][p];
     }
+}
+
+template <typename C>
+void interleave(const C *grid, int n_beam, int F, int64_t P, C *T, hipStream_t s) {
+    const int tf = F <= 8 ? 8 : F <= 16 ? 16 : F <= 32 ? 32 : 64;
+    const dim3 g((unsigned)((P + 4096 / tf - 1) / (4096 / tf)), (unsigned)((F + tf - 1) / tf), (unsigned)n_beam);
+    if (tf == 8)
+        k_grid_interleave<C, 8><<<g, 256, 0, s>>>(grid, F, P, T);
+    else if (tf == 16)
+        k_grid_interleave<C, 16><<<g, 256, 0, s>>>(grid, F, P, T);
+    else if (tf == 32)
+        k_grid_interleave<C, 32><<<g, 256, 0, s>>>(grid, F, P, T);
+    else
+        k_grid_interleave<C, 64><<<g, 256, 0, s>>>(grid, F, P, T);
 }
 
 // Row weights of the 4-row za stencil folded onto the grid rows base..base+3:
@@ -147,33 +168,53 @@ __global__ void __launch_bounds__(256) k_stencil(InterpArgs a, Batch bt) {
     }
 }
 
-// A group of LPS lanes per (visible source, time slot of the batch, 4 channels
-// of the batch): a tap's interleaved run T[b][j][k][f .. f + 3][0 .. ncomp) is
-// 4 ncomp complex values, and lane l of the group reads its l-th 16-byte piece
+// Beams that one block of k_interp_tf evaluates its sources on.
+constexpr int kBeamGroup = 4;
+
+// Blocks of `spb` sources that one XCD may have to do of a slot with up to max_m.
+__host__ __device__ inline int64_t tf_blocks_per_xcd(int64_t max_m, int spb) {
+    return ((max_m + spb - 1) / spb + 7) / 8;
+}
+
+// A group of LPS lanes per (visible source, time slot of the batch, FG channels
+// of the batch): a tap's interleaved run T[b][j][k][f .. f + FG - 1][0 .. ncomp) is
+// FG ncomp complex values, and lane l of the group reads its l-th 16-byte piece
 // (two complex64 or one complex128), so a wave's load covers whole runs of
 // 64 / LPS sources.  The group reads the source's stencil from the scratch
-// k_stencil wrote (ST), or every lane forms it.
-template <typename R, int MODE, int NCOMP, bool ST>
+// k_stencil wrote (ST), or every lane forms it.  FG is 4, or 2 where the batch has
+// at most two channels: then every lane has values to read, and a store of 16
+// sources by 4 components covers whole 128-byte lines.
+//
+// Bound by what the 16 taps fetch past L2.  128 antennas with a beam each, 50 000
+// sources, 4 times of 2 channels: 2.50 ms with 4 channels a group (half the lanes
+// idle) and an eighth of all slots' source range to each XCD (half of it below the
+// horizon, so half the XCDs idle), 1.45 ms without these two faults, 1.02 ms in
+// groups of 4 beams (16: 1.11, 8: 1.03, 2: 1.05), which is 4.1 GB at 4.0 TB/s.  More
+// waves in flight (fewer registers, by launch bounds) were slower: 1.71 against 1.45 ms.
+template <typename R, int MODE, int NCOMP, bool ST, int FG>
 __global__ void __launch_bounds__(256) k_interp_tf(InterpArgs a, Batch bt) {
     typedef typename CplxOf<R>::T C;
-    constexpr int FG = 4;                            // channels per group
     constexpr int PER = 16 / sizeof(C);              // complex values per lane (16 bytes)
     constexpr int LPS = FG * NCOMP / PER;            // lanes per source
     // XCD-aware block order: workgroups go to the 8 XCDs round-robin by linear id,
-    // so each XCD is given one contiguous range of (channel group, slot, source
-    // block) work; neighbouring (sky-cell ordered) sources then share one L2 and
-    // the grid lines they have in common are fetched into it once.
-    const uint32_t gx = gridDim.x, gy = gridDim.y;
-    const uint32_t total = gx * gy * gridDim.z;
-    const uint32_t lin = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
-    const uint32_t xq = total / 8, xr = total % 8, xcd = lin % 8;
-    const uint32_t task = xcd * xq + (xcd < xr ? xcd : xr) + lin / 8;
-    const uint32_t bx = task % gx;
-    const int slot = (int)((task / gx) % gy);
-    const int fg = (int)(task / (gx * gy)) * FG;    // first channel of the group, relative to the batch
-    const int l = threadIdx.x % LPS;
-    const int64_t m = (int64_t)bx * (blockDim.x / LPS) + threadIdx.x / LPS;
+    // and each XCD is given one contiguous eighth of every slot's visible sources;
+    // neighbouring (sky-cell ordered) sources then share one L2 and the grid lines
+    // they have in common are fetched into it once, and the XCDs have equal work
+    // however many of the sources are up.  Groups of beams go outermost, so that the
+    // slots read a beam's grid from the MALL after its first.
+    const uint32_t i = blockIdx.x / 8, xcd = blockIdx.x % 8;
+    const uint32_t per = (uint32_t)tf_blocks_per_xcd(a.max_m, blockDim.x / LPS);
+    const int slot = (int)(i / per % (uint32_t)bt.ntb);
+    const uint32_t j = i / per / (uint32_t)bt.ntb;
+    const uint32_t ngf = (uint32_t)(bt.nfb + FG - 1) / FG;
+    const int fg = (int)(j % ngf) * FG;  // first channel of the group, relative to the batch
+    const int b0 = (int)(j / ngf) * kBeamGroup, b1 = b0 + kBeamGroup < a.n_beam ? b0 + kBeamGroup : a.n_beam;
     const int64_t M = a.count ? a.count[slot] : a.fixed_count;
+    const int64_t nb = (M + blockDim.x / LPS - 1) / (blockDim.x / LPS);  // blocks of this slot
+    const int64_t bx = nb * xcd / 8 + i % per;
+    if (bx >= nb * (xcd + 1) / 8) return;
+    const int l = threadIdx.x % LPS;
+    const int64_t m = bx * (blockDim.x / LPS) + threadIdx.x / LPS;
     if (m >= M || fg >= bt.nfb) return;
     const int nf = bt.nfb - fg < FG ? bt.nfb - fg : FG;
     constexpr int NT = MODE == BILINEAR ? 2 : 4;
@@ -217,7 +258,7 @@ __global__ void __launch_bounds__(256) k_interp_tf(InterpArgs a, Batch bt) {
         pm = pol_sqrt(a.flux[o], a.flux[o + a.stokes_stride], a.flux[o + 2 * a.stokes_stride],
                       a.flux[o + 3 * a.stokes_stride]);
     }
-    for (int b = 0; b < a.n_beam; b++) {
+    for (int b = b0; b < b1; b++) {
         const C *T = (const C *)a.grid + (int64_t)b * a.n_za * a.n_az * F + (int64_t)fabs0 * NCOMP + e0;
         R ax[PER], ay[PER];
         for (int p = 0; p < PER; p++) ax[p] = ay[p] = R(0);
@@ -282,28 +323,34 @@ __global__ void __launch_bounds__(256) k_interp_tf(InterpArgs a, Batch bt) {
     }
 }
 
+template <typename R, int MODE, bool ST, int FG>
+void launch_tf_fg(const InterpArgs &a, const Batch &bt, hipStream_t s) {
+    const int ncomp = a.n_feed * a.n_ax;
+    const int lps = FG * ncomp * (int)sizeof(typename CplxOf<R>::T) / 16;  // lanes per source
+    const int sources_per_block = 256 / lps;
+    const dim3 g((unsigned)(8 * tf_blocks_per_xcd(a.max_m, sources_per_block) * bt.ntb * ((bt.nfb + FG - 1) / FG) *
+                          ((a.n_beam + kBeamGroup - 1) / kBeamGroup)));
+    if (ncomp == 4)
+        k_interp_tf<R, MODE, 4, ST, FG><<<g, 256, 0, s>>>(a, bt);
+    else if (ncomp == 2)
+        k_interp_tf<R, MODE, 2, ST, FG><<<g, 256, 0, s>>>(a, bt);
+    else
+        k_interp_tf<R, MODE, 1, ST, FG><<<g, 256, 0, s>>>(a, bt);
+}
+
 template <typename R, int MODE>
 hipError_t launch_tf_mode(const InterpArgs &a, const Batch &bt, hipStream_t s) {
-    const int ncomp = a.n_feed * a.n_ax;
-    const int lps = 4 * ncomp * (int)sizeof(typename CplxOf<R>::T) / 16;  // lanes per source
-    const int sources_per_block = 256 / lps;
-    dim3 g((unsigned)((a.max_m + sources_per_block - 1) / sources_per_block), bt.n_inst / bt.nfb,
-           (unsigned)((bt.nfb + 3) / 4));
     if (a.stencil) {
         k_stencil<R, MODE><<<dim3((unsigned)((a.max_m + 255) / 256), (unsigned)bt.ntb), 256, 0, s>>>(a, bt);
-        if (ncomp == 4)
-            k_interp_tf<R, MODE, 4, true><<<g, 256, 0, s>>>(a, bt);
-        else if (ncomp == 2)
-            k_interp_tf<R, MODE, 2, true><<<g, 256, 0, s>>>(a, bt);
+        if (bt.nfb <= 2)
+            launch_tf_fg<R, MODE, true, 2>(a, bt, s);
         else
-            k_interp_tf<R, MODE, 1, true><<<g, 256, 0, s>>>(a, bt);
+            launch_tf_fg<R, MODE, true, 4>(a, bt, s);
     } else {
-        if (ncomp == 4)
-            k_interp_tf<R, MODE, 4, false><<<g, 256, 0, s>>>(a, bt);
-        else if (ncomp == 2)
-            k_interp_tf<R, MODE, 2, false><<<g, 256, 0, s>>>(a, bt);
+        if (bt.nfb <= 2)
+            launch_tf_fg<R, MODE, false, 2>(a, bt, s);
         else
-            k_interp_tf<R, MODE, 1, false><<<g, 256, 0, s>>>(a, bt);
+            launch_tf_fg<R, MODE, false, 4>(a, bt, s);
     }
     return hipGetLastError();
 }
@@ -314,11 +361,10 @@ hipError_t launch_grid_interleave(int prec, const void *grid, int n_beam, int n_
                                   void *T, hipStream_t s) {
     const int F = n_freq * ncomp;
     const int64_t P = (int64_t)n_za * n_az;
-    dim3 g((unsigned)((P + 63) / 64), (unsigned)((F + 63) / 64), (unsigned)n_beam);
     if (prec == P64)
-        k_grid_interleave<double2><<<g, 256, 0, s>>>((const double2 *)grid, F, P, (double2 *)T);
+        interleave((const double2 *)grid, n_beam, F, P, (double2 *)T, s);
     else
-        k_grid_interleave<float2><<<g, 256, 0, s>>>((const float2 *)grid, F, P, (float2 *)T);
+        interleave((const float2 *)grid, n_beam, F, P, (float2 *)T, s);
     return hipGetLastError();
 }
 
