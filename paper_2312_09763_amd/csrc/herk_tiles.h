@@ -1,5 +1,5 @@
 // Tile geometry shared by the product kernels that form Z in LDS
-// (kernels_herk_fused.hip, kernels_herk_x6.hip).
+// (kernels_herk_fused.hip, kernels_herk_x6.hip, kernels_pairs.hip).
 #pragma once
 
 #include "internal.h"
@@ -36,6 +36,37 @@ struct AntEntry {
     int b;              // beam index, -1 for padding rows
     int pad;
 };
+
+// packed bf16 words of one complex64 value: z = hi + mid + lo, each round-to-nearest-even
+__device__ inline void split3(float re, float im, uint32_t &hi, uint32_t &mid, uint32_t &lo) {
+    const f32x2_t z = {re, im};
+    const bf16x2_t h = __builtin_convertvector(z, bf16x2_t);
+    const f32x2_t r = z - __builtin_convertvector(h, f32x2_t);
+    const bf16x2_t m = __builtin_convertvector(r, bf16x2_t);
+    const f32x2_t q = r - __builtin_convertvector(m, f32x2_t);
+    const bf16x2_t l = __builtin_convertvector(q, bf16x2_t);
+    hi = __builtin_bit_cast(uint32_t, h);
+    mid = __builtin_bit_cast(uint32_t, m);
+    lo = __builtin_bit_cast(uint32_t, l);
+}
+
+// packed (hi, lo) bf16 words of one complex64 value: hi = bf16(z), lo = bf16(z - hi),
+// both round-to-nearest-even (v_cvt_pk_bf16_f32 on gfx950)
+__device__ inline void split2(float re, float im, uint32_t &hi, uint32_t &lo) {
+    const f32x2_t z = {re, im};
+    const bf16x2_t h = __builtin_convertvector(z, bf16x2_t);
+    const f32x2_t r = z - __builtin_convertvector(h, f32x2_t);
+    const bf16x2_t l = __builtin_convertvector(r, bf16x2_t);
+    hi = __builtin_bit_cast(uint32_t, h);
+    lo = __builtin_bit_cast(uint32_t, l);
+}
+
+// F = exp(-2 pi i p), p in cycles: FP64 reduction, hardware sine and cosine in revolutions
+__device__ __forceinline__ void fringe(double p, float &fr, float &fi) {
+    const float r = (float)__builtin_amdgcn_fract(p);
+    fi = __builtin_amdgcn_sinf(-r);
+    fr = __builtin_amdgcn_cosf(-r);
+}
 
 // the column fragment rotated for the imaginary part: (re, im) -> (-im, re) per bf16 pair
 __device__ inline u32x4 bf16_rot_col(u32x4 v) {

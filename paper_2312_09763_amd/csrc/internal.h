@@ -270,18 +270,36 @@ struct SubmatArgs {
     int64_t ksplit;          // columns per k-split (multiple of 16)
     int32_t max_splits;
     void *part;              // [n_inst][max_splits][n_tiles][ST][ST] complex partials
-    // Z formed in the stages instead of read (launch_submat_fused, FP32 / BF16X3):
-    // Z[(a, p), (m, k)] = B[inst][beam(a)][p][k][m] F_a(m) from these inputs
-    const double *antc;      // [n_ant][3] centred ENU
-    const int32_t *bidx;     // [n_ant] sanitised beam index
-    const double *freqs;     // [n_freq]
-    const double *s_hat;     // [nslots][3][ld_src]
-    const void *B;           // sqrt(I) A (or A M), complex64 [n_inst][n_beam][n_feed][n_ax][ld_src]
-    int64_t ld_src;
-    int32_t n_feed, n_beam, f0;
 };
 hipError_t launch_submat(int prec, const SubmatArgs &a, hipStream_t s);
-hipError_t launch_submat_fused(int prec, const SubmatArgs &a, hipStream_t s);
+// The same product with Z formed in LDS (FP32 / BF16X3 fused contexts):
+//   Z[(a, p), (m, k)] = B[inst][beam(a)][p][k][m] F_a(m).
+constexpr int kPairTile = 16;    // output tile side
+constexpr int kPairBlocks = 22;  // blocks of 16 rows that one workgroup can stage twice in LDS
+constexpr int kPairTiles = 96;   // tiles of one workgroup: 6 a wave
+struct PairBundle {
+    int32_t row0, n_rows;    // its rows (whole blocks of 16) in rows[]
+    int32_t tile0, n_tiles;  // its tiles in tiles[]
+};
+struct PairArgs {
+    const int32_t *rows;        // Z rows a n_feed + p of every bundle's blocks, -1 = padding
+    const int32_t *tiles;       // [n_tiles] row block | column block << 8, within the bundle
+    const PairBundle *bundles;  // [n_bundle]
+    int32_t n_tiles, n_bundle;
+    const int32_t *count;       // [nslots] visible counts (K = n_ax * count)
+    int32_t n_ax, n_feed, n_beam, nfb, n_inst, f0;
+    int32_t n_split;            // k-splits of split_cols(K, n_split) columns
+    const double *antc;         // [n_ant][3] centred ENU
+    const int32_t *bidx;        // [n_ant] sanitised beam index
+    const double *freqs;        // [n_freq]
+    const double *s_hat;        // [nslots][3][ld_src]
+    const void *B;              // sqrt(I) A (or A M), complex64 [n_inst][n_beam][n_feed][n_ax][ld_src]
+    int64_t ld_src;
+    void *part;                 // [n_inst][n_split][n_tiles][16][16] complex64 partials
+};
+hipError_t launch_pair_tiles(int prec, const PairArgs &a, hipStream_t s);
+// Columns of each of n k-splits of K columns, whole stages of 16 (the last ones may be short or empty)
+__host__ __device__ inline int64_t split_cols(int64_t K, int64_t n) { return ((K + n - 1) / n + 15) / 16 * 16; }
 struct SubmatReduceArgs {
     const void *part;
     int32_t n_tiles, max_splits, st;
@@ -290,7 +308,7 @@ struct SubmatReduceArgs {
     const int32_t *count;
     int64_t fixed_k;
     int32_t n_ax, nfb, n_inst;
-    int64_t ksplit;
+    int64_t ksplit;          // columns per split, or 0: split_cols(K, max_splits)
     double *vacc;            // [n_inst][n_pair][n_feed][n_feed] complex128 running sums
     int32_t first, last;
     void *out;               // [n_time][n_freq][n_pair][n_feed][n_feed]

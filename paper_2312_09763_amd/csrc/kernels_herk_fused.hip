@@ -35,17 +35,6 @@ namespace {
 
 constexpr int kWT = 64, kKC = 32;
 
-// packed (hi, lo) bf16 words of one complex64 value: hi = bf16(z), lo = bf16(z - hi),
-// both round-to-nearest-even (v_cvt_pk_bf16_f32 on gfx950)
-__device__ inline void split2(float re, float im, uint32_t &hi, uint32_t &lo) {
-    const f32x2_t z = {re, im};
-    const bf16x2_t h = __builtin_convertvector(z, bf16x2_t);
-    const f32x2_t r = z - __builtin_convertvector(h, f32x2_t);
-    const bf16x2_t l = __builtin_convertvector(r, bf16x2_t);
-    hi = __builtin_bit_cast(uint32_t, h);
-    lo = __builtin_bit_cast(uint32_t, l);
-}
-
 __device__ inline u32x4 bf16_rot(u32x4 v) {
     u32x4 r;
     for (int q = 0; q < 4; q++) r[q] = __builtin_amdgcn_alignbit(v[q], v[q], 16) ^ 0x80000000u;

@@ -37,20 +37,6 @@ namespace {
 typedef RowGeom<208, 64, 1> GeomX6;
 constexpr int kSPS = 16;                  // sources per stage
 constexpr int kPad = 3 * GeomX6::PLANEB;  // the padding's offset in a row
-constexpr int kSegment = 768;            // sources accumulated before they are added to the partial
-
-// packed bf16 words of one complex64 value: z = hi + mid + lo, each round-to-nearest-even
-__device__ inline void split3(float re, float im, uint32_t &hi, uint32_t &mid, uint32_t &lo) {
-    const f32x2_t z = {re, im};
-    const bf16x2_t h = __builtin_convertvector(z, bf16x2_t);
-    const f32x2_t r = z - __builtin_convertvector(h, f32x2_t);
-    const bf16x2_t m = __builtin_convertvector(r, bf16x2_t);
-    const f32x2_t q = r - __builtin_convertvector(m, f32x2_t);
-    const bf16x2_t l = __builtin_convertvector(q, bf16x2_t);
-    hi = __builtin_bit_cast(uint32_t, h);
-    mid = __builtin_bit_cast(uint32_t, m);
-    lo = __builtin_bit_cast(uint32_t, l);
-}
 
 // two sources (2 mp, 2 mp + 1) of a row
 __device__ __forceinline__ void store_row(unsigned char *buf, int row, int mp, const float (&vr)[2],
@@ -262,13 +248,6 @@ struct Pads {
         return Src{xy.x, xy.y, *(const double *)at(st, m, 1), f.x, f.y, f.z, f.w};
     }
 };
-
-// F = exp(-2 pi i p), p in cycles: FP64 reduction, hardware sine and cosine in revolutions
-__device__ __forceinline__ void fringe(double p, float &fr, float &fi) {
-    const float r = (float)__builtin_amdgcn_fract(p);
-    fi = __builtin_amdgcn_sinf(-r);
-    fr = __builtin_amdgcn_cosf(-r);
-}
 
 // ---------------------------------------------------------------------------
 // Diagonal blocks of the product over sources: planes P0 = s0 F, P1 = s1 F,

@@ -17,6 +17,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <new>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -88,10 +89,14 @@ struct matvis_ctx {
     bool pr_set = false;
     int32_t pr_n = 0, pr_tiles = 0;
     int64_t pr_size = 0;
-    int32_t *pr_rows = nullptr;  // [tiles][2][ST] Z rows
+    int32_t *pr_rows = nullptr;  // [tiles][2][ST] Z rows; rows of the bundles where Z is formed in LDS
     int32_t *pr_loc = nullptr;   // [n_pair][nf][nf][2]
-    void *pr_part = nullptr;     // [B_cap][max_splits][tiles][ST][ST]
-    void *pr_Z = nullptr, *pr_Z_lo = nullptr;  // fused contexts: Z of a batch for the pairs, when it fits
+    void *pr_part = nullptr;     // [B_cap][pr_splits][tiles][ST][ST]
+    void *pr_Z = nullptr;        // fused FP64 contexts: Z of a batch for the pairs
+    int pr_splits = 1;
+    int32_t pr_nbundle = 0;      // Z formed in LDS: the bundles and their tiles
+    PairBundle *pr_bundles = nullptr;
+    int32_t *pr_tile_list = nullptr;
     double *pr_vacc = nullptr;   // [B_cap][n_pair][nf][nf] complex128
 };
 
@@ -428,6 +433,117 @@ matvis_status matvis_finish(matvis_ctx *c) {
 
 namespace {
 
+// The tiles of a pair plan: rows of Z, where each pair lies (tile, element), and, where
+// Z is formed in LDS, the tiles' blocks and their bundles.
+struct PairTiles {
+    std::vector<int32_t> rows, loc, tiles;
+    std::vector<PairBundle> bundles;
+    int n_tiles = 0;
+};
+
+// 32 x 32 tiles over every sub-matrix's Z rows (antenna a, feed p -> row a nf + p)
+PairTiles pair_submatrices(const red::Plan &P, const int32_t *pair_a, const int32_t *pair_b, int n_pair, int n_ant,
+                           int nf) {
+    const int ST = kSubmatTile;
+    PairTiles T;
+    std::vector<int32_t> &rows = T.rows, &loc = T.loc, base;
+    std::vector<int> ntc;
+    for (size_t x = 0; x < P.A.size(); x++) {
+        const int ra = (int)P.A[x].size() * nf, rb = (int)P.B[x].size() * nf;
+        const int nta = (ra + ST - 1) / ST, ntb = (rb + ST - 1) / ST;
+        base.push_back((int32_t)(rows.size() / (2 * ST)));
+        ntc.push_back(ntb);
+        for (int ti = 0; ti < nta; ti++)
+            for (int tj = 0; tj < ntb; tj++) {
+                for (int r = 0; r < ST; r++) {
+                    const int q = ti * ST + r;
+                    rows.push_back(q < ra ? P.A[x][q / nf] * nf + q % nf : -1);
+                }
+                for (int r = 0; r < ST; r++) {
+                    const int q = tj * ST + r;
+                    rows.push_back(q < rb ? P.B[x][q / nf] * nf + q % nf : -1);
+                }
+            }
+    }
+    T.n_tiles = (int)(rows.size() / (2 * ST));
+    std::vector<int> sub_of(n_ant, -1), pos_in(n_ant, -1);
+    for (size_t x = 0; x < P.A.size(); x++)
+        for (size_t i = 0; i < P.A[x].size(); i++) {
+            sub_of[P.A[x][i]] = (int)x;
+            pos_in[P.A[x][i]] = (int)i;
+        }
+    loc.resize((size_t)n_pair * nf * nf * 2);
+    for (int u = 0; u < n_pair; u++) {
+        const int x = sub_of[pair_a[u]];
+        const auto &B = P.B[x];
+        const int ib = (int)(std::lower_bound(B.begin(), B.end(), pair_b[u]) - B.begin());
+        for (int p = 0; p < nf; p++)
+            for (int q = 0; q < nf; q++) {
+                const int r = pos_in[pair_a[u]] * nf + p, col = ib * nf + q;
+                const size_t e = (((size_t)u * nf + p) * nf + q) * 2;
+                loc[e] = base[x] + (r / ST) * ntc[x] + col / ST;
+                loc[e + 1] = (r % ST) * ST + col % ST;
+            }
+    }
+    return T;
+}
+
+// The rows that some pair uses, in order, in blocks of 16; the 16 x 16 tiles that hold a
+// pair, by column block; bundles of tiles as they come, closed when the next tile would
+// exceed a workgroup's tiles or staged blocks.
+PairTiles pair_bundles(const int32_t *pair_a, const int32_t *pair_b, int n_pair, int nf) {
+    PairTiles T;
+    std::map<int32_t, int32_t> pos;  // antenna -> place among the used ones
+    for (int u = 0; u < n_pair; u++) pos[pair_a[u]] = pos[pair_b[u]] = 0;
+    std::vector<int32_t> used;
+    for (auto &kv : pos) {
+        kv.second = (int32_t)used.size();
+        used.push_back(kv.first);
+    }
+    const int n_rows = (int)used.size() * nf, B = kPairTile;
+    std::map<std::pair<int32_t, int32_t>, int32_t> tile;  // (column block, row block) -> index
+    auto each = [&](auto f) {
+        for (int u = 0; u < n_pair; u++)
+            for (int p = 0; p < nf; p++)
+                for (int q = 0; q < nf; q++)
+                    f(((size_t)u * nf + p) * nf + q, pos[pair_a[u]] * nf + p, pos[pair_b[u]] * nf + q);
+    };
+    each([&](size_t, int32_t r, int32_t c) { tile[{c / B, r / B}] = 0; });
+    std::vector<int32_t> blocks;  // of the open bundle
+    auto slot = [&](int32_t b) {
+        return (int32_t)(std::find(blocks.begin(), blocks.end(), b) - blocks.begin());
+    };
+    PairBundle bd{0, 0, 0, 0};
+    auto close = [&]() {
+        bd.n_rows = (int32_t)blocks.size() * B;
+        bd.n_tiles = T.n_tiles - bd.tile0;
+        T.bundles.push_back(bd);
+        for (int32_t b : blocks)
+            for (int i = 0; i < B; i++) {
+                const int r = b * B + i;
+                T.rows.push_back(r < n_rows ? used[r / nf] * nf + r % nf : -1);
+            }
+        bd = PairBundle{(int32_t)T.rows.size(), 0, T.n_tiles, 0};
+        blocks.clear();
+    };
+    for (auto &kv : tile) {
+        const int32_t J = kv.first.first, I = kv.first.second;
+        const int fresh = (slot(I) == (int)blocks.size()) + (J != I && slot(J) == (int)blocks.size());
+        if ((int)blocks.size() + fresh > kPairBlocks || T.n_tiles - bd.tile0 == kPairTiles) close();
+        for (int32_t b : {J, I})
+            if (slot(b) == (int)blocks.size()) blocks.push_back(b);
+        T.tiles.push_back(slot(I) | slot(J) << 8);
+        kv.second = T.n_tiles++;
+    }
+    close();
+    T.loc.resize((size_t)n_pair * nf * nf * 2);
+    each([&](size_t e, int32_t r, int32_t c) {
+        T.loc[2 * e] = tile[{c / B, r / B}];
+        T.loc[2 * e + 1] = (r % B) * B + c % B;
+    });
+    return T;
+}
+
 // Enqueue the whole simulate sequence on stream s (no host waits).
 matvis_status enqueue_simulate(matvis_ctx *c, const double *antpos, const int32_t *beam_idx, const double *freqs,
                                int32_t n_freq, const double *lsts, int32_t n_time, const double *radec, int64_t n_src,
@@ -576,48 +692,58 @@ matvis_status enqueue_simulate(matvis_ctx *c, const double *antpos, const int32_
                     STEP(c, MATVIS_STEP_ZFORM, s, launch_zform(prec, za, bt, s));
                     if (!pairs) STEP(c, MATVIS_STEP_HERK, s, launch_herk(prec, ha, s));
                 } else if (pairs && c->pr_Z) {
-                    // the pairs of a fused context with room for a batch of Z: form Z once
-                    // (B already carries the sky) rather than once per sub-matrix tile
+                    // the pairs of a fused FP64 context (B already carries the sky)
                     za.flux = nullptr;
                     za.Z = c->pr_Z;
-                    za.Z_lo = c->pr_Z_lo;
                     STEP(c, MATVIS_STEP_ZFORM, s, launch_zform(prec, za, bt, s));
                 }
                 if (pairs) {
                     // App. A: only the planned sub-matrices, then the requested pairs
-                    SubmatArgs sa{};
-                    sa.Z = c->fused ? c->pr_Z : c->Z;
-                    sa.Z_lo = c->fused ? c->pr_Z_lo : c->Z_lo;
-                    sa.ldz = c->ldz;
-                    sa.inst_stride = (int64_t)c->Np * c->ldz;
-                    sa.rows = c->pr_rows;
-                    sa.n_tiles = c->pr_tiles;
-                    sa.count = c->count;
-                    sa.n_ax = g.n_ax;
-                    sa.nfb = nfb;
-                    sa.n_inst = bt.n_inst;
-                    sa.ksplit = c->ksplit;
-                    sa.max_splits = c->pair_splits;
-                    sa.part = c->pr_part;
-                    if (c->fused && !c->pr_Z) {  // Z formed in the stages from B = sqrt(I) A and the fringe phase
-                        sa.antc = c->antc;
-                        sa.bidx = c->bidx;
-                        sa.freqs = freqs;
-                        sa.s_hat = c->s_hat;
-                        sa.B = c->A;
-                        sa.ld_src = c->chunk;
-                        sa.n_feed = g.n_feed;
-                        sa.n_beam = g.n_beam;
-                        sa.f0 = f0;
-                        STEP(c, MATVIS_STEP_HERK, s, launch_submat_fused(prec, sa, s));
+                    if (c->pr_nbundle) {
+                        PairArgs pa{};
+                        pa.rows = c->pr_rows;
+                        pa.tiles = c->pr_tile_list;
+                        pa.bundles = c->pr_bundles;
+                        pa.n_tiles = c->pr_tiles;
+                        pa.n_bundle = c->pr_nbundle;
+                        pa.count = c->count;
+                        pa.n_ax = g.n_ax;
+                        pa.n_feed = g.n_feed;
+                        pa.n_beam = g.n_beam;
+                        pa.nfb = nfb;
+                        pa.n_inst = bt.n_inst;
+                        pa.f0 = f0;
+                        pa.n_split = c->pr_splits;
+                        pa.antc = c->antc;
+                        pa.bidx = c->bidx;
+                        pa.freqs = freqs;
+                        pa.s_hat = c->s_hat;
+                        pa.B = c->A;
+                        pa.ld_src = c->chunk;
+                        pa.part = c->pr_part;
+                        STEP(c, MATVIS_STEP_HERK, s, launch_pair_tiles(prec, pa, s));
                     } else {
+                        SubmatArgs sa{};
+                        sa.Z = c->fused ? c->pr_Z : c->Z;
+                        sa.Z_lo = c->Z_lo;
+                        sa.ldz = c->ldz;
+                        sa.inst_stride = (int64_t)c->Np * c->ldz;
+                        sa.rows = c->pr_rows;
+                        sa.n_tiles = c->pr_tiles;
+                        sa.count = c->count;
+                        sa.n_ax = g.n_ax;
+                        sa.nfb = nfb;
+                        sa.n_inst = bt.n_inst;
+                        sa.ksplit = c->ksplit;
+                        sa.max_splits = c->pr_splits;
+                        sa.part = c->pr_part;
                         STEP(c, MATVIS_STEP_HERK, s, launch_submat(prec, sa, s));
                     }
                     SubmatReduceArgs sr{};
                     sr.part = c->pr_part;
                     sr.n_tiles = c->pr_tiles;
-                    sr.max_splits = c->pair_splits;
-                    sr.st = kSubmatTile;
+                    sr.max_splits = c->pr_splits;
+                    sr.st = c->pr_nbundle ? kPairTile : kSubmatTile;
                     sr.loc = c->pr_loc;
                     sr.n_pair = c->pr_n;
                     sr.n_feed = g.n_feed;
@@ -625,7 +751,7 @@ matvis_status enqueue_simulate(matvis_ctx *c, const double *antpos, const int32_
                     sr.n_ax = g.n_ax;
                     sr.nfb = nfb;
                     sr.n_inst = bt.n_inst;
-                    sr.ksplit = c->ksplit;
+                    sr.ksplit = c->pr_nbundle ? 0 : c->ksplit;
                     sr.vacc = c->pr_vacc;
                     sr.first = ch == 0;
                     sr.last = ch == n_chunks - 1;
@@ -759,49 +885,31 @@ matvis_status matvis_set_pairs(matvis_ctx *c, const int32_t *pair_a, const int32
     for (int u = 0; u < n_pair; u++)
         if (pair_a[u] < 0 || pair_a[u] >= g.n_ant || pair_b[u] < 0 || pair_b[u] >= g.n_ant)
             return fail(c, MATVIS_EINVAL, "pair antenna outside [0, n_ant)");
-    const red::Plan P = red::plan(pair_a, pair_b, n_pair, g.n_ant, n_sub);
-    const int nf = g.n_feed, ST = kSubmatTile;
-    // tiles of every sub-matrix over its Z rows (antenna a, feed p -> row a nf + p)
-    std::vector<int32_t> rows, base;
-    std::vector<int> ntc;
+    const int nf = g.n_feed;
+    const bool in_lds = c->fused && g.precision != P64;  // else Z in device memory
     int64_t size = 0;
-    for (size_t x = 0; x < P.A.size(); x++) {
-        const int ra = (int)P.A[x].size() * nf, rb = (int)P.B[x].size() * nf;
-        const int nta = (ra + ST - 1) / ST, ntb = (rb + ST - 1) / ST;
-        base.push_back((int32_t)(rows.size() / (2 * ST)));
-        ntc.push_back(ntb);
-        size += (int64_t)P.A[x].size() * P.B[x].size();
-        for (int ti = 0; ti < nta; ti++)
-            for (int tj = 0; tj < ntb; tj++) {
-                for (int r = 0; r < ST; r++) {
-                    const int q = ti * ST + r;
-                    rows.push_back(q < ra ? P.A[x][q / nf] * nf + q % nf : -1);
-                }
-                for (int r = 0; r < ST; r++) {
-                    const int q = tj * ST + r;
-                    rows.push_back(q < rb ? P.B[x][q / nf] * nf + q % nf : -1);
-                }
-            }
+    PairTiles T;
+    try {
+        const red::Plan P = red::plan(pair_a, pair_b, n_pair, g.n_ant, n_sub);
+        for (size_t x = 0; x < P.A.size(); x++) size += (int64_t)P.A[x].size() * P.B[x].size();
+        T = in_lds ? pair_bundles(pair_a, pair_b, n_pair, nf)
+                   : pair_submatrices(P, pair_a, pair_b, n_pair, g.n_ant, nf);
+    } catch (const std::bad_alloc &) {
+        return fail(c, MATVIS_ENOMEM, "host memory for the pair plan");
     }
-    const int n_tiles = (int)(rows.size() / (2 * ST));
-    std::vector<int> sub_of(g.n_ant, -1), pos_in(g.n_ant, -1);
-    for (size_t x = 0; x < P.A.size(); x++)
-        for (size_t i = 0; i < P.A[x].size(); i++) {
-            sub_of[P.A[x][i]] = (int)x;
-            pos_in[P.A[x][i]] = (int)i;
-        }
-    std::vector<int32_t> loc((size_t)n_pair * nf * nf * 2);
-    for (int u = 0; u < n_pair; u++) {
-        const int x = sub_of[pair_a[u]];
-        const auto &B = P.B[x];
-        const int ib = (int)(std::lower_bound(B.begin(), B.end(), pair_b[u]) - B.begin());
-        for (int p = 0; p < nf; p++)
-            for (int q = 0; q < nf; q++) {
-                const int r = pos_in[pair_a[u]] * nf + p, col = ib * nf + q;
-                const size_t e = (((size_t)u * nf + p) * nf + q) * 2;
-                loc[e] = base[x] + (r / ST) * ntc[x] + col / ST;
-                loc[e + 1] = (r % ST) * ST + col % ST;
-            }
+    const int ST = in_lds ? kPairTile : kSubmatTile;
+    const int B_cap = c->ntb * c->nfb;
+    const auto &rows = T.rows;
+    const auto &loc = T.loc;
+    const int n_tiles = T.n_tiles;
+    int splits = c->pair_splits;
+    if (in_lds) {
+        // A workgroup has a CU to itself: as many k-splits as fill whole rounds of the
+        // CUs, none above the context's columns per split nor of fewer than 8 stages.
+        const int64_t per_split = (int64_t)B_cap * (int64_t)T.bundles.size();
+        const int64_t rounds = (per_split * splits + c->n_cu - 1) / c->n_cu;
+        const int64_t most = std::max<int64_t>(1, c->ldz / 128);
+        splits = (int)std::max<int64_t>(splits, std::min(most, rounds * c->n_cu / per_split));
     }
     HIPCHK(c, hipSetDevice(c->device));
     HIPCHK(c, hipDeviceSynchronize());
@@ -809,7 +917,8 @@ matvis_status matvis_set_pairs(matvis_ctx *c, const int32_t *pair_a, const int32
     for (auto &kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
     c->graphs.clear();
     c->graph_order.clear();
-    for (void *q : {(void *)c->pr_rows, (void *)c->pr_loc, c->pr_part, (void *)c->pr_vacc, c->pr_Z, c->pr_Z_lo}) {
+    for (void *q : {(void *)c->pr_rows, (void *)c->pr_loc, c->pr_part, (void *)c->pr_vacc, c->pr_Z,
+                    (void *)c->pr_bundles, (void *)c->pr_tile_list}) {
         if (!q) continue;
         auto it = std::find(c->allocs.begin(), c->allocs.end(), q);
         if (it != c->allocs.end()) c->allocs.erase(it);
@@ -818,31 +927,34 @@ matvis_status matvis_set_pairs(matvis_ctx *c, const int32_t *pair_a, const int32
     c->pr_rows = c->pr_loc = nullptr;
     c->pr_part = nullptr;
     c->pr_vacc = nullptr;
-    c->pr_Z = c->pr_Z_lo = nullptr;
+    c->pr_Z = nullptr;
+    c->pr_bundles = nullptr;
+    c->pr_tile_list = nullptr;
+    c->pr_nbundle = 0;
     c->pr_set = false;
-    const int B_cap = c->ntb * c->nfb;
     matvis_status st;
     if ((st = dalloc(c, &c->pr_rows, sizeof(int32_t) * rows.size())) != MATVIS_OK) return st;
     if ((st = dalloc(c, &c->pr_loc, sizeof(int32_t) * loc.size())) != MATVIS_OK) return st;
-    if ((st = dalloc(c, &c->pr_part, cbytes(g.precision) * (size_t)B_cap * c->pair_splits * n_tiles * ST * ST)) !=
+    if ((st = dalloc(c, &c->pr_part, cbytes(g.precision) * (size_t)B_cap * splits * n_tiles * ST * ST)) !=
         MATVIS_OK)
         return st;
     if ((st = dalloc(c, &c->pr_vacc, sizeof(double) * 2 * (size_t)B_cap * n_pair * nf * nf)) != MATVIS_OK) return st;
-    // Fused contexts: a sub-matrix tile reuses a formed Z row only within its 32
-    // rows, so forming Z once per batch in device memory is faster whenever it
-    // fits a fixed budget; otherwise the tiles form their rows in the stages (FP64
-    // always has it: its batch is sized for one).
-    if (c->fused) {
-        const size_t zplane = (g.precision == PB3 ? (size_t)4 : cbytes(g.precision)) * B_cap * c->Np * c->ldz;
-        if (g.precision == P64 || zplane * (g.precision == PB3 ? 2 : 1) <= ((size_t)8 << 30)) {
-            if ((st = dalloc(c, &c->pr_Z, zplane)) != MATVIS_OK) return st;
-            if (g.precision == PB3 && (st = dalloc(c, &c->pr_Z_lo, zplane)) != MATVIS_OK) return st;
-        }
+    if (c->fused && g.precision == P64) {  // its batch is sized for a Z
+        if ((st = dalloc(c, &c->pr_Z, cbytes(g.precision) * (size_t)B_cap * c->Np * c->ldz)) != MATVIS_OK) return st;
+    }
+    if (in_lds) {
+        if ((st = dalloc(c, &c->pr_bundles, sizeof(PairBundle) * T.bundles.size())) != MATVIS_OK) return st;
+        if ((st = dalloc(c, &c->pr_tile_list, sizeof(int32_t) * T.tiles.size())) != MATVIS_OK) return st;
+        HIPCHK(c, hipMemcpy(c->pr_bundles, T.bundles.data(), sizeof(PairBundle) * T.bundles.size(),
+                            hipMemcpyHostToDevice));
+        HIPCHK(c, hipMemcpy(c->pr_tile_list, T.tiles.data(), sizeof(int32_t) * T.tiles.size(), hipMemcpyHostToDevice));
     }
     HIPCHK(c, hipMemcpy(c->pr_rows, rows.data(), sizeof(int32_t) * rows.size(), hipMemcpyHostToDevice));
     HIPCHK(c, hipMemcpy(c->pr_loc, loc.data(), sizeof(int32_t) * loc.size(), hipMemcpyHostToDevice));
     c->pr_n = n_pair;
     c->pr_tiles = n_tiles;
+    c->pr_splits = splits;
+    c->pr_nbundle = (int32_t)T.bundles.size();
     c->pr_size = size;
     c->pr_set = true;
     if (size_out) *size_out = size;
