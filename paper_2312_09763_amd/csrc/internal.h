@@ -86,23 +86,41 @@ struct SkyBufs {
 
 // ---- sky (kernels_sky.hip) -------------------------------------------------
 hipError_t launch_xeq(const double *radec, int64_t n_src, double *xeq, int64_t ld, hipStream_t s);
-// Eq. (xeq) with the sources put in sky-cell order (stable): xeq[.][pos] is
-// source perm[pos].  Scratch: xeq_in [3][ld] doubles, cell [ld] int16, hist
-// [sort_hist_entries(ld)] int32.
+// The sources in sky-cell order (stable): xeq[.][pos] is source perm[pos].  Scratch:
+// xeq_in [3][ld] doubles, cell [ld] int16, hist [sort_hist_entries(ld)] int32, of which
+// launch_prepare fills xeq_in, cell and hist.
 struct SortBufs {
     double *xeq_in;
     int16_t *cell;
     int32_t *hist;
     int32_t *perm;
 };
-hipError_t launch_xeq_sorted(const double *radec, int64_t n_src, int64_t ld, SortBufs sb, double *xeq, hipStream_t s);
+// What a call does once from its inputs: Eq. (xeq) and the cells, the centred antennas,
+// the rotation matrices, the checks.
+struct PrepareArgs {
+    const double *radec;  // [2][n_src]
+    int64_t n_src, ld;
+    SortBufs sort;
+    const double *antpos;
+    const int32_t *beam_idx;  // or null
+    int32_t n_ant, n_beam;
+    double *antc;
+    int32_t *bidx;
+    const double *lsts;
+    int32_t n_time;
+    double latitude;
+    double *rot;
+    // n_flux values of Stokes I are checked (>= 0, finite); with pol the four planes
+    // [4][n_flux] are checked for a physical brightness matrix.
+    const double *flux;
+    int64_t n_flux;
+    int pol;
+    int32_t *flags;
+};
+hipError_t launch_prepare(const PrepareArgs &a, hipStream_t s);
+hipError_t launch_sort(int64_t n_src, int64_t ld, SortBufs sb, double *xeq, hipStream_t s);
 int64_t sort_hist_entries(int64_t max_src);
 hipError_t launch_rotmats(const double *lsts, int32_t n_time, double latitude, double *rot, hipStream_t s);
-// n_flux values of Stokes I are checked (>= 0, finite); with pol the four planes
-// [4][n_flux] are checked for a physical brightness matrix.
-hipError_t launch_prep_inputs(const double *antpos, int32_t n_ant, const int32_t *beam_idx, int32_t n_beam,
-                              const double *flux, int64_t n_flux, int pol, double *antc, int32_t *bidx,
-                              int32_t *flags, hipStream_t s);
 hipError_t launch_sky(const SkyBufs &b, int32_t t0, int32_t ntb, int64_t c0, int64_t nsrc_chunk, hipStream_t s);
 
 // ---- beam (kernels_beam.hip) -----------------------------------------------

@@ -340,7 +340,13 @@ void launch_tf_fg(const InterpArgs &a, const Batch &bt, hipStream_t s) {
 
 template <typename R, int MODE>
 hipError_t launch_tf_mode(const InterpArgs &a, const Batch &bt, hipStream_t s) {
-    if (a.stencil) {
+    // Stencils are formed by every lane of a source, rather than once in a launch of its
+    // own, where that is less than the launch: 2^20 lane stencils take about 2 us, the
+    // launch 3 to 5.
+    const int fg = bt.nfb <= 2 ? 2 : 4, ncomp = a.n_feed * a.n_ax;
+    const int64_t uses = (int64_t)((bt.nfb + fg - 1) / fg) * ((a.n_beam + kBeamGroup - 1) / kBeamGroup) *
+                         (fg * ncomp * (int)sizeof(typename CplxOf<R>::T) / 16);
+    if (a.stencil && uses * a.max_m * bt.ntb > (1 << 20)) {
         k_stencil<R, MODE><<<dim3((unsigned)((a.max_m + 255) / 256), (unsigned)bt.ntb), 256, 0, s>>>(a, bt);
         if (bt.nfb <= 2)
             launch_tf_fg<R, MODE, true, 2>(a, bt, s);

@@ -1,11 +1,16 @@
 // Sky geometry on the device: Eq. (xeq), Eq. (rotation), the topocentric
 // rotation of Alg. 2 step (i) and the order-preserving horizon compaction.
 //
-// Compaction is three passes per (time batch, source chunk):
+// Compaction is up to three passes per (time batch, source chunk):
 //   count   : one wave64 ballot per 64 sources, popcount, per-block sums;
 //   scan    : exclusive prefix over the block sums of every time;
 //   scatter : recompute the rotation (cheaper than storing it), place each
 //             visible source at block offset + wave offset + mbcnt lane rank.
+// Up to kFoldBlocks blocks the scatter sums the earlier blocks' counts itself, and up
+// to kOneBlocks it counts them itself too: a launch costs 4 to 5 us in the call's
+// serial chain, the redundant work less (2000 sources, 4 times: 11.2 -> 4.7 us; 20 011
+// sources, 3 times: 14.1 -> 9.3 us).  Past kFoldBlocks the sums, which grow with the
+// square of the blocks, would cost more than the scan.
 // The result lists visible sources in ascending index order, so it is
 // deterministic and equal to a sequential filter.
 //
@@ -15,6 +20,8 @@
 // threads that interpolate the beam for them -- fall on nearby grid points.
 // The sky arrays then follow that order; the index lists hold the original
 // source numbers, so fluxes are read unchanged.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace mv {
@@ -56,13 +63,12 @@ __device__ inline int sky_cell(double x, double y, double z) {
 }
 
 // Eq. (xeq) in input order, each source's sky cell, and per-block cell counts.
-__global__ void __launch_bounds__(kSkyBlock) k_xeq_cells(const double *__restrict__ radec, int64_t n,
-                                                         double *__restrict__ xeq_in, int64_t ld,
-                                                         int16_t *__restrict__ cell, int32_t *__restrict__ hist) {
-    __shared__ int h[kCells];
+__device__ __forceinline__ void xeq_cells(int *h, int blk, const double *__restrict__ radec, int64_t n,
+                                          double *__restrict__ xeq_in, int64_t ld, int16_t *__restrict__ cell,
+                                          int32_t *__restrict__ hist) {
     for (int c = threadIdx.x; c < kCells; c += kSkyBlock) h[c] = 0;
     __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * kSkyBlock + threadIdx.x;
+    const int64_t i = (int64_t)blk * kSkyBlock + threadIdx.x;
     if (i < n) {
         double sr, cr, sd, cd;
         sincos(radec[i], &sr, &cr);
@@ -76,7 +82,7 @@ __global__ void __launch_bounds__(kSkyBlock) k_xeq_cells(const double *__restric
         atomicAdd(&h[c], 1);
     }
     __syncthreads();
-    for (int c = threadIdx.x; c < kCells; c += kSkyBlock) hist[(int64_t)blockIdx.x * kCells + c] = h[c];
+    for (int c = threadIdx.x; c < kCells; c += kSkyBlock) hist[(int64_t)blk * kCells + c] = h[c];
 }
 
 // hist[b][c] -> first position of block b's cell-c sources in the cell-major
@@ -88,75 +94,82 @@ __global__ void __launch_bounds__(kSkyBlock) k_xeq_cells(const double *__restric
 //                         chunks scanned on top: part[ch][c] = first position of
 //                         chunk ch's cell-c sources (one workgroup);
 //   k_cell_apply:         each chunk walks its blocks, hist[b][c] = position.
+// Each is a chain of loads more than anything: batches of them are in flight ahead of the
+// stores, and the first and last pass take a workgroup per chunk and slice of cells
+// (20 011 sources: 11.6 + 10.1 + 7.4 -> 4.5 + 5.8 + 4.5 us; the middle pass at 3.1 million
+// sources 118 -> 68 us).  Up to kDirectBlocks blocks the one workgroup scans hist itself,
+// which costs it no more than as many chunks (2000 sources: 13.2 us in three launches,
+// 5.2 in one).
+constexpr int kDirectBlocks = 64;
 __host__ __device__ inline int cell_chunk(int nblk) { return ((nblk + 255) / 256 + 7) / 8 * 8; }
 
-__global__ void __launch_bounds__(256) k_cell_chunk_sums(const int32_t *__restrict__ hist, int nblk, int chunk,
-                                                         int32_t *__restrict__ part) {
-    const int ch = blockIdx.x;
+constexpr int kCellSlice = 256;  // cells of one workgroup of the first and last pass
+static_assert(kCells % kCellSlice == 0, "whole slices");
+
+__global__ void __launch_bounds__(kCellSlice) k_cell_chunk_sums(const int32_t *__restrict__ hist, int nblk, int chunk,
+                                                                int32_t *__restrict__ part) {
+    const int ch = blockIdx.x, c = blockIdx.y * kCellSlice + threadIdx.x;
     const int b0 = ch * chunk, b1 = nblk < b0 + chunk ? nblk : b0 + chunk;
-    for (int c = threadIdx.x; c < kCells; c += 256) {
-        int run = 0;
+    int run = 0;
 #pragma unroll 8
-        for (int b = b0; b < b1; b++) run += hist[(int64_t)b * kCells + c];
-        part[(int64_t)ch * kCells + c] = run;
-    }
+    for (int b = b0; b < b1; b++) run += hist[(int64_t)b * kCells + c];
+    part[(int64_t)ch * kCells + c] = run;
 }
 
-__global__ void __launch_bounds__(1024) k_cell_chunk_offsets(int32_t *__restrict__ part, int nchunk) {
-    __shared__ int tot[kCells];
-    __shared__ int wsum[1024 / kWave];
-    for (int c = threadIdx.x; c < kCells; c += 1024) {
-        int run = 0;
+// Two cells per thread.
+__global__ void __launch_bounds__(kCells / 2) k_cell_chunk_offsets(int32_t *part, int nchunk) {
+    constexpr int NW = kCells / 2 / kWave;
+    __shared__ int wsum[NW];
+    int2 *p = (int2 *)part + threadIdx.x;
+    int2 tot = make_int2(0, 0);
 #pragma unroll 16
-        for (int ch = 0; ch < nchunk; ch++) run += part[(int64_t)ch * kCells + c];
-        tot[c] = run;
+    for (int ch = 0; ch < nchunk; ch++) {
+        const int2 v = p[(int64_t)ch * (kCells / 2)];
+        tot.x += v.x;
+        tot.y += v.y;
     }
-    __syncthreads();
-    // exclusive scan of the cell totals (kCells <= 2 x 1024)
+    // exclusive scan of the cell totals
     const int lane = lane_id(), w = threadIdx.x / kWave;
-    int carry = 0;
-    for (int base = 0; base < kCells; base += 1024) {
-        const int c = base + threadIdx.x;
-        const int v = c < kCells ? tot[c] : 0;
-        int x = v;
-        for (int d = 1; d < kWave; d <<= 1) {
-            const int y = __shfl_up(x, d, kWave);
-            if (lane >= d) x += y;
-        }
-        if (lane == kWave - 1) wsum[w] = x;
-        __syncthreads();
-        int woff = 0;
-        for (int q = 0; q < w; q++) woff += wsum[q];
-        const int excl = carry + woff + x - v;
-        int block_total = 0;
-        for (int q = 0; q < 1024 / kWave; q++) block_total += wsum[q];
-        __syncthreads();
-        if (c < kCells) tot[c] = excl;
-        carry += block_total;
-        __syncthreads();
+    int x = tot.x + tot.y;
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int y = __shfl_up(x, d, kWave);
+        if (lane >= d) x += y;
     }
-    for (int c = threadIdx.x; c < kCells; c += 1024) {
-        int run = tot[c];
-        for (int ch = 0; ch < nchunk; ch++) {
-            const int v = part[(int64_t)ch * kCells + c];
-            part[(int64_t)ch * kCells + c] = run;
-            run += v;
-        }
+    if (lane == kWave - 1) wsum[w] = x;
+    __syncthreads();
+    int2 run = make_int2(x - tot.x - tot.y, 0);
+    for (int q = 0; q < w; q++) run.x += wsum[q];
+    run.y = run.x + tot.x;
+    for (int ch = 0; ch < nchunk; ch += 16) {  // sixteen loads ahead of their stores
+        int2 v[16];
+#pragma unroll
+        for (int q = 0; q < 16; q++)
+            v[q] = ch + q < nchunk ? p[(int64_t)(ch + q) * (kCells / 2)] : make_int2(0, 0);
+#pragma unroll
+        for (int q = 0; q < 16; q++)
+            if (ch + q < nchunk) {
+                p[(int64_t)(ch + q) * (kCells / 2)] = run;
+                run.x += v[q].x;
+                run.y += v[q].y;
+            }
     }
 }
 
-__global__ void __launch_bounds__(256) k_cell_apply(int32_t *__restrict__ hist, int nblk, int chunk,
-                                                    const int32_t *__restrict__ part) {
-    const int ch = blockIdx.x;
+__global__ void __launch_bounds__(kCellSlice) k_cell_apply(int32_t *hist, int nblk, int chunk,
+                                                           const int32_t *__restrict__ part) {
+    const int ch = blockIdx.x, c = blockIdx.y * kCellSlice + threadIdx.x;
     const int b0 = ch * chunk, b1 = nblk < b0 + chunk ? nblk : b0 + chunk;
-    for (int c = threadIdx.x; c < kCells; c += 256) {
-        int run = part[(int64_t)ch * kCells + c];
-#pragma unroll 8
-        for (int b = b0; b < b1; b++) {
-            const int v = hist[(int64_t)b * kCells + c];
-            hist[(int64_t)b * kCells + c] = run;
-            run += v;
-        }
+    int run = part[(int64_t)ch * kCells + c];
+    for (int b = b0; b < b1; b += 8) {  // eight loads ahead of their stores
+        int v[8];
+#pragma unroll
+        for (int q = 0; q < 8; q++) v[q] = b + q < b1 ? hist[(int64_t)(b + q) * kCells + c] : 0;
+#pragma unroll
+        for (int q = 0; q < 8; q++)
+            if (b + q < b1) {
+                hist[(int64_t)(b + q) * kCells + c] = run;
+                run += v[q];
+            }
     }
 }
 
@@ -192,8 +205,8 @@ __global__ void k_xeq(const double *__restrict__ radec, int64_t n, double *__res
 }
 
 // R(t) of Eq. (rotation) with hour angle H = -LST and latitude l.
-__global__ void k_rotmats(const double *__restrict__ lsts, int n_time, double lat, double *__restrict__ rot) {
-    int t = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void rotmat(int t, const double *__restrict__ lsts, int n_time, double lat,
+                                       double *__restrict__ rot) {
     if (t >= n_time) return;
     double sH, cH, sl, cl;
     sincos(-lsts[t], &sH, &cH);
@@ -211,11 +224,10 @@ __global__ void k_rotmats(const double *__restrict__ lsts, int n_time, double la
 }
 
 // One block: centre the antennas on their mean (a common offset cancels in
-// every baseline), sanitise beam indices, and flag invalid inputs.  The flux
-// check runs grid-wide in k_check_flux.
-__global__ void k_prep_ant(const double *__restrict__ antpos, int n_ant, const int32_t *__restrict__ beam_idx,
-                           int n_beam, double *__restrict__ antc, int32_t *__restrict__ bidx, int32_t *flags) {
-    __shared__ double red[3][kSkyBlock];
+// every baseline), sanitise beam indices, and flag invalid inputs.
+__device__ __forceinline__ void prep_ant(double (*red)[kSkyBlock], const double *__restrict__ antpos, int n_ant,
+                                         const int32_t *__restrict__ beam_idx, int n_beam, double *__restrict__ antc,
+                                         int32_t *__restrict__ bidx, int32_t *flags) {
     double s0 = 0.0, s1 = 0.0, s2 = 0.0;
     int bad = 0;
     for (int a = threadIdx.x; a < n_ant; a += blockDim.x) {
@@ -250,9 +262,10 @@ __global__ void k_prep_ant(const double *__restrict__ antpos, int n_ant, const i
     if (bad) atomicOr(flags, bad);
 }
 
-__global__ void k_check_flux(const double *__restrict__ flux, int64_t n, int pol, int32_t *flags) {
+__device__ __forceinline__ void check_flux(int blk, int n_blk, const double *__restrict__ flux, int64_t n, int pol,
+                                           int32_t *flags) {
     bool bad = false;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t i = (int64_t)blk * kSkyBlock + threadIdx.x; i < n; i += (int64_t)n_blk * kSkyBlock) {
         double f = flux[i];
         if (!(f >= 0.0) || !isfinite(f)) bad = true;
         if (pol) {
@@ -264,6 +277,27 @@ __global__ void k_check_flux(const double *__restrict__ flux, int64_t n, int pol
     }
     unsigned long long m = __ballot(bad);
     if (m && lane_id() == __ffsll((long long)m) - 1) atomicOr(flags, FLAG_BAD_FLUX);
+}
+
+// Everything a call does once and that depends on its inputs alone, by block range:
+// the sources' positions and cells, the antennas, the rotation matrices of the times,
+// the flux check.  As four launches in a row they took 18 us of a small call's 120.
+__global__ void __launch_bounds__(kSkyBlock) k_prepare(PrepareArgs a, int b_src, int b_rot, int b_flux) {
+    __shared__ union {
+        int h[kCells];
+        double red[3][kSkyBlock];
+    } sm;
+    int b = blockIdx.x;
+    if (b < b_src) return xeq_cells(sm.h, b, a.radec, a.n_src, a.sort.xeq_in, a.ld, a.sort.cell, a.sort.hist);
+    b -= b_src;
+    if (b == 0) return prep_ant(sm.red, a.antpos, a.n_ant, a.beam_idx, a.n_beam, a.antc, a.bidx, a.flags);
+    b -= 1;
+    if (b < b_rot) return rotmat(b * kSkyBlock + threadIdx.x, a.lsts, a.n_time, a.latitude, a.rot);
+    check_flux(b - b_rot, b_flux, a.flux, a.n_flux, a.pol, a.flags);
+}
+
+__global__ void k_rotmats(const double *__restrict__ lsts, int n_time, double lat, double *__restrict__ rot) {
+    rotmat(blockIdx.x * blockDim.x + threadIdx.x, lsts, n_time, lat, rot);
 }
 
 // Up-component of R(t) X_eq for source n.
@@ -328,8 +362,16 @@ __global__ void __launch_bounds__(1024) k_sky_scan(SkyBufs b, int nblk) {
     if (threadIdx.x == 0) b.count[ts] = carry_s;
 }
 
+constexpr int kOneBlocks = 16, kFoldBlocks = 2048;
+
+// Block offsets: SCANNED reads the scan's, SUMMED sums the earlier blocks' counts,
+// COUNTED counts the visible sources of the earlier blocks.
+enum SkyOffset { SCANNED, SUMMED, COUNTED };
+
+template <SkyOffset FROM>
 __global__ void __launch_bounds__(kSkyBlock) k_sky_scatter(SkyBufs b, int t0, int64_t c0, int64_t nsrc, int nblk) {
-    __shared__ int wsum[kSkyBlock / kWave];
+    constexpr int NW = kSkyBlock / kWave;
+    __shared__ int wsum[NW], wbefore[NW];
     const int ts = blockIdx.y;
     const double *r = b.rot + 9 * (t0 + ts);
     const int64_t ld = b.ld_src;
@@ -341,17 +383,38 @@ __global__ void __launch_bounds__(kSkyBlock) k_sky_scatter(SkyBufs b, int t0, in
         double x = b.xeq[n], y = b.xeq[b.ld_xeq + n], z = b.xeq[2 * b.ld_xeq + n];
         e = r[0] * x + r[1] * y + r[2] * z;
         nn = r[3] * x + r[4] * y + r[5] * z;
-        u = r[6] * x + r[7] * y + r[8] * z;
+        u = up_of(r, b.xeq, b.ld_xeq, n);
         vis = u > 0.0;
     }
     unsigned long long m = __ballot(vis);
     const int w = threadIdx.x / kWave;
-    if (lane_id() == 0) wsum[w] = __popcll(m);
+    int before = 0;  // visible sources of earlier blocks, this wave's share
+    if (FROM == SUMMED) {
+        for (int q = threadIdx.x; q < (int)blockIdx.x; q += kSkyBlock) before += b.blk_count[(int64_t)ts * nblk + q];
+        for (int d = kWave / 2; d > 0; d >>= 1) before += __shfl_xor(before, d, kWave);
+    } else if (FROM == COUNTED) {
+        for (int q = 0; q < (int)blockIdx.x; q++)  // whole blocks: all their sources exist
+            before += __popcll(__ballot(up_of(r, b.xeq, b.ld_xeq, c0 + q * kSkyBlock + threadIdx.x) > 0.0));
+    }
+    if (lane_id() == 0) {
+        wsum[w] = __popcll(m);
+        wbefore[w] = before;
+    }
     __syncthreads();
-    int woff = 0;
-    for (int i = 0; i < w; i++) woff += wsum[i];
+    int64_t o = 0;
+    if (FROM == SCANNED) {
+        o = b.blk_off[(int64_t)ts * nblk + blockIdx.x];
+    } else {
+        for (int i = 0; i < NW; i++) o += wbefore[i];
+        if ((int)blockIdx.x == nblk - 1 && threadIdx.x == 0) {
+            int total = (int)o;
+            for (int i = 0; i < NW; i++) total += wsum[i];
+            b.count[ts] = total;
+        }
+    }
+    for (int i = 0; i < w; i++) o += wsum[i];
     if (vis) {
-        int64_t o = b.blk_off[(int64_t)ts * nblk + blockIdx.x] + woff + rank_below(m);
+        o += rank_below(m);
         b.idx[ts * ld + o] = b.perm ? b.perm[c0 + j] : (int32_t)(c0 + j);
         double *sh = b.s_hat + (int64_t)ts * 3 * ld;
         sh[o] = e;
@@ -375,20 +438,29 @@ hipError_t launch_xeq(const double *radec, int64_t n_src, double *xeq, int64_t l
     return hipGetLastError();
 }
 
-hipError_t launch_xeq_sorted(const double *radec, int64_t n_src, int64_t ld, SortBufs sb, double *xeq, hipStream_t s) {
+hipError_t launch_prepare(const PrepareArgs &a, hipStream_t s) {
+    const int64_t b_src = a.n_src > 0 ? (a.n_src + kSkyBlock - 1) / kSkyBlock : 0;
+    const int64_t b_rot = a.n_time > 0 ? (a.n_time + kSkyBlock - 1) / kSkyBlock : 0;
+    const int64_t b_flux = a.n_flux > 0 && a.flux ? std::min<int64_t>((a.n_flux + 255) / 256, 4096) : 0;
+    k_prepare<<<(unsigned)(b_src + 1 + b_rot + b_flux), kSkyBlock, 0, s>>>(a, (int)b_src, (int)b_rot, (int)b_flux);
+    return hipGetLastError();
+}
+
+hipError_t launch_sort(int64_t n_src, int64_t ld, SortBufs sb, double *xeq, hipStream_t s) {
     if (n_src <= 0) return hipSuccess;
     const int nblk = (int)((n_src + kSkyBlock - 1) / kSkyBlock);
-    k_xeq_cells<<<nblk, kSkyBlock, 0, s>>>(radec, n_src, sb.xeq_in, ld, sb.cell, sb.hist);
+    if (nblk <= kDirectBlocks) {
+        k_cell_chunk_offsets<<<1, kCells / 2, 0, s>>>(sb.hist, nblk);
+    } else {
+        // chunk partials after the per-block counts (sort_hist_entries leaves room)
+        const int chunk = cell_chunk(nblk);
+        const int nchunk = (nblk + chunk - 1) / chunk;
+        int32_t *part = sb.hist + (int64_t)nblk * kCells;
+        k_cell_chunk_sums<<<dim3(nchunk, kCells / kCellSlice), kCellSlice, 0, s>>>(sb.hist, nblk, chunk, part);
+        k_cell_chunk_offsets<<<1, kCells / 2, 0, s>>>(part, nchunk);
+        k_cell_apply<<<dim3(nchunk, kCells / kCellSlice), kCellSlice, 0, s>>>(sb.hist, nblk, chunk, part);
+    }
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    // chunk partials after the per-block counts (sort_hist_entries leaves room)
-    const int chunk = cell_chunk(nblk);
-    const int nchunk = (nblk + chunk - 1) / chunk;
-    int32_t *part = sb.hist + (int64_t)nblk * kCells;
-    k_cell_chunk_sums<<<nchunk, 256, 0, s>>>(sb.hist, nblk, chunk, part);
-    k_cell_chunk_offsets<<<1, 1024, 0, s>>>(part, nchunk);
-    k_cell_apply<<<nchunk, 256, 0, s>>>(sb.hist, nblk, chunk, part);
-    e = hipGetLastError();
     if (e != hipSuccess) return e;
     k_cell_scatter<<<nblk, kSkyBlock, 0, s>>>(sb.xeq_in, n_src, ld, sb.cell, sb.hist, xeq, sb.perm);
     return hipGetLastError();
@@ -405,30 +477,26 @@ hipError_t launch_rotmats(const double *lsts, int32_t n_time, double latitude, d
     return hipGetLastError();
 }
 
-hipError_t launch_prep_inputs(const double *antpos, int32_t n_ant, const int32_t *beam_idx, int32_t n_beam,
-                              const double *flux, int64_t n_flux, int pol, double *antc, int32_t *bidx,
-                              int32_t *flags, hipStream_t s) {
-    k_prep_ant<<<1, kSkyBlock, 0, s>>>(antpos, n_ant, beam_idx, n_beam, antc, bidx, flags);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || n_flux <= 0 || !flux) return e;
-    int64_t blocks = (n_flux + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
-    k_check_flux<<<(unsigned)blocks, 256, 0, s>>>(flux, n_flux, pol, flags);
-    return hipGetLastError();
-}
-
 hipError_t launch_sky(const SkyBufs &b, int32_t t0, int32_t ntb, int64_t c0, int64_t nsrc_chunk, hipStream_t s) {
     if (ntb <= 0) return hipSuccess;
     int nblk = (int)((nsrc_chunk + kSkyBlock - 1) / kSkyBlock);
     if (nblk == 0) nblk = 1;
     dim3 g(nblk, ntb);
+    if (nblk <= kOneBlocks) {
+        k_sky_scatter<COUNTED><<<g, kSkyBlock, 0, s>>>(b, t0, c0, nsrc_chunk, nblk);
+        return hipGetLastError();
+    }
     k_sky_count<<<g, kSkyBlock, 0, s>>>(b, t0, c0, nsrc_chunk, nblk);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (nblk <= kFoldBlocks) {
+        k_sky_scatter<SUMMED><<<g, kSkyBlock, 0, s>>>(b, t0, c0, nsrc_chunk, nblk);
+        return hipGetLastError();
+    }
     k_sky_scan<<<ntb, 1024, 0, s>>>(b, nblk);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_sky_scatter<<<g, kSkyBlock, 0, s>>>(b, t0, c0, nsrc_chunk, nblk);
+    k_sky_scatter<SCANNED><<<g, kSkyBlock, 0, s>>>(b, t0, c0, nsrc_chunk, nblk);
     return hipGetLastError();
 }
 

@@ -23,7 +23,7 @@ namespace mv {
 
 namespace {
 
-constexpr int kAntGroup = 16;
+constexpr int kAntGroup = 16;  // antennas of a block's loop at most
 
 __device__ inline uint32_t bf16_bits_rne(float x) {
     uint32_t u = __float_as_uint(x);
@@ -42,7 +42,7 @@ __device__ inline void split_bf16(float re, float im, uint32_t &hi, uint32_t &lo
 }
 
 template <int PREC>
-__global__ void __launch_bounds__(256) k_zform(ZformArgs a, Batch bt) {
+__global__ void __launch_bounds__(256) k_zform(ZformArgs a, Batch bt, int ant_group) {
     typedef typename std::conditional<PREC == P64, double, float>::type R;
     typedef typename std::conditional<PREC == P64, double2, float2>::type C;
     const int inst = blockIdx.z;
@@ -54,8 +54,8 @@ __global__ void __launch_bounds__(256) k_zform(ZformArgs a, Batch bt) {
     const int64_t kpad = ((nx * M + kColPad - 1) / kColPad) * kColPad;
     const int64_t mpad = (kpad + nx - 1) / nx;
     if (m >= mpad) return;
-    const int a0 = blockIdx.y * kAntGroup;
-    const int a1 = a0 + kAntGroup < a.n_ant ? a0 + kAntGroup : a.n_ant;
+    const int a0 = blockIdx.y * ant_group;
+    const int a1 = a0 + ant_group < a.n_ant ? a0 + ant_group : a.n_ant;
     const bool live = m < M;
     const int64_t ld = a.ld_src;
     const int64_t zinst = (int64_t)inst * a.n_rows_pad * a.ldz;
@@ -160,13 +160,20 @@ __global__ void k_z_import(const void *Zin, int n_row, int64_t n_col, int64_t ld
 
 hipError_t launch_zform(int prec, const ZformArgs &a, const Batch &bt, hipStream_t s) {
     if (bt.n_inst <= 0 || a.max_m <= 0) return hipSuccess;
-    dim3 g((unsigned)((a.max_m + 255) / 256), (a.n_ant + kAntGroup - 1) / kAntGroup, bt.n_inst);
+    // Fewer antennas per block while the blocks would not give each CU four: the serial
+    // chain of phases is what a small call waits for (37 antennas, 2000 sources, 8
+    // instances: 17.2 us in groups of 16, 10.8 in groups of 2; with two or eight blocks a
+    // CU 11.4 and 12.4).
+    int group = kAntGroup;
+    const int64_t bx = (a.max_m + 255) / 256;
+    while (group > 1 && bx * ((a.n_ant + group - 1) / group) * bt.n_inst < 4 * 256) group /= 2;
+    dim3 g((unsigned)bx, (a.n_ant + group - 1) / group, bt.n_inst);
     if (prec == P64)
-        k_zform<P64><<<g, 256, 0, s>>>(a, bt);
+        k_zform<P64><<<g, 256, 0, s>>>(a, bt, group);
     else if (prec == P32)
-        k_zform<P32><<<g, 256, 0, s>>>(a, bt);
+        k_zform<P32><<<g, 256, 0, s>>>(a, bt, group);
     else
-        k_zform<PB3><<<g, 256, 0, s>>>(a, bt);
+        k_zform<PB3><<<g, 256, 0, s>>>(a, bt, group);
     return hipGetLastError();
 }
 

@@ -551,15 +551,16 @@ matvis_status enqueue_simulate(matvis_ctx *c, const double *antpos, const int32_
     const matvis_config &g = c->cfg;
     const int prec = g.precision;
     const int pol = (g.flags & MATVIS_FLAG_POLARISED_SKY) ? 1 : 0;
-    STEP(c, MATVIS_STEP_OTHER, s,
-         launch_prep_inputs(antpos, g.n_ant, beam_idx, g.n_beam, flux, (int64_t)n_freq * n_src, pol, c->antc,
-                            c->bidx, c->flags, s));
+    const SortBufs sort{c->xeq_in, c->cell, c->cell_hist, c->perm};
     STEP(c, MATVIS_STEP_SKY, s,
-         launch_xeq_sorted(radec, n_src, g.max_src, SortBufs{c->xeq_in, c->cell, c->cell_hist, c->perm}, c->xeq, s));
+         launch_prepare(PrepareArgs{radec, n_src, g.max_src, sort, antpos, beam_idx, g.n_ant, g.n_beam, c->antc,
+                                    c->bidx, lsts, n_time, g.latitude_rad, c->rot, flux, (int64_t)n_freq * n_src,
+                                    pol, c->flags},
+                        s));
+    STEP(c, MATVIS_STEP_SKY, s, launch_sort(n_src, g.max_src, sort, c->xeq, s));
     if (c->gridT)
         STEP(c, MATVIS_STEP_BEAM, s,
              launch_grid_interleave(prec, grid, g.n_beam, n_freq, g.n_feed * g.n_ax, g.n_za, g.n_az, c->gridT, s));
-    STEP(c, MATVIS_STEP_SKY, s, launch_rotmats(lsts, n_time, g.latitude_rad, c->rot, s));
     const int64_t n_chunks = std::max<int64_t>(1, (n_src + c->chunk - 1) / c->chunk);
     const int ncomp = g.n_feed * g.n_ax;
     const int B_cap = c->ntb * c->nfb;  // instances the batch buffers hold
