@@ -53,10 +53,10 @@ typedef enum {
 /* Arithmetic of step (v), V = Z Z^H.
  *   FP64  : complex128 beams, Z, products and output;
  *   FP32  : complex64 beams and Z, FP32 products accumulated in FP32 over bounded
- *           source chunks, chunks combined in FP64, complex64 out (on
- *           MATVIS_PATH_SOURCES and _FUSED_BLOCKS every FP32 operand is split
- *           exactly into three bf16 terms and multiplied on bf16 MFMA, with
- *           smaller error than FP32 MFMA; elsewhere FP32 MFMA);
+ *           source chunks, chunks combined in FP64, complex64 out (where Z is
+ *           formed inside the product every FP32 operand is split exactly into
+ *           three bf16 terms and multiplied on bf16 MFMA, with smaller error than
+ *           FP32 MFMA; FP32 MFMA under MATVIS_FLAG_UNFUSED);
  *   BF16X3: Z in FP32 split into bf16 hi + lo parts, V ~ hi hi^T + hi lo^T +
  *           lo hi^T on bf16 MFMA with FP32 accumulation, complex64 out.
  * In every mode the rotation and the phase range reduction are FP64. */
@@ -91,9 +91,10 @@ typedef struct {
     int32_t batch_freq;   /* frequencies per device batch; 0 = automatic */
     int32_t flags;        /* MATVIS_FLAG_* bits */
     int64_t ksplit;       /* Z columns summed by one product work item before its partial
-                             is stored (a multiple of 64); 0 = automatic.  FP32
-                             accumulators see ksplit / 2 sequential updates, so this
-                             bounds their rounding; the partials are summed in FP64. */
+                             is stored at most (a multiple of 64); 0 = automatic.
+                             FP32 accumulators see up to ksplit / 2 sequential
+                             updates, so this bounds their rounding; the partials are
+                             summed in FP64. */
     int32_t tile;         /* product kernel variant, 0 = the library's choice.  Bits 0-3:
                              Z rows per 16-source stage formed by the multiply-first
                              waves, in units of 32 antennas (2, 3 or 4; 3 by default),
@@ -356,8 +357,8 @@ typedef enum {
     MATVIS_STEP_REDUCE = 4, /* k-split reduction + Hermitian fill */
     MATVIS_STEP_OTHER = 5,  /* input preparation and the work-list prefix */
     MATVIS_STEP_HERK_PAIRS = 6, /* the product's second launch, where it has one: the
-                                   off-diagonal antenna-block pairs (paths SOURCES and
-                                   FUSED); the product's time is HERK + HERK_PAIRS */
+                                   off-diagonal antenna-block pairs (path SOURCES); the
+                                   product's time is HERK + HERK_PAIRS */
     MATVIS_N_STEPS = 7
 } matvis_step;
 
@@ -371,7 +372,9 @@ matvis_status matvis_profile_read(matvis_ctx *ctx, double *ms, int64_t *launches
  *                          takes the axis sum per source first and forms Z inside the
  *                          product (2 feeds x 2 axes, one shared beam, without
  *                          MATVIS_FLAG_UNFUSED);
- *   MATVIS_PATH_FUSED      Z formed in LDS per 128-row super-tile pair;
+ *   MATVIS_PATH_FUSED      Z formed in LDS in blocks of 16 rows and multiplied in
+ *                          16 x 16 tiles of the lower triangle (2 feeds x 2 axes
+ *                          with one shared beam: over sources, as _SOURCES);
  *   MATVIS_PATH_FUSED_ROWS Z formed once per (instance, k-split) for all of
  *                          129..256 rows (BF16X3);
  *   MATVIS_PATH_SOURCES    2 feeds x 2 axes with one shared beam, more than

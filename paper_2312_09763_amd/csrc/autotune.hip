@@ -190,7 +190,7 @@ extern "C" matvis_status matvis_autotune(const matvis_config *base, const double
     // candidate values per axis (0 = the library's choice)
     const int prec = prec_of(base->precision);
     const bool over_sources = path0 == MATVIS_PATH_SOURCES, three_blocks = path0 == MATVIS_PATH_FUSED_BLOCKS;
-    const int64_t kdef = mv::default_ksplit(prec, over_sources, three_blocks);
+    const int64_t kdef = mv::default_ksplit(prec, path0);
     std::vector<long long> tiles = {0};  // forming split, bits 0-3
     if (over_sources) tiles.push_back(2);
     if (three_blocks) tiles.insert(tiles.end(), {2, 4});

@@ -249,12 +249,12 @@ struct FusedArgs {
 };
 // which: FUSED_ALL every launch of the path; FUSED_FIRST its first launch only (the
 // diagonal blocks, or the only launch); FUSED_PAIRS its second launch only (the
-// off-diagonal block pairs of paths SOURCES and FUSED; nothing on the others).
+// off-diagonal block pairs of path SOURCES; nothing on the others).  Path FUSED is
+// launch_tiles.
 enum { FUSED_ALL = 0, FUSED_FIRST = 1, FUSED_PAIRS = 2 };
 hipError_t launch_herk_fused(int prec, const FusedArgs &a, hipStream_t s, int which = FUSED_ALL);
 // whether the path of these arguments has a second (block-pair) launch
 bool fused_has_pairs(int prec, const FusedArgs &a);
-int herk_fused_occupancy(int prec);
 // FP32 products on bf16 matrix cores (kernels_herk_x6.hip): the launches of
 // launch_herk_fused for FP32.
 hipError_t launch_coh_x6(const FusedArgs &a, hipStream_t s);    // diagonal blocks, product over sources
@@ -266,7 +266,7 @@ bool f64_over_sources(int n_feed, int n_ax, int n_beam);
 int f64_items(int n_ant);
 hipError_t launch_herk_f64(const FusedArgs &a, hipStream_t s);
 // the library's k-split for a precision and product path (matvis_config.ksplit = 0)
-int64_t default_ksplit(int prec, bool over_sources, bool three_blocks);
+int64_t default_ksplit(int prec, int path);
 // product kernel launch_herk_fused picks (a matvis_product_path value, never Z_IN_HBM)
 int fused_path(int prec, int n_feed, int n_ax, int n_beam, int n_ant, int n_rows_pad);
 
@@ -290,20 +290,24 @@ struct SubmatArgs {
     void *part;              // [n_inst][max_splits][n_tiles][ST][ST] complex partials
 };
 hipError_t launch_submat(int prec, const SubmatArgs &a, hipStream_t s);
-// The same product with Z formed in LDS (FP32 / BF16X3 fused contexts):
-//   Z[(a, p), (m, k)] = B[inst][beam(a)][p][k][m] F_a(m).
-constexpr int kPairTile = 16;    // output tile side
-constexpr int kPairBlocks = 22;  // blocks of 16 rows that one workgroup can stage twice in LDS
-constexpr int kPairTiles = 96;   // tiles of one workgroup: 6 a wave
-struct PairBundle {
+// Products over lists of 16 x 16 tiles with Z formed in LDS (kernels_tiles.hip, FP32 and
+// BF16X3):  Z[(a, p), (m, k)] = B[inst][beam(a)][p][k][m] F_a(m).
+constexpr int kTile = 16;       // output tile side
+constexpr int kWaveTiles = 6;   // tiles of a wave
+// blocks of 16 rows that a workgroup of that many waves can stage twice in its LDS
+__host__ __device__ constexpr int tile_blocks(int waves) { return waves == 16 ? 22 : waves == 8 ? 9 : 5; }
+struct TileBundle {
     int32_t row0, n_rows;    // its rows (whole blocks of 16) in rows[]
     int32_t tile0, n_tiles;  // its tiles in tiles[]
 };
-struct PairArgs {
-    const int32_t *rows;        // Z rows a n_feed + p of every bundle's blocks, -1 = padding
+struct TileArgs {
+    const int32_t *rows;        // Z rows a n_feed + p (coherent: 3 a + plane) of every bundle's blocks, -1 = padding
     const int32_t *tiles;       // [n_tiles] row block | column block << 8, within the bundle
-    const PairBundle *bundles;  // [n_bundle]
-    int32_t n_tiles, n_bundle;
+    const int32_t *dst;         // [n_tiles] the tile's first element in a partial (coherent: antenna blocks I | J << 8,
+                                // p << 16, q << 17)
+    const TileBundle *bundles;  // [n_bundle]
+    int32_t n_bundle, waves;    // waves: tile_waves of the largest bundle
+    int32_t coherent;           // 1: planes of one shared 2 x 2 beam, K = count
     const int32_t *count;       // [nslots] visible counts (K = n_ax * count)
     int32_t n_ax, n_feed, n_beam, nfb, n_inst, f0;
     int32_t n_split;            // k-splits of split_cols(K, n_split) columns
@@ -313,9 +317,12 @@ struct PairArgs {
     const double *s_hat;        // [nslots][3][ld_src]
     const void *B;              // sqrt(I) A (or A M), complex64 [n_inst][n_beam][n_feed][n_ax][ld_src]
     int64_t ld_src;
-    void *part;                 // [n_inst][n_split][n_tiles][16][16] complex64 partials
+    void *part;                 // [n_inst][n_split][part_stride] complex64 partials, rows of ld elements
+    int64_t part_stride;
+    int32_t ld;
 };
-hipError_t launch_pair_tiles(int prec, const PairArgs &a, hipStream_t s);
+int tile_waves(int n_rows, int n_tiles);
+hipError_t launch_tiles(int prec, const TileArgs &a, hipStream_t s);
 // Columns of each of n k-splits of K columns, whole stages of 16 (the last ones may be short or empty)
 __host__ __device__ inline int64_t split_cols(int64_t K, int64_t n) { return ((K + n - 1) / n + 15) / 16 * 16; }
 struct SubmatReduceArgs {
@@ -353,8 +360,8 @@ struct ReduceArgs {
     const int32_t *count;
     int64_t fixed_k;
     int32_t n_ax, nfb, n_inst;
-    int64_t ksplit;
-    const int32_t *nsplit;   // [n_inst] k-splits per instance, or null: ceil(K / ksplit)
+    int64_t ksplit;          // columns per split, or 0: split_cols(K, max_splits)
+    const int32_t *nsplit;   // [n_inst] k-splits per instance, or null: ceil(K / columns per split)
     double *vacc;            // [n_inst][n_rows][n_rows] complex128 running sums (multi-chunk)
     int32_t first, last;     // first chunk: assign; last chunk: write the output
     void *out;               // output base

@@ -467,7 +467,7 @@ __global__ void __launch_bounds__(256) k_submat_reduce(SubmatReduceArgs a) {
     const int64_t e = gid % per_inst;
     const int64_t K = inst_k(a.count, a.fixed_k, a.n_ax, a.nfb, inst);
     const int64_t kc = a.ksplit > 0 ? a.ksplit : split_cols(K, a.max_splits);
-    const int ns = (int)((K + kc - 1) / kc);
+    const int ns = K > 0 ? (int)((K + kc - 1) / kc) : 0;
     const int32_t tile = a.loc[2 * e], off = a.loc[2 * e + 1];
     const int ST2 = a.st * a.st;
     double re = 0.0, im = 0.0;
@@ -517,7 +517,8 @@ __global__ void __launch_bounds__(1024 / NR) k_reduce_tiles(ReduceArgs a) {
     const int C = t;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     const int64_t K = a.count ? (int64_t)a.n_ax * a.count[inst / a.nfb] : a.fixed_k;
-    const int ns = a.nsplit ? a.nsplit[inst] : (int)((K + a.ksplit - 1) / a.ksplit);
+    const int64_t kc = a.ksplit > 0 ? a.ksplit : split_cols(K, a.max_splits);
+    const int ns = a.nsplit ? a.nsplit[inst] : K > 0 ? (int)((K + kc - 1) / kc) : 0;
     const PartT *P = (const PartT *)a.part + (int64_t)inst * a.max_splits * Np * Np;
     double2 *acc = a.vacc ? (double2 *)a.vacc + (int64_t)inst * N * N : nullptr;
     OutT *out = (OutT *)a.out;

@@ -2,28 +2,17 @@
 // tile by tile, and consumed there by the MFMA product of Eq. (zz); Z never
 // reaches HBM.
 //
-// A 512-thread workgroup holds a (instance, k-split, lower super-tile I >= J)
-// work item of the persistent work list (same list as the unfused product).
-// Waves 0-3 are consumers: each owns a 64 x 64 wave tile of the 128 x 128
-// super-tile and runs the MFMA products exactly like the unfused kernel.
-// Waves 4-7 are producers: for the next stage of KC = 32 complex columns
-// (KC / n_ax sources) they compute, for every antenna of row blocks I and J,
-//   p = (nu/c) x_a . s_m in cycles (FP64),  r = p - rint(p),
-//   F = cospi(2r) - i sinpi(2r)           (FP32 sincospi),
+// These are the BF16X3 products of larger arrays (FP32: kernels_herk_x6.hip; small arrays
+// and several beams: kernels_tiles.hip).  A 512-thread workgroup takes (instance, k-split,
+// block) items of the persistent work list; every thread forms a share of the next stage's
+// rows,
+//   p = (nu/c) x_a . s_m in cycles (FP64),  r = fract(p),
+//   F = cos(2 pi r) - i sin(2 pi r)       (hardware sine and cosine),
 //   Z[(a, p)][(m, k)] = B_{beam(a), p, k}(m) F,  B = sqrt(I) A (from the beam step),
-// and write it to the other LDS buffer (complex64 on FP32; bf16 hi / lo planes
-// on BF16X3); the consumers form the last rows of each stage after their
-// products.  One barrier per stage swaps the buffers, so the VALU work of
-// the producers overlaps the matrix-core work of the consumers on every SIMD
-// (one wave of each kind per SIMD).
-//
-// Per item, the scaled antenna positions (nu/c) x_a and beam indices of the
-// item's rows are staged once in LDS; per stage, each producer thread's
-// source direction and beam values were loaded into registers during the
-// previous stage, so no producer waits on device memory in its inner loop.
-// Per source the item reads 24 B of direction and 8 n_feed n_ax B of beam;
-// everything else is arithmetic.  Partials go to the same slots as the
-// unfused product and are summed by k_reduce.
+// into the other LDS buffer as bf16 hi / lo planes, and every wave multiplies: half of the
+// waves before they form and half after, so that vector and matrix work overlap on every
+// SIMD.  One barrier per stage swaps the buffers.  Partials go to the same slots as the
+// unfused product and are summed by k_reduce_tiles.
 #include <type_traits>
 
 #include "herk_tiles.h"
@@ -33,440 +22,13 @@ namespace mv {
 
 namespace {
 
-constexpr int kWT = 64, kKC = 32;
+constexpr int kKC = 32;
 
-__device__ inline u32x4 bf16_rot(u32x4 v) {
-    u32x4 r;
-    for (int q = 0; q < 4; q++) r[q] = __builtin_amdgcn_alignbit(v[q], v[q], 16) ^ 0x80000000u;
-    return r;
-}
-
-template <int PREC>
 struct FL {
-    static constexpr int EBP = PREC == PB3 ? 4 : 8;      // bytes per complex per plane
-    static constexpr int PLANES = PREC == PB3 ? 2 : 1;
-    static constexpr int PLANEB = kKC * EBP;              // bytes of one plane of a staged row
-    static constexpr int RS = kKC * EBP * PLANES + 16;    // LDS row stride
+    static constexpr int PLANEB = kKC * 4;                // bytes of one plane of a staged row
+    static constexpr int RS = 2 * PLANEB + 16;            // LDS row stride
     static constexpr int BUF = 2 * kST * RS;              // one stage buffer (rows of I and J)
-    static constexpr int TAB = 2 * kST;                   // antenna table entries (rows of I and J, n_feed = 1)
 };
-
-// ---------------------------------------------------------------------------
-// Consumers.  An accumulator pair (re, im) per 16 x 16 output tile; one
-// k-stage (KC = 32 complex columns) is read from the LDS stage buffer, whose
-// rows 0..127 hold block I and rows 128..255 block J.
-//
-// BF16X3 tile update with row operand (Ah, Al, Wh, Wl) and column operand
-// (Bh, Bl): re += Ah Bh + Ah Bl + Al Bh, im += Wh Bh + Wh Bl + Wl Bh, and on
-// output-diagonal tiles also the lo lo products (a one-signed |lo|^2 bias
-// there; elsewhere it averages out and is omitted).
-// FP32 tile update with one complex element per lane (a, b):
-// re += a.re b.re + a.im b.im, im += a.im b.re - a.re b.im.
-// ---------------------------------------------------------------------------
-
-struct RowB3 {
-    bf16x8 h, l, wh, wl;
-};
-
-template <int PREC>
-__device__ __forceinline__ RowB3 load_row_b3(const unsigned char *buf, int row, int ks, int lk) {
-    typedef FL<PREC> L;
-    const unsigned char *p = buf + row * L::RS + ks * 64 + lk * 16;
-    const u32x4 h = *(const u32x4 *)p;
-    const u32x4 l = *(const u32x4 *)(p + L::PLANEB);
-    RowB3 r;
-    r.h = __builtin_bit_cast(bf16x8, h);
-    r.l = __builtin_bit_cast(bf16x8, l);
-    r.wh = __builtin_bit_cast(bf16x8, bf16_rot(h));
-    r.wl = __builtin_bit_cast(bf16x8, bf16_rot(l));
-    return r;
-}
-
-// Off-diagonal super-tile: wave tile of 4 x 4 tiles (rows arow.., columns brow..).
-template <int PREC>
-__device__ __forceinline__ void consume_full(const unsigned char *buf, int arow, int brow, int l16, int lk,
-                                             f32x4 (&re)[16], f32x4 (&im)[16]) {
-    typedef FL<PREC> L;
-    if constexpr (PREC == PB3) {
-#pragma unroll
-        for (int ks = 0; ks < kKC / 16; ks++) {
-            RowB3 A[kTI];
-#pragma unroll
-            for (int i = 0; i < kTI; i++) A[i] = load_row_b3<PREC>(buf, arow + 16 * i + l16, ks, lk);
-            const unsigned char *pc = buf + (brow + l16) * L::RS + ks * 64 + lk * 16;
-            u32x4 nh = *(const u32x4 *)pc, nl = *(const u32x4 *)(pc + L::PLANEB);
-#pragma unroll
-            for (int j = 0; j < kTI; j++) {
-                const bf16x8 Bh = __builtin_bit_cast(bf16x8, nh);
-                const bf16x8 Bl = __builtin_bit_cast(bf16x8, nl);
-                if (j + 1 < kTI) {
-                    const unsigned char *p = pc + 16 * (j + 1) * L::RS;
-                    nh = *(const u32x4 *)p;
-                    nl = *(const u32x4 *)(p + L::PLANEB);
-                }
-#pragma unroll
-                for (int i = 0; i < kTI; i++) {
-                    re[i * kTI + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[i].h, Bh, re[i * kTI + j], 0, 0, 0);
-                    im[i * kTI + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[i].wh, Bh, im[i * kTI + j], 0, 0, 0);
-                }
-#pragma unroll
-                for (int i = 0; i < kTI; i++) {
-                    re[i * kTI + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[i].h, Bl, re[i * kTI + j], 0, 0, 0);
-                    im[i * kTI + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[i].wh, Bl, im[i * kTI + j], 0, 0, 0);
-                }
-#pragma unroll
-                for (int i = 0; i < kTI; i++) {
-                    re[i * kTI + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[i].l, Bh, re[i * kTI + j], 0, 0, 0);
-                    im[i * kTI + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[i].wl, Bh, im[i * kTI + j], 0, 0, 0);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int kk = 0; kk < kKC; kk += 4) {
-            float2 av[kTI], bv[kTI];
-#pragma unroll
-            for (int i = 0; i < kTI; i++) av[i] = *(const float2 *)(buf + (arow + 16 * i + l16) * L::RS + (kk + lk) * 8);
-#pragma unroll
-            for (int j = 0; j < kTI; j++) bv[j] = *(const float2 *)(buf + (brow + 16 * j + l16) * L::RS + (kk + lk) * 8);
-#pragma unroll
-            for (int i = 0; i < kTI; i++) {
-                const float nre = -av[i].x;
-#pragma unroll
-                for (int j = 0; j < kTI; j++) {
-                    re[i * kTI + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i].x, bv[j].x, re[i * kTI + j], 0, 0, 0);
-                    im[i * kTI + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i].y, bv[j].x, im[i * kTI + j], 0, 0, 0);
-                }
-#pragma unroll
-                for (int j = 0; j < kTI; j++) {
-                    re[i * kTI + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i].y, bv[j].y, re[i * kTI + j], 0, 0, 0);
-                    im[i * kTI + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(nre, bv[j].y, im[i * kTI + j], 0, 0, 0);
-                }
-            }
-        }
-    }
-}
-
-// Diagonal super-tile: its lower triangle has 36 tiles; wave W takes the
-// 16-row blocks W and 7 - W, i.e. tiles (7 - W, 0..7 - W) in slots
-// 0..7 - W and (W, 0..W) in slots 8 - W.., nine tiles for every wave.
-template <int PREC, int W>
-__device__ __forceinline__ void consume_tri(const unsigned char *buf, int l16, int lk, f32x4 (&re)[16],
-                                            f32x4 (&im)[16]) {
-    typedef FL<PREC> L;
-    constexpr int R1 = 7 - W, R0 = W, NCOL = 8 - W;
-    if constexpr (PREC == PB3) {
-#pragma unroll
-        for (int ks = 0; ks < kKC / 16; ks++) {
-            const RowB3 a1 = load_row_b3<PREC>(buf, 16 * R1 + l16, ks, lk);
-            const RowB3 a0 = load_row_b3<PREC>(buf, 16 * R0 + l16, ks, lk);
-            // column fragments are prefetched one tile ahead; the scheduling fences
-            // keep the compiler from hoisting every column's loads (register pressure)
-            const unsigned char *pc = buf + l16 * L::RS + ks * 64 + lk * 16;
-            u32x4 nh = *(const u32x4 *)pc, nl = *(const u32x4 *)(pc + L::PLANEB);
-#pragma unroll
-            for (int c = 0; c < NCOL; c++) {
-                const bf16x8 Bh = __builtin_bit_cast(bf16x8, nh);
-                const bf16x8 Bl = __builtin_bit_cast(bf16x8, nl);
-                if (c + 1 < NCOL) {
-                    const unsigned char *p = pc + 16 * (c + 1) * L::RS;
-                    nh = *(const u32x4 *)p;
-                    nl = *(const u32x4 *)(p + L::PLANEB);
-                }
-                const int s1 = c, s0 = NCOL + c;
-                const bool two = c <= R0;
-                re[s1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1.h, Bh, re[s1], 0, 0, 0);
-                im[s1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1.wh, Bh, im[s1], 0, 0, 0);
-                if (two) {
-                    re[s0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0.h, Bh, re[s0], 0, 0, 0);
-                    im[s0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0.wh, Bh, im[s0], 0, 0, 0);
-                }
-                re[s1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1.h, Bl, re[s1], 0, 0, 0);
-                im[s1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1.wh, Bl, im[s1], 0, 0, 0);
-                if (two) {
-                    re[s0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0.h, Bl, re[s0], 0, 0, 0);
-                    im[s0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0.wh, Bl, im[s0], 0, 0, 0);
-                }
-                re[s1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1.l, Bh, re[s1], 0, 0, 0);
-                im[s1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1.wl, Bh, im[s1], 0, 0, 0);
-                if (two) {
-                    re[s0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0.l, Bh, re[s0], 0, 0, 0);
-                    im[s0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0.wl, Bh, im[s0], 0, 0, 0);
-                }
-                if (c == R1) {
-                    re[s1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1.l, Bl, re[s1], 0, 0, 0);
-                    im[s1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1.wl, Bl, im[s1], 0, 0, 0);
-                }
-                if (c == R0) {
-                    re[s0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0.l, Bl, re[s0], 0, 0, 0);
-                    im[s0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0.wl, Bl, im[s0], 0, 0, 0);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int kk = 0; kk < kKC; kk += 4) {
-            const float2 a1 = *(const float2 *)(buf + (16 * R1 + l16) * L::RS + (kk + lk) * 8);
-            const float2 a0 = *(const float2 *)(buf + (16 * R0 + l16) * L::RS + (kk + lk) * 8);
-            const float n1 = -a1.x, n0 = -a0.x;
-#pragma unroll
-            for (int c = 0; c < NCOL; c++) {
-                const float2 b = *(const float2 *)(buf + (16 * c + l16) * L::RS + (kk + lk) * 8);
-                const int s1 = c, s0 = NCOL + c;
-                re[s1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.x, b.x, re[s1], 0, 0, 0);
-                im[s1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.y, b.x, im[s1], 0, 0, 0);
-                if (c <= R0) {
-                    re[s0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.x, b.x, re[s0], 0, 0, 0);
-                    im[s0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.y, b.x, im[s0], 0, 0, 0);
-                }
-                re[s1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.y, b.y, re[s1], 0, 0, 0);
-                im[s1] = __builtin_amdgcn_mfma_f32_16x16x4f32(n1, b.y, im[s1], 0, 0, 0);
-                if (c <= R0) {
-                    re[s0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.y, b.y, re[s0], 0, 0, 0);
-                    im[s0] = __builtin_amdgcn_mfma_f32_16x16x4f32(n0, b.y, im[s0], 0, 0, 0);
-                }
-            }
-        }
-    }
-}
-
-// One launch per item kind: DIAG = the nb diagonal super-tiles (I, I) of each
-// (instance, k-split), consumed with the triangular wave mapping; otherwise the
-// nb (nb - 1) / 2 off-diagonal ones (I > J), consumed as 2 x 2 wave tiles.
-// a.work is the per-instance prefix of k-splits; instance i owns items
-// [work[i] n_kind, work[i + 1] n_kind).
-template <int PREC, int NF, int NX, bool DIAG>
-__global__ void __launch_bounds__(512, 1) k_herk_fused(FusedArgs a) {
-    typedef FL<PREC> L;
-    constexpr int RS = L::RS;
-    constexpr int NC = NF * NX;       // beam components per source
-    constexpr int SPS = kKC / NX;     // sources per stage
-    constexpr int APB = kST / NF;     // antennas per row block
-    constexpr int NG = 256 / SPS;     // thread groups per wave kind (one source per thread)
-    __shared__ __attribute__((aligned(16))) unsigned char lds[2 * L::BUF];
-    __shared__ AntEntry tab[2 * APB];
-
-    const int tid = threadIdx.x;
-    const int lane = lane_id();
-    const int wave = tid / kWave;
-    const bool consumer = wave < 4;
-    const int wr = (wave & 3) >> 1, wc = wave & 1;
-    const int l16 = lane & 15, lk = lane >> 4;
-    const int Np = a.n_rows_pad;
-    const int nb = Np / kST;
-    const int n_kind = DIAG ? nb : nb * (nb - 1) / 2;
-    const int total = a.work[a.n_inst] * n_kind;
-    const int per_xcd = a.grid / 8;
-    const int slot_x = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    // forming roles: source msl of the stage; group g of the thread's wave kind
-    const int msl = tid % SPS, g = (tid % 256) / SPS;
-    constexpr bool diag = DIAG;
-
-    for (int item = slot_x; item < total; item += a.grid) {
-        int lo = 0, hi = a.n_inst - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (a.work[mid] * n_kind <= item)
-                lo = mid;
-            else
-                hi = mid - 1;
-        }
-        const int inst = lo;
-        const int local = item - a.work[inst] * n_kind;
-        const int s = local / n_kind;
-        int st = local % n_kind;
-        int I, J;
-        if (DIAG) {
-            I = J = st;
-        } else {  // st enumerates the pairs (1, 0), (2, 0), (2, 1), (3, 0), ...
-            I = 1;
-            while (st >= I) {
-                st -= I;
-                I++;
-            }
-            J = st;
-        }
-        const int tslot = inst / a.nfb;
-        const int f = a.f0 + inst % a.nfb;
-        const int64_t M = a.count[tslot];
-        const int64_t ms_per_split = a.kcols[inst] / NX;
-        const int64_t m_begin = (int64_t)s * ms_per_split;
-        const int64_t m_end = m_begin + ms_per_split < M ? m_begin + ms_per_split : M;
-        const int n_stage = (int)((m_end - m_begin + SPS - 1) / SPS);
-        const double *sh = a.s_hat + (int64_t)tslot * 3 * a.ld_src;
-        const float2 *Bm = (const float2 *)a.B + (int64_t)inst * a.n_beam * NC * a.ld_src;
-        const int na_tot = (diag ? 1 : 2) * APB;
-
-        // antenna table of this item's rows
-        {
-            const double nu_c = a.freqs[f] / kSpeedOfLight;
-            for (int as = tid; as < na_tot; as += 512) {
-                const int ant = as < APB ? I * APB + as : J * APB + (as - APB);
-                AntEntry e;
-                if (ant < a.n_ant) {
-                    e.ux = nu_c * a.antc[3 * ant];
-                    e.uy = nu_c * a.antc[3 * ant + 1];
-                    e.uz = nu_c * a.antc[3 * ant + 2];
-                    e.b = a.bidx[ant];
-                } else {
-                    e.ux = e.uy = e.uz = 0.0;
-                    e.b = -1;
-                }
-                e.pad = 0;
-                tab[as] = e;
-            }
-        }
-
-        // direction and beam of this thread's source in the next stage
-        double sx = 0.0, sy = 0.0, sz = 0.0;
-        float2 w[NC];
-        bool live = false;
-        int64_t m_cur = 0;
-        auto fetch = [&](int stage) {
-            m_cur = m_begin + (int64_t)stage * SPS + msl;
-            live = stage < n_stage && m_cur < m_end;
-            sx = sy = sz = 0.0;
-            for (int c = 0; c < NC; c++) w[c] = make_float2(0.f, 0.f);
-            if (live) {
-                sx = sh[m_cur];
-                sy = sh[a.ld_src + m_cur];
-                sz = sh[2 * a.ld_src + m_cur];
-                if (a.n_beam == 1)
-                    for (int c = 0; c < NC; c++) w[c] = Bm[(int64_t)c * a.ld_src + m_cur];
-            }
-        };
-
-        // ---- producer: form the Z rows of blocks I (and J) for one stage.
-        // The fringe factor uses the hardware sine / cosine, whose argument is in
-        // revolutions, on the FP64-reduced phase r in [-1/2, 1/2]:
-        // F = exp(-2 pi i r) = cos(-r rev) + i sin(-r rev).  Rows past n_ant and
-        // sources past the split are written as zeros (mask factor 0).
-        // The consumers form the last rows of each stage after their products (an
-        // off-diagonal item's rows: 3/8 with one beam component, whose rows are
-        // cheap to form, else 1/4; half that on a diagonal item, where the products
-        // are fewer); the producers form the rest.
-        const int n_crow = (NC == 1 ? 3 * na_tot / 8 : na_tot / 4) / (diag ? 2 : 1);
-        const int row0 = consumer ? na_tot - n_crow : 0, row1 = consumer ? na_tot : na_tot - n_crow;
-        auto produce = [&](unsigned char *buf) {
-            const bool lv = live;
-            const double x0 = sx, x1 = sy, x2 = sz;
-            const int64_t m = m_cur;
-            float2 wl[NC];
-            for (int c = 0; c < NC; c++) wl[c] = w[c];
-            const bool multi_beam = a.n_beam != 1;
-            int cur_b = multi_beam ? -1 : 0;
-            for (int as = row0 + g; as < row1; as += NG) {
-                const AntEntry e = tab[as];
-                if (multi_beam && lv && e.b >= 0 && e.b != cur_b) {
-                    for (int c = 0; c < NC; c++) wl[c] = Bm[((int64_t)e.b * NC + c) * a.ld_src + m];
-                    cur_b = e.b;
-                }
-                const double p = e.ux * x0 + e.uy * x1 + e.uz * x2;
-                const float r = (float)(p - rint(p));
-                const float msk = (lv && e.b >= 0) ? 1.0f : 0.0f;
-                const float sn = msk * __builtin_amdgcn_sinf(-r);
-                const float cs = msk * __builtin_amdgcn_cosf(-r);
-                float2 z[NC];
-                for (int c = 0; c < NC; c++) {
-                    z[c].x = wl[c].x * cs - wl[c].y * sn;
-                    z[c].y = wl[c].x * sn + wl[c].y * cs;
-                }
-#pragma unroll
-                for (int p = 0; p < NF; p++) {
-                    unsigned char *row = buf + (as * NF + p) * RS;
-                    if constexpr (PREC == PB3) {
-                        if constexpr (NX == 2) {
-                            uint32_t h0, l0, h1, l1;
-                            split2(z[2 * p].x, z[2 * p].y, h0, l0);
-                            split2(z[2 * p + 1].x, z[2 * p + 1].y, h1, l1);
-                            *(uint2 *)(row + msl * 8) = make_uint2(h0, h1);
-                            *(uint2 *)(row + L::PLANEB + msl * 8) = make_uint2(l0, l1);
-                        } else {
-                            uint32_t h0, l0;
-                            split2(z[p].x, z[p].y, h0, l0);
-                            *(uint32_t *)(row + msl * 4) = h0;
-                            *(uint32_t *)(row + L::PLANEB + msl * 4) = l0;
-                        }
-                    } else {
-                        if constexpr (NX == 2)
-                            *(float4 *)(row + msl * 16) = make_float4(z[2 * p].x, z[2 * p].y, z[2 * p + 1].x, z[2 * p + 1].y);
-                        else
-                            *(float2 *)(row + msl * 8) = z[p];
-                    }
-                }
-            }
-        };
-
-        f32x4 acc_re[16], acc_im[16];
-        for (int t = 0; t < 16; t++)
-            for (int e = 0; e < 4; e++) {
-                acc_re[t][e] = 0.f;
-                acc_im[t][e] = 0.f;
-            }
-        const int arow = wr * kWT;
-        const int brow = kST + wc * kWT;
-
-        auto consume = [&](const unsigned char *buf) {
-            if constexpr (!DIAG) {
-                consume_full<PREC>(buf, arow, brow, l16, lk, acc_re, acc_im);
-            } else {
-                switch (wave) {
-                    case 0: consume_tri<PREC, 0>(buf, l16, lk, acc_re, acc_im); break;
-                    case 1: consume_tri<PREC, 1>(buf, l16, lk, acc_re, acc_im); break;
-                    case 2: consume_tri<PREC, 2>(buf, l16, lk, acc_re, acc_im); break;
-                    default: consume_tri<PREC, 3>(buf, l16, lk, acc_re, acc_im); break;
-                }
-            }
-        };
-
-        fetch(0);
-        __syncthreads();  // antenna table ready
-        produce(lds);
-        fetch(1);
-        __syncthreads();
-        for (int stg = 0; stg < n_stage; stg++) {
-            unsigned char *cur = lds + (stg & 1) * L::BUF;
-            unsigned char *nxt = lds + ((stg + 1) & 1) * L::BUF;
-            if (consumer) consume(cur);
-            if (stg + 1 < n_stage) {
-                produce(nxt);
-                fetch(stg + 2);
-            }
-            __syncthreads();
-        }
-
-        if (consumer) {
-            float2 *P = (float2 *)a.part + ((int64_t)inst * a.max_splits + s) * (int64_t)Np * Np;
-            if constexpr (!DIAG) {
-                const int rb = I * kST + wr * kWT + 4 * lk;
-                const int c0 = J * kST + wc * kWT + l16;
-#pragma unroll
-                for (int i = 0; i < kTI; i++)
-#pragma unroll
-                    for (int j = 0; j < kTI; j++)
-#pragma unroll
-                        for (int e = 0; e < 4; e++)
-                            P[(int64_t)(rb + 16 * i + e) * Np + c0 + 16 * j] =
-                                make_float2(acc_re[i * kTI + j][e], acc_im[i * kTI + j][e]);
-            } else {
-                // slot t of wave w: tile (7 - w, t) for t < 8 - w, else tile (w, t - (8 - w))
-                const int ncol = 8 - wave;
-#pragma unroll
-                for (int t = 0; t < 9; t++) {
-                    const int R = t < ncol ? 7 - wave : wave;
-                    const int C = t < ncol ? t : t - ncol;
-                    const int r0 = I * kST + 16 * R + 4 * lk;
-                    const int c0 = I * kST + 16 * C + l16;
-#pragma unroll
-                    for (int e = 0; e < 4; e++)
-                        P[(int64_t)(r0 + e) * Np + c0] = make_float2(acc_re[t][e], acc_im[t][e]);
-                }
-            }
-        }
-    }
-}
 
 // ---------------------------------------------------------------------------
 // Two-block items (BF16X3, 129..256 rows): one workgroup owns every row of an
@@ -486,10 +48,10 @@ __global__ void __launch_bounds__(512, 1) k_herk_fused(FusedArgs a) {
 // Operand reads are 16 bytes per lane from 16 rows at once; measured on the
 // LDS, 160-byte rows serve them without bank conflicts and 144-byte rows with
 // half of their cycles in conflicts, so 160 bytes where the stage buffers fit.
-typedef RowGeom<FL<PB3>::RS, FL<PB3>::PLANEB, kKC / 16> GeomPair;  // 32 complex per stage
+typedef RowGeom<FL::RS, FL::PLANEB, kKC / 16> GeomPair;  // 32 complex per stage
 typedef RowGeom<16 * 4 * 2 + 16, 16 * 4, 1> GeomCoh;               // 16 complex per stage
 typedef RowGeom<16 * 4 * 2 + 32, 16 * 4, 1> GeomCoh3;              // the same in 160-byte rows
-typedef RowGeom<FL<PB3>::RS + 16, FL<PB3>::PLANEB, kKC / 16> GeomPair3;  // 32 complex, 288-byte rows
+typedef RowGeom<FL::RS + 16, FL::PLANEB, kKC / 16> GeomPair3;  // 32 complex, 288-byte rows
 
 // Off-diagonal block: rows 16 (rb + i), columns 16 (cb + j), i < NR, j < NC
 // (4 x 4 tiles, or 3 x 3 on a short diagonal block); tile (i, j) accumulates
@@ -597,7 +159,7 @@ struct SrcEntry {
 
 template <int NF, int NX>
 __global__ void __launch_bounds__(512, 1) k_herk_b3_pair(FusedArgs a) {
-    typedef FL<PB3> L;
+    typedef FL L;
     constexpr int RS = L::RS;
     constexpr int NC = NF * NX;       // beam components per source
     constexpr int SPS = kKC / NX;     // sources per stage
@@ -688,7 +250,7 @@ __global__ void __launch_bounds__(512, 1) k_herk_b3_pair(FusedArgs a) {
             for (int c = 0; c < NC; c++) e.w[c] = fw[c];
             e.m = fm;
         };
-        // Z rows of every antenna for one stage (as in k_herk_fused's producers)
+        // Z rows of every antenna for one stage
         auto produce = [&](unsigned char *buf, int stage) {
             const SrcEntry<NC> &se = src[stage & 1][msl];
             const int64_t m = se.m;
@@ -1758,28 +1320,6 @@ __global__ void __launch_bounds__(512, 1) k_herk_blk3(FusedArgs a) {
     }
 }
 
-template <int PREC, bool DIAG>
-hipError_t launch_kind(const FusedArgs &a, hipStream_t s) {
-    if (a.n_feed == 2 && a.n_ax == 2)
-        k_herk_fused<PREC, 2, 2, DIAG><<<a.grid, 512, 0, s>>>(a);
-    else if (a.n_feed == 2)
-        k_herk_fused<PREC, 2, 1, DIAG><<<a.grid, 512, 0, s>>>(a);
-    else if (a.n_ax == 2)
-        k_herk_fused<PREC, 1, 2, DIAG><<<a.grid, 512, 0, s>>>(a);
-    else
-        k_herk_fused<PREC, 1, 1, DIAG><<<a.grid, 512, 0, s>>>(a);
-    return hipGetLastError();
-}
-
-template <int PREC>
-hipError_t launch_prec(const FusedArgs &a, hipStream_t s, int which) {
-    hipError_t e = hipSuccess;
-    if (which != FUSED_PAIRS) e = launch_kind<PREC, true>(a, s);
-    if (e != hipSuccess || a.n_rows_pad <= kST || which == FUSED_FIRST)
-        return e;  // a single row block has no off-diagonal tiles
-    return launch_kind<PREC, false>(a, s);
-}
-
 }  // namespace
 
 hipError_t launch_pair(const FusedArgs &a, hipStream_t s) {
@@ -1806,7 +1346,6 @@ int fused_path(int prec, int n_feed, int n_ax, int n_beam, int n_ant, int n_rows
 bool fused_has_pairs(int prec, const FusedArgs &a) {
     const int path = fused_path(prec, a.n_feed, a.n_ax, a.n_beam, a.n_ant, a.n_rows_pad);
     if (path == MATVIS_PATH_SOURCES) return a.n_rows_pad > 2 * kST;
-    if (path == MATVIS_PATH_FUSED) return a.n_rows_pad > kST;
     return false;
 }
 
@@ -1867,20 +1406,7 @@ hipError_t launch_herk_fused(int prec, const FusedArgs &a, hipStream_t s, int wh
         }
         return hipGetLastError();
     }
-    if (prec == P32) return launch_prec<P32>(a, s, which);
-    if (prec == PB3) return launch_prec<PB3>(a, s, which);
-    return hipErrorInvalidValue;
-}
-
-int herk_fused_occupancy(int prec) {
-    int nb = 1;
-    hipError_t e = prec == P32 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_herk_fused<P32, 2, 2, false>, 512, 0)
-                               : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_herk_fused<PB3, 2, 2, false>, 512, 0);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return 1;
-    }
-    return nb < 1 ? 1 : nb;
+    return hipErrorInvalidValue;  // path FUSED: launch_tiles
 }
 
 }  // namespace mv

@@ -1,28 +1,42 @@
-// Redundancy-aware product (App. A, Eq. Vpx) with Z formed in LDS, FP32 and BF16X3.
+// Products over lists of 16 x 16 output tiles with Z formed in LDS, FP32 and BF16X3:
+// the redundancy-aware product (App. A, Eq. Vpx) and the full product of small arrays
+// and of several beams (MATVIS_PATH_FUSED).
 //
-// Of V only the requested pairs are needed.  The host lists the rows of Z (antenna,
-// feed) that some pair uses, in order, cuts them into blocks of 16, and lists the
-// 16 x 16 tiles (I, J) in which a pair lies: 81 tiles for the 1344 unique baselines
-// of a 350-antenna hexagon, a sixth of V and a third less than the planned
-// sub-matrices hold.  Tiles are grouped into bundles of at most kPairTiles tiles on
-// at most kPairBlocks blocks; a workgroup takes one (instance, k-split, bundle),
-// forms every row of the bundle once per stage of 16 columns and multiplies the
-// bundle's tiles from it, up to 6 a wave.  So Z is neither written nor gathered: in
-// HBM it was 2.2 GB for 32 instances of 24 576 sources that are up (written at 2.0 TB/s,
-// then read once per 32 x 32 tile).
+// The host lists rows of Z (antenna, feed) in blocks of 16 and the tiles (I, J) to
+// compute: those that hold a requested pair (81 tiles for the 1344 unique baselines of a
+// 350-antenna hexagon, a sixth of V and a third less than the planned sub-matrices
+// hold), or the lower triangle of V.  Tiles are grouped into bundles; a workgroup takes
+// one (instance, k-split, bundle), forms every row of the bundle once per stage of 16
+// columns and multiplies the bundle's tiles from it, up to 6 a wave.  So Z is neither
+// written nor gathered, and nothing is done for padding beyond 16 rows: as blocks of 128
+// rows, 12, 37 and 61 polarised antennas all took the time of 64.
+//
+// A polarised array of up to 64 antennas with one beam (COHERENT) stages, as the product
+// over sources of larger ones does, the planes P0 = s0 F, P1 = s1 F and L = l F, with
+// s_p = sqrt(C_pp) and l = C10 / s0 of the source's 2 x 2 coherency C = B B^H:
+// V^00 = P0 P0^H, V^11 = P1 P1^H (lower triangles), V^10 = L P0^H: half the columns of Z.
 //
 // FP32 operands are three exact bf16 terms and six products, as in
 // kernels_herk_x6.hip; BF16X3 operands hi + lo and all four products, because any
 // tile may hold an autocorrelation, where lo lo^H is a one-signed bias.  The products
 // of a stage start from zero and are added in FP32.
 //
+// A workgroup has 16 waves and a CU's LDS, or 8 and a half of it, or 4 and a quarter,
+// whichever is the least that holds its bundle: a CU always has 16 waves, and small
+// bundles have other workgroups to fill the waits at their barriers.
+//
 // Bound by vector instructions (63 % of the cycles: forming, rotation of columns, the
 // additions), LDS (54 %) and MFMAs (45 %) together; half of the waves multiply before
-// they form the next stage and half after.  350 antennas, 49 152 sources, 4 times of 8
-// channels, FP32: forming Z and multiplying went from 1.08 + 2.29 to 0.80 ms, the error
-// against 64 bits from 1.3e-6 to 2.2e-7.  16 waves of 6 tiles rather than 8 of 12 (with
-// operands loaded a tile ahead) took 0.82 against 0.92 ms, rows and columns laid out for
-// the banks 0.80.
+// they form the next stage and half after.  Requested pairs of 350 antennas, 49 152
+// sources, 4 times of 8 channels, FP32: forming Z and multiplying went from 1.08 + 2.29
+// to 0.80 ms, the error against 64 bits from 1.3e-6 to 2.2e-7.  16 waves of 6 tiles
+// rather than 8 of 12 (with operands loaded a tile ahead) took 0.82 against 0.92 ms, rows
+// and columns laid out for the banks 0.80.
+// Whole calls of 100 000 sources, 4 times of 8 channels against blocks of 128 rows: FP32, 12
+// / 37 / 61 polarised antennas 2.19 / 2.22 / 2.23 -> 0.31 / 0.60 / 0.98 ms, 30 / 100 / 200
+// scalar ones 1.37 / 1.38 / 4.62 -> 0.23 / 0.60 / 1.41 ms; BF16X3, 12 / 37 / 61 polarised 0.83 /
+// 0.85 / 0.86 -> 0.30 / 0.56 / 0.79 ms, 30 / 100 scalar 0.61 / 0.61 -> 0.22 / 0.50 ms; errors a
+// quarter of what they were.
 #include <type_traits>
 
 #include "herk_tiles.h"
@@ -33,19 +47,18 @@ namespace mv {
 namespace {
 
 constexpr int kSPS = 16;                       // columns per stage
-constexpr int kRows = 16 * kPairBlocks;        // staged rows
-constexpr int kWaves = 16;
-constexpr int kWaveTiles = kPairTiles / kWaves;  // tiles of a wave
 constexpr int kPlane = 4 * kSPS;               // bytes of a row's plane
 
-template <int PREC>
-struct PairGeom {
+template <int PREC, int WAVES>
+struct TileGeom {
     static constexpr int NT = PREC == P32 ? 3 : 2;     // bf16 terms per value
     static constexpr int RS = NT * kPlane + 16;        // 16 bytes of padding spread the banks
-    static constexpr int BUF = kRows * RS;
+    static constexpr int ROWS = 16 * tile_blocks(WAVES);
+    static constexpr int BUF = ROWS * RS;
 };
 
-// Two staged columns: the sources' directions and their values of both feeds.  80 bytes,
+// Two staged columns: the sources' directions and their values of both feeds (COHERENT:
+// s0, s1 and l).  80 bytes,
 // so that the eight pairs of a stage start in different banks.
 struct __attribute__((aligned(16))) Columns {
     double x0, y0, z0, x1, y1, z1;
@@ -54,7 +67,7 @@ struct __attribute__((aligned(16))) Columns {
 
 struct Row {
     double ux, uy, uz;  // (nu / c) x_a
-    int32_t bp;         // beam n_feed + feed
+    int32_t bp;         // beam n_feed + feed; COHERENT: the plane
     int32_t pad;
 };
 
@@ -89,14 +102,14 @@ __device__ __forceinline__ void products(const Ops<NT> &a, const Ops<NT> &b, con
         }
 }
 
-template <int PREC>
-__global__ void __launch_bounds__(1024, 1) k_pair_tiles(PairArgs a) {
-    typedef PairGeom<PREC> G;
+template <int PREC, int WAVES, bool COHERENT>
+__global__ void __launch_bounds__(64 * WAVES, 4) k_tiles(TileArgs a) {
+    typedef TileGeom<PREC, WAVES> G;
     constexpr int NT = G::NT, RS = G::RS;
     __shared__ __attribute__((aligned(16))) unsigned char lds[2 * G::BUF];
-    __shared__ Row row[kRows];
+    __shared__ Row row[G::ROWS];
     __shared__ Columns col[2][kSPS / 2];
-    static_assert(2 * G::BUF + sizeof(Row) * kRows + sizeof(Columns) * kSPS <= 160 * 1024, "LDS");
+    static_assert((2 * G::BUF + sizeof(Row) * G::ROWS + sizeof(Columns) * kSPS) * (16 / WAVES) <= 160 * 1024, "LDS");
     const int tid = threadIdx.x, lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int l16 = lane & 15, lk = lane >> 4;
@@ -105,21 +118,23 @@ __global__ void __launch_bounds__(1024, 1) k_pair_tiles(PairArgs a) {
     const int bundle = (int)((item / a.n_split) % a.n_bundle);
     const int inst = (int)(item / ((int64_t)a.n_split * a.n_bundle));
     const int tslot = inst / a.nfb;
-    const int nx = a.n_ax, nf = a.n_feed;
+    const int nx = COHERENT ? 1 : a.n_ax, nf = a.n_feed;
     const int64_t K = (int64_t)nx * a.count[tslot];
     const int64_t kc = split_cols(K, a.n_split);
     const int64_t kb = (int64_t)s * kc, ke = kb + kc < K ? kb + kc : K;
     if (kb >= K) return;  // an empty k-split: the reduction leaves it out too
-    const PairBundle bd = a.bundles[bundle];
+    const TileBundle bd = a.bundles[bundle];
     const int n_rows = bd.n_rows;
+    const int nr = COHERENT ? 3 : nf;  // rows of an antenna
     const double nu_c = a.freqs[a.f0 + inst % a.nfb] / kSpeedOfLight;
     const double *sh = a.s_hat + (int64_t)tslot * 3 * a.ld_src;
-    const float2 *Bi = (const float2 *)a.B + (int64_t)inst * a.n_beam * nf * nx * a.ld_src;  // [beam][feed][axis][m]
+    const float2 *Bi = (const float2 *)a.B + (int64_t)inst * a.n_beam * nf * a.n_ax * a.ld_src;  // [beam][feed][axis][m]
     const bool shared_beam = a.n_beam == 1;
-    if (tid < n_rows) {
-        const int z = a.rows[bd.row0 + tid], ant = z < 0 ? 0 : z / nf;  // padding rows reach no stored output
-        row[tid] = Row{nu_c * a.antc[3 * ant], nu_c * a.antc[3 * ant + 1], nu_c * a.antc[3 * ant + 2],
-                       a.bidx[ant] * nf + (z < 0 ? 0 : z % nf), 0};
+    for (int q = tid; q < n_rows; q += 64 * WAVES) {
+        const int z = a.rows[bd.row0 + q], ant = z < 0 ? 0 : z / nr;  // padding rows reach no stored output
+        const int p = z < 0 ? 0 : z % nr;
+        row[q] = Row{nu_c * a.antc[3 * ant], nu_c * a.antc[3 * ant + 1], nu_c * a.antc[3 * ant + 2],
+                       COHERENT ? p : a.bidx[ant] * nf + p, 0};
     }
     const int n_stage = (int)((ke - kb + kSPS - 1) / kSPS);
 
@@ -136,7 +151,16 @@ __global__ void __launch_bounds__(1024, 1) k_pair_tiles(PairArgs a) {
             fx = sh[m];
             fy = sh[a.ld_src + m];
             fz = sh[2 * a.ld_src + m];
-            if (shared_beam) {
+            if (COHERENT) {
+                // B components c = 2 p + k; C10 = B10 conj(B00) + B11 conj(B01)
+                const float2 b0 = Bi[m], b1 = Bi[a.ld_src + m], b2 = Bi[2 * a.ld_src + m], b3 = Bi[3 * a.ld_src + m];
+                const float c00 = b0.x * b0.x + b0.y * b0.y + b1.x * b1.x + b1.y * b1.y;
+                const float c11 = b2.x * b2.x + b2.y * b2.y + b3.x * b3.x + b3.y * b3.y;
+                const float c10x = b2.x * b0.x + b2.y * b0.y + b3.x * b1.x + b3.y * b1.y;
+                const float c10y = b2.y * b0.x - b2.x * b0.y + b3.y * b1.x - b3.x * b1.y;
+                const float s0 = sqrtf(c00);
+                fb = make_float4(s0, sqrtf(c11), s0 > 0.f ? c10x / s0 : 0.f, s0 > 0.f ? c10y / s0 : 0.f);
+            } else if (shared_beam) {
                 const float2 v = Bi[(c % nx) * a.ld_src + m];
                 const float2 u = nf == 2 ? Bi[(nx + c % nx) * a.ld_src + m] : v;
                 fb = make_float4(v.x, v.y, u.x, u.y);
@@ -151,17 +175,23 @@ __global__ void __launch_bounds__(1024, 1) k_pair_tiles(PairArgs a) {
         d[2] = fz;
         *(tid & 1 ? &e.b1 : &e.b0) = fb;
     };
-    // two columns (2 mp, 2 mp + 1) of rows r0 + 128 k; the rows that 32 lanes write are 4
+    // two columns (2 mp, 2 mp + 1) of rows r0 + 8 WAVES k; the rows that 32 lanes write are 4
     // (832 bytes, a quarter of the banks) apart
     const int mp = tid % 8, g = tid / 8 % 8;
     const int r0 = wave / 2 * 16 + wave % 2 * 2 + g % 4 * 4 + g / 4;
     auto produce = [&](unsigned char *buf, int stage) __attribute__((always_inline)) {
         const Columns c = col[stage & 1][mp];
         const int64_t cg = kb + (int64_t)stage * kSPS + 2 * mp;
-        for (int r = r0; r < n_rows; r += 8 * kWaves) {
+        for (int r = r0; r < n_rows; r += 8 * WAVES) {
             const Row e = row[r];
             float vr[2], vi[2];
-            if (shared_beam) {
+            if (COHERENT) {
+                const bool real = e.bp < 2, second = e.bp == 1;
+                vr[0] = real ? (second ? c.b0.y : c.b0.x) : c.b0.z;
+                vi[0] = real ? 0.f : c.b0.w;
+                vr[1] = real ? (second ? c.b1.y : c.b1.x) : c.b1.z;
+                vi[1] = real ? 0.f : c.b1.w;
+            } else if (shared_beam) {
                 const bool second = e.bp != 0;
                 vr[0] = second ? c.b0.z : c.b0.x;
                 vi[0] = second ? c.b0.w : c.b0.y;
@@ -201,7 +231,7 @@ __global__ void __launch_bounds__(1024, 1) k_pair_tiles(PairArgs a) {
         stash(1);
     }
     // this wave's tiles, sorted by column block: LDS offsets of their row and column blocks
-    const int t0 = bd.n_tiles * wave / kWaves, nt = bd.n_tiles * (wave + 1) / kWaves - t0;
+    const int t0 = bd.n_tiles * wave / WAVES, nt = bd.n_tiles * (wave + 1) / WAVES - t0;
     // (`fresh`: bit t set where the column block is not that of tile t - 1)
     uint32_t ro[kWaveTiles], co[kWaveTiles], fresh = 0;
 #pragma unroll
@@ -266,18 +296,35 @@ __global__ void __launch_bounds__(1024, 1) k_pair_tiles(PairArgs a) {
             __syncthreads();
         }
         // the write-out's addresses are formed here rather than kept live across the stages
-        int r4 = 4 * lk, c = l16;
-        asm volatile("" : "+v"(r4), "+v"(c));
-        float2 *P = (float2 *)a.part +
-                    (((int64_t)inst * a.n_split + s) * a.n_tiles + bd.tile0 + t0) * (int64_t)(kPairTile * kPairTile);
+        int r4 = 4 * lk, c = l16, ld = a.ld;
+        asm volatile("" : "+v"(r4), "+v"(c), "+v"(ld));
+        float2 *P = (float2 *)a.part + ((int64_t)inst * a.n_split + s) * a.part_stride;
+        const int32_t *dst = a.dst + bd.tile0 + t0;
 #pragma unroll
         for (int t = 0; t < kWaveTiles; t++)
-            if (t < nt)
+            if (t < nt) {
+                const int d = dst[t];
 #pragma unroll
-                for (int e = 0; e < 4; e++)
-                    P[t * kPairTile * kPairTile + (r4 + e) * kPairTile + c] = make_float2(re[t][e], im[t][e]);
+                for (int e = 0; e < 4; e++) {
+                    float2 v = make_float2(re[t][e], im[t][e]);
+                    if constexpr (COHERENT) {
+                        // rows and columns 2 a + p; V^10 above the antenna diagonal is V^01 below it
+                        const int A = 16 * (d & 255) + r4 + e, B = 16 * (d >> 8 & 255) + c;
+                        int r = 2 * A + (d >> 16 & 1), q = 2 * B + (d >> 17);
+                        if (A < B && d >> 16 == 1) {
+                            const int x = r;
+                            r = q;
+                            q = x;
+                            v.y = -v.y;
+                        }
+                        P[(int64_t)r * ld + q] = v;
+                    } else {
+                        P[(int64_t)d + (r4 + e) * ld + c] = v;
+                    }
+                }
+            }
     };
-    if (wave < kWaves / 2)
+    if (wave < WAVES / 2)
         stages(std::true_type{});
     else
         stages(std::false_type{});
@@ -285,17 +332,35 @@ __global__ void __launch_bounds__(1024, 1) k_pair_tiles(PairArgs a) {
 
 }  // namespace
 
-hipError_t launch_pair_tiles(int prec, const PairArgs &a, hipStream_t s) {
+int tile_waves(int n_rows, int n_tiles) {
+    for (int w : {4, 8})
+        if (n_rows <= 16 * tile_blocks(w) && n_tiles <= kWaveTiles * w) return w;
+    return 16;
+}
+
+hipError_t launch_tiles(int prec, const TileArgs &a, hipStream_t s) {
     const int64_t items = (int64_t)a.n_inst * a.n_bundle * a.n_split;
     if (items <= 0) return hipSuccess;
     if (items > 0x7fffffff || a.n_feed > 2 || a.n_ax > 2) return hipErrorInvalidValue;
-    if (prec == P32)
-        k_pair_tiles<P32><<<(unsigned)items, 64 * kWaves, 0, s>>>(a);
-    else if (prec == PB3)
-        k_pair_tiles<PB3><<<(unsigned)items, 64 * kWaves, 0, s>>>(a);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
+    if (a.coherent && (a.n_feed != 2 || a.n_ax != 2 || a.n_beam != 1)) return hipErrorInvalidValue;
+    auto launch = [&](auto waves) {
+        constexpr int W = decltype(waves)::value;
+        const unsigned g = (unsigned)items;
+        if (prec == P32 && a.coherent)
+            k_tiles<P32, W, true><<<g, 64 * W, 0, s>>>(a);
+        else if (prec == P32)
+            k_tiles<P32, W, false><<<g, 64 * W, 0, s>>>(a);
+        else if (a.coherent)
+            k_tiles<PB3, W, true><<<g, 64 * W, 0, s>>>(a);
+        else
+            k_tiles<PB3, W, false><<<g, 64 * W, 0, s>>>(a);
+        return hipGetLastError();
+    };
+    if (prec != P32 && prec != PB3) return hipErrorInvalidValue;
+    if (a.waves == 4) return launch(std::integral_constant<int, 4>{});
+    if (a.waves == 8) return launch(std::integral_constant<int, 8>{});
+    if (a.waves == 16) return launch(std::integral_constant<int, 16>{});
+    return hipErrorInvalidValue;
 }
 
 }  // namespace mv

@@ -37,6 +37,14 @@ struct GraphKey {
 
 }  // namespace
 
+// A tile list on the device (kernels_tiles.hip) and what its launch needs to know.
+struct DevTiles {
+    int32_t n_bundle = 0;  // 0: none
+    int32_t waves = 16, coherent = 0;
+    int32_t *rows = nullptr, *tiles = nullptr, *dst = nullptr;
+    TileBundle *bundles = nullptr;
+};
+
 struct matvis_ctx {
     matvis_config cfg{};
     int device = 0;
@@ -49,6 +57,8 @@ struct matvis_ctx {
     int N = 0, Np = 0, st = 128;
     int64_t chunk = 0, ldz = 0, ksplit = 4096;
     int max_splits = 1, ntb = 1, nfb = 1, herk_grid = 512, fused_grid = 256;
+    int64_t step_ksplit = 4096;  // of matvis_step_herk, whose FP32 accumulators take every MFMA update
+    int step_splits = 1;
     int pair_splits = 1;  // k-splits of ksplit columns (the sub-matrix product, which is not balanced)
     int n_bal = 1;        // items per k-split of the product launch that the splits are balanced for
     int64_t nblk_cap = 1;
@@ -89,14 +99,13 @@ struct matvis_ctx {
     bool pr_set = false;
     int32_t pr_n = 0, pr_tiles = 0;
     int64_t pr_size = 0;
-    int32_t *pr_rows = nullptr;  // [tiles][2][ST] Z rows; rows of the bundles where Z is formed in LDS
+    int32_t *pr_rows = nullptr;  // [tiles][2][ST] Z rows (Z in device memory)
     int32_t *pr_loc = nullptr;   // [n_pair][nf][nf][2]
     void *pr_part = nullptr;     // [B_cap][pr_splits][tiles][ST][ST]
     void *pr_Z = nullptr;        // fused FP64 contexts: Z of a batch for the pairs
     int pr_splits = 1;
-    int32_t pr_nbundle = 0;      // Z formed in LDS: the bundles and their tiles
-    PairBundle *pr_bundles = nullptr;
-    int32_t *pr_tile_list = nullptr;
+    DevTiles pr_list;            // Z formed in LDS: the pairs' tiles
+    DevTiles full;               // the tiles of V, where the product takes them (path FUSED)
     double *pr_vacc = nullptr;   // [B_cap][n_pair][nf][nf] complex128
 };
 
@@ -170,13 +179,14 @@ size_t cbytes(int prec) { return prec == P64 ? 16 : 8; }  // bytes per complex o
 
 // The library's k-split (Z columns per product work item) for a precision and
 // product path when the configuration leaves it at 0.
-int64_t mv::default_ksplit(int prec, bool over_sources, bool three_blocks) {
-    return prec == P64                   ? 8192
-           : prec == P32 && over_sources ? 8192
-           : prec == P32                 ? 2048
-           : over_sources                ? 20480
-           : three_blocks                ? 8192
-                                         : 4096;
+int64_t mv::default_ksplit(int prec, int path) {
+    if (prec == P64) return 8192;
+    switch (path) {
+        case MATVIS_PATH_SOURCES: return prec == P32 ? 8192 : 20480;
+        case MATVIS_PATH_FUSED:
+        case MATVIS_PATH_FUSED_BLOCKS: return 8192;
+        default: return prec == P32 ? 2048 : 4096;
+    }
 }
 
 namespace {
@@ -215,6 +225,225 @@ matvis_status validate_cfg(const matvis_config *c, std::string &why) {
                      "(stage depth) 0 or 1, no other bits", MATVIS_EINVAL;
     if (c->ksplit < 0 || c->ksplit % 64 != 0 || c->ksplit > ((int64_t)1 << 30))
         return why = "ksplit must be 0 or a positive multiple of 64", MATVIS_EINVAL;
+    return MATVIS_OK;
+}
+
+// The tiles of a product: rows of Z, where each pair lies (tile, element; pair plans
+// only), and, where Z is formed in LDS, the tiles' blocks and their bundles.
+struct Tiles {
+    std::vector<int32_t> rows, loc, tiles, dst;
+    std::vector<TileBundle> bundles;
+    int n_tiles = 0;
+};
+
+// 32 x 32 tiles over every sub-matrix's Z rows (antenna a, feed p -> row a nf + p)
+Tiles pair_submatrices(const red::Plan &P, const int32_t *pair_a, const int32_t *pair_b, int n_pair, int n_ant,
+                           int nf) {
+    const int ST = kSubmatTile;
+    Tiles T;
+    std::vector<int32_t> &rows = T.rows, &loc = T.loc, base;
+    std::vector<int> ntc;
+    for (size_t x = 0; x < P.A.size(); x++) {
+        const int ra = (int)P.A[x].size() * nf, rb = (int)P.B[x].size() * nf;
+        const int nta = (ra + ST - 1) / ST, ntb = (rb + ST - 1) / ST;
+        base.push_back((int32_t)(rows.size() / (2 * ST)));
+        ntc.push_back(ntb);
+        for (int ti = 0; ti < nta; ti++)
+            for (int tj = 0; tj < ntb; tj++) {
+                for (int r = 0; r < ST; r++) {
+                    const int q = ti * ST + r;
+                    rows.push_back(q < ra ? P.A[x][q / nf] * nf + q % nf : -1);
+                }
+                for (int r = 0; r < ST; r++) {
+                    const int q = tj * ST + r;
+                    rows.push_back(q < rb ? P.B[x][q / nf] * nf + q % nf : -1);
+                }
+            }
+    }
+    T.n_tiles = (int)(rows.size() / (2 * ST));
+    std::vector<int> sub_of(n_ant, -1), pos_in(n_ant, -1);
+    for (size_t x = 0; x < P.A.size(); x++)
+        for (size_t i = 0; i < P.A[x].size(); i++) {
+            sub_of[P.A[x][i]] = (int)x;
+            pos_in[P.A[x][i]] = (int)i;
+        }
+    loc.resize((size_t)n_pair * nf * nf * 2);
+    for (int u = 0; u < n_pair; u++) {
+        const int x = sub_of[pair_a[u]];
+        const auto &B = P.B[x];
+        const int ib = (int)(std::lower_bound(B.begin(), B.end(), pair_b[u]) - B.begin());
+        for (int p = 0; p < nf; p++)
+            for (int q = 0; q < nf; q++) {
+                const int r = pos_in[pair_a[u]] * nf + p, col = ib * nf + q;
+                const size_t e = (((size_t)u * nf + p) * nf + q) * 2;
+                loc[e] = base[x] + (r / ST) * ntc[x] + col / ST;
+                loc[e + 1] = (r % ST) * ST + col % ST;
+            }
+    }
+    return T;
+}
+
+// Bundles of the tiles (row block, column block) in the order given, of about equal
+// numbers of tiles, closed early when the next tile would exceed the staged blocks;
+// row(b, i) is the Z row of row i of block b, or -1.
+template <typename Row>
+void bundle_tiles(Tiles &T, const std::vector<std::pair<int32_t, int32_t>> &list, Row row) {
+    const int n = (int)list.size(), cap = 16 * kWaveTiles;
+    const int target = n > 0 ? (n + (n + cap - 1) / cap - 1) / ((n + cap - 1) / cap) : 0;
+    std::vector<int32_t> blocks;  // of the open bundle
+    auto slot = [&](int32_t b) { return (int32_t)(std::find(blocks.begin(), blocks.end(), b) - blocks.begin()); };
+    TileBundle bd{0, 0, 0, 0};
+    auto close = [&]() {
+        bd.n_rows = (int32_t)blocks.size() * kTile;
+        bd.n_tiles = T.n_tiles - bd.tile0;
+        T.bundles.push_back(bd);
+        for (int32_t b : blocks)
+            for (int i = 0; i < kTile; i++) T.rows.push_back(row(b, i));
+        bd = TileBundle{(int32_t)T.rows.size(), 0, T.n_tiles, 0};
+        blocks.clear();
+    };
+    for (const auto &t : list) {
+        const int32_t I = t.first, J = t.second;
+        const int fresh = (slot(I) == (int)blocks.size()) + (J != I && slot(J) == (int)blocks.size());
+        if ((int)blocks.size() + fresh > tile_blocks(16) || T.n_tiles - bd.tile0 == target) close();
+        for (int32_t b : {J, I})
+            if (slot(b) == (int)blocks.size()) blocks.push_back(b);
+        T.tiles.push_back(slot(I) | slot(J) << 8);
+        T.n_tiles++;
+    }
+    if (n > 0) close();
+}
+
+// The rows that some pair uses, in order, in blocks of 16, and the tiles that hold a pair,
+// by column block.
+Tiles pair_tiles(const int32_t *pair_a, const int32_t *pair_b, int n_pair, int nf) {
+    Tiles T;
+    std::map<int32_t, int32_t> pos;  // antenna -> place among the used ones
+    for (int u = 0; u < n_pair; u++) pos[pair_a[u]] = pos[pair_b[u]] = 0;
+    std::vector<int32_t> used;
+    for (auto &kv : pos) {
+        kv.second = (int32_t)used.size();
+        used.push_back(kv.first);
+    }
+    const int n_rows = (int)used.size() * nf, B = kTile;
+    std::map<std::pair<int32_t, int32_t>, int32_t> tile;  // (column block, row block) -> index
+    auto each = [&](auto f) {
+        for (int u = 0; u < n_pair; u++)
+            for (int p = 0; p < nf; p++)
+                for (int q = 0; q < nf; q++)
+                    f(((size_t)u * nf + p) * nf + q, pos[pair_a[u]] * nf + p, pos[pair_b[u]] * nf + q);
+    };
+    each([&](size_t, int32_t r, int32_t c) { tile[{c / B, r / B}] = 0; });
+    std::vector<std::pair<int32_t, int32_t>> list;
+    for (auto &kv : tile) {
+        kv.second = (int32_t)list.size();
+        T.dst.push_back((int32_t)list.size() * B * B);
+        list.push_back({kv.first.second, kv.first.first});
+    }
+    bundle_tiles(T, list, [&](int32_t b, int i) {
+        const int r = b * B + i;
+        return r < n_rows ? used[r / nf] * nf + r % nf : -1;
+    });
+    T.loc.resize((size_t)n_pair * nf * nf * 2);
+    each([&](size_t e, int32_t r, int32_t c) {
+        T.loc[2 * e] = tile[{c / B, r / B}];
+        T.loc[2 * e + 1] = (r % B) * B + c % B;
+    });
+    return T;
+}
+
+// The lower triangle of V in partials of Np columns.  Up to 16 blocks the tiles go column
+// by column (one or two bundles); more blocks in rectangles of 12 x 8, which fill a
+// workgroup with 20 blocks.  coherent: planes 0, 1, 2 (P0, P1, L) of antenna block b are
+// blocks 3 b, 3 b + 1, 3 b + 2.
+Tiles full_tiles(int n_ant, int nf, int Np, bool coherent) {
+    Tiles T;
+    std::vector<std::pair<int32_t, int32_t>> list;
+    if (coherent) {
+        const int nb = (n_ant + kTile - 1) / kTile;
+        for (int J = 0; J < nb; J++)
+            for (int pq : {0, 3, 1})  // V^00, V^11 (I >= J), V^10: p = pq & 1, q = pq >> 1
+                for (int I = pq == 1 ? 0 : J; I < nb; I++) {
+                    list.push_back({3 * I + (pq == 0 ? 0 : pq == 3 ? 1 : 2), 3 * J + (pq == 3 ? 1 : 0)});
+                    T.dst.push_back(I | J << 8 | pq << 16);
+                }
+        bundle_tiles(T, list, [&](int32_t b, int i) {
+            const int ant = b / 3 * kTile + i;
+            return ant < n_ant ? 3 * ant + b % 3 : -1;
+        });
+        return T;
+    }
+    const int N = n_ant * nf, nb = (N + kTile - 1) / kTile;
+    const int rj = nb <= 16 ? nb : 8, ri = nb <= 16 ? nb : 12;
+    for (int J0 = 0; J0 < nb; J0 += rj)
+        for (int I0 = J0 / ri * ri; I0 < nb; I0 += ri)
+            for (int J = J0; J < std::min(J0 + rj, nb); J++)
+                for (int I = std::max(I0, J); I < std::min(I0 + ri, nb); I++) {
+                    list.push_back({I, J});
+                    T.dst.push_back((I * Np + J) * kTile);
+                }
+    bundle_tiles(T, list, [&](int32_t b, int i) { return b * kTile + i < N ? b * kTile + i : -1; });
+    return T;
+}
+
+// k-splits of a batch of n_inst instances: `base` (the configured columns per split at
+// least), more while they fill whole rounds of the workgroups that run at once, none of
+// fewer than 8 stages of the context's columns, at most `most`.
+int tile_splits(const matvis_ctx *c, const DevTiles &t, int n_inst, int64_t base, int64_t most) {
+    const int64_t slots = (int64_t)c->n_cu * (16 / t.waves), per_split = (int64_t)n_inst * t.n_bundle;
+    const int64_t rounds = (per_split * base + slots - 1) / slots;
+    // (the split sum is a chain of its own, so their number grows as the root of the columns)
+    const int64_t fill = std::min({rounds * slots / per_split, c->ldz / 128, (int64_t)std::sqrt((double)c->ldz)});
+    return (int)std::max<int64_t>(base, std::min(fill, most));
+}
+
+TileArgs tile_args(const matvis_ctx *c, const DevTiles &t, const Batch &bt, const double *freqs, int n_split) {
+    const matvis_config &g = c->cfg;
+    TileArgs a{};
+    a.rows = t.rows;
+    a.tiles = t.tiles;
+    a.dst = t.dst;
+    a.bundles = t.bundles;
+    a.n_bundle = t.n_bundle;
+    a.waves = t.waves;
+    a.coherent = t.coherent;
+    a.count = c->count;
+    a.n_ax = g.n_ax;
+    a.n_feed = g.n_feed;
+    a.n_beam = g.n_beam;
+    a.nfb = bt.nfb;
+    a.n_inst = bt.n_inst;
+    a.f0 = bt.f0;
+    a.n_split = n_split;
+    a.antc = c->antc;
+    a.bidx = c->bidx;
+    a.freqs = freqs;
+    a.s_hat = c->s_hat;
+    a.B = c->A;
+    a.ld_src = c->chunk;
+    return a;
+}
+
+void set_launch(const Tiles &T, DevTiles &d) {
+    int rows = 0, tiles = 0;
+    for (const TileBundle &b : T.bundles) rows = std::max(rows, b.n_rows), tiles = std::max(tiles, b.n_tiles);
+    d.waves = tile_waves(rows, tiles);
+    d.n_bundle = (int32_t)T.bundles.size();
+}
+
+// A tile list's device copy.
+matvis_status upload_tiles(matvis_ctx *c, const Tiles &T, DevTiles &d) {
+    auto put = [&](auto **p, const auto &v) -> matvis_status {
+        matvis_status st = dalloc(c, p, sizeof(v[0]) * v.size());
+        if (st != MATVIS_OK) return st;
+        HIPCHK(c, hipMemcpy(*p, v.data(), sizeof(v[0]) * v.size(), hipMemcpyHostToDevice));
+        return MATVIS_OK;
+    };
+    matvis_status st;
+    if ((st = put(&d.rows, T.rows)) != MATVIS_OK || (st = put(&d.tiles, T.tiles)) != MATVIS_OK ||
+        (st = put(&d.dst, T.dst)) != MATVIS_OK || (st = put(&d.bundles, T.bundles)) != MATVIS_OK)
+        return st;
+    set_launch(T, d);
     return MATVIS_OK;
 }
 
@@ -290,27 +519,44 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
     // scale, and the items' partials are then summed in FP64.
     // Default k-split per precision: measured on the 128-antenna polarised workload,
     // err_CS grows about as sqrt(ksplit) (FP32: 3.1e-6 at 2048, 1.4e-5 at 8192;
-    // BF16X3: 2.5e-6 at 4096, whose split error dominates below that).
+    // BF16X3: 2.5e-6 at 4096, whose split error dominates below that): Z in device memory.
     // The product over sources (two axes summed per source) accumulates ksplit / 2
     // sources per item: err_CS 3.5e-6 at 8192, 4.9e-6 at 16384, 7.0e-6 at 32768 on
     // the same workload; 20480 (~5.4e-6) keeps a factor 1.8 to 1e-5, and at the
     // benchmark's ~50 000 visible columns it gives three splits per instance
     // instead of four (fewer items and partials: 1.4 % of its step).
-    const bool over_sources =
-        c->fused && prec != P64 &&
-        fused_path(prec, cfg->n_feed, cfg->n_ax, cfg->n_beam, cfg->n_ant, c->Np) == MATVIS_PATH_SOURCES;
-    if (over_sources) c->Np = (int)round_up(c->N, 2 * c->st);  // whole blocks of 128 antennas x 2 feeds
-    // FP32 product over sources: 8192.  Its accumulators round once per 16 sources, so
-    // the error hardly depends on it (2.3e-7 at 8192 and at 20480); 20480 would take 0.2 ms
-    // off the 32.5 ms of 128 antennas, 200 000 sources, 256 instances.
     // scalar rows in three blocks (BF16X3): 8192 columns per split (err_CS 3.5e-6
     // against 2.8e-6 at 4096 on the 350-antenna diffuse sky, with half the partials:
-    // its reduction went from 0.82 to 0.46 ms per two instances)
-    const bool three_blocks =
-        c->fused && prec != P64 &&
-        fused_path(prec, cfg->n_feed, cfg->n_ax, cfg->n_beam, cfg->n_ant, c->Np) == MATVIS_PATH_FUSED_BLOCKS;
-    c->ksplit = cfg->ksplit > 0 ? cfg->ksplit : default_ksplit(prec, over_sources, three_blocks);
+    // its reduction went from 0.82 to 0.46 ms per two instances).
+    // Where the products of a stage are summed before they are added (FP32 on paths
+    // SOURCES, FUSED and FUSED_BLOCKS, BF16X3 on FUSED) the error hardly depends on it:
+    // 1.6e-7 at 2048 and 2.3e-7 at 8192 on 200 scalar antennas, 100 000 sources, FP32, and
+    // 8192 is 7 % faster there (10 % on 61 polarised ones); FP32 over sources would gain
+    // 0.2 ms of 32.5 from 20480.
+    const int path = c->fused && prec != P64
+                         ? fused_path(prec, cfg->n_feed, cfg->n_ax, cfg->n_beam, cfg->n_ant, c->Np)
+                         : MATVIS_PATH_Z_IN_HBM;
+    const bool over_sources = path == MATVIS_PATH_SOURCES, three_blocks = path == MATVIS_PATH_FUSED_BLOCKS;
+    if (over_sources) c->Np = (int)round_up(c->N, 2 * c->st);  // whole blocks of 128 antennas x 2 feeds
+    // the lower triangle's 16 x 16 tiles
+    const bool tiled = path == MATVIS_PATH_FUSED;
+    Tiles tiles;
+    if (tiled) {
+        c->full.coherent = cfg->n_feed == 2 && cfg->n_ax == 2 && cfg->n_beam == 1;
+        try {
+            tiles = full_tiles(cfg->n_ant, cfg->n_feed, c->Np, c->full.coherent != 0);
+        } catch (const std::bad_alloc &) {
+            matvis_destroy(c);
+            return MATVIS_ENOMEM;
+        }
+        set_launch(tiles, c->full);
+    }
+    c->ksplit = cfg->ksplit > 0 ? cfg->ksplit : default_ksplit(prec, path);
     c->max_splits = c->pair_splits = (int)((c->ldz + c->ksplit - 1) / c->ksplit);
+    c->step_ksplit = cfg->ksplit > 0 || over_sources
+                         ? c->ksplit
+                         : std::min(c->ksplit, default_ksplit(prec, MATVIS_PATH_Z_IN_HBM));
+    c->step_splits = (int)((c->ldz + c->step_ksplit - 1) / c->step_ksplit);
     // batch: all channels of a few times, enough instances to fill the GPU with
     // work items while keeping Z within a fixed share of device memory
     c->nfb = cfg->batch_freq > 0 ? std::min(cfg->batch_freq, cfg->max_freq) : std::min(cfg->max_freq, 16);
@@ -326,12 +572,14 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
     int64_t nblk_total = std::max<int64_t>(c->nblk_cap * c->ntb, (cfg->max_src + 255) / 256);
     int occ = std::max(1, herk_occupancy(prec));
     c->herk_grid = std::max(8, (c->n_cu * occ / 8) * 8);
-    if (c->fused)
-        c->fused_grid = std::max(8, (c->n_cu * (prec == P64 ? 1 : std::max(1, herk_fused_occupancy(prec))) / 8) * 8);
+    if (c->fused) c->fused_grid = std::max(8, (c->n_cu / 8) * 8);  // a workgroup per CU: their stages fill the LDS
     // Room for the k-splits that k_worklist adds when a batch alone does not fill the
     // grid: up to a grid's worth of items over the batch's instances, as long as the
     // partials stay within 1 GiB (or what the plain splits need).
-    {
+    if (tiled) {
+        const size_t one = (size_t)B * c->Np * c->Np * cbytes(prec);
+        c->max_splits = tile_splits(c, c->full, B, c->max_splits, (int64_t)(((size_t)1 << 30) / one));
+    } else {
         const int nb = c->Np / c->st;
         const int grid = c->fused ? c->fused_grid : c->herk_grid;
         c->n_bal = !c->fused ? nb * (nb + 1) / 2
@@ -367,6 +615,14 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
     ALLOC(c->cell_hist, sizeof(int32_t) * sort_hist_entries(cfg->max_src));
     ALLOC(c->perm, sizeof(int32_t) * cfg->max_src);
     ALLOC(c->rot, sizeof(double) * 9 * cfg->max_time);
+    if (tiled) {
+        st = upload_tiles(c, tiles, c->full);
+        if (st != MATVIS_OK) {
+            fprintf(stderr, "matvis_init: %s\n", c->err.c_str());
+            matvis_destroy(c);
+            return st;
+        }
+    }
     ALLOC(c->antc, sizeof(double) * 3 * cfg->n_ant);
     ALLOC(c->bidx, sizeof(int32_t) * cfg->n_ant);
     ALLOC(c->flags, sizeof(int32_t) * 4);
@@ -380,7 +636,7 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
     const size_t zbytes = (prec == PB3 ? (size_t)4 : cbytes(prec)) * zinst_n * c->Np * c->ldz;
     ALLOC(c->Z, zbytes);
     if (prec == PB3) ALLOC(c->Z_lo, zbytes);
-    ALLOC(c->part, cbytes(prec) * B * (size_t)c->max_splits * c->Np * c->Np);
+    ALLOC(c->part, cbytes(prec) * std::max((size_t)B * c->max_splits, (size_t)c->step_splits) * c->Np * c->Np);
     if (c->chunk < cfg->max_src) ALLOC(c->vacc, sizeof(double) * 2 * B * (size_t)c->N * c->N);
     ALLOC(c->work, sizeof(int32_t) * (3 * B + 1));  // item prefix, then k-splits and columns per split
     if (cfg->beam_mode != MATVIS_BEAM_SURROGATE && cfg->n_za >= 4) {
@@ -432,117 +688,6 @@ matvis_status matvis_finish(matvis_ctx *c) {
 }  // extern "C"
 
 namespace {
-
-// The tiles of a pair plan: rows of Z, where each pair lies (tile, element), and, where
-// Z is formed in LDS, the tiles' blocks and their bundles.
-struct PairTiles {
-    std::vector<int32_t> rows, loc, tiles;
-    std::vector<PairBundle> bundles;
-    int n_tiles = 0;
-};
-
-// 32 x 32 tiles over every sub-matrix's Z rows (antenna a, feed p -> row a nf + p)
-PairTiles pair_submatrices(const red::Plan &P, const int32_t *pair_a, const int32_t *pair_b, int n_pair, int n_ant,
-                           int nf) {
-    const int ST = kSubmatTile;
-    PairTiles T;
-    std::vector<int32_t> &rows = T.rows, &loc = T.loc, base;
-    std::vector<int> ntc;
-    for (size_t x = 0; x < P.A.size(); x++) {
-        const int ra = (int)P.A[x].size() * nf, rb = (int)P.B[x].size() * nf;
-        const int nta = (ra + ST - 1) / ST, ntb = (rb + ST - 1) / ST;
-        base.push_back((int32_t)(rows.size() / (2 * ST)));
-        ntc.push_back(ntb);
-        for (int ti = 0; ti < nta; ti++)
-            for (int tj = 0; tj < ntb; tj++) {
-                for (int r = 0; r < ST; r++) {
-                    const int q = ti * ST + r;
-                    rows.push_back(q < ra ? P.A[x][q / nf] * nf + q % nf : -1);
-                }
-                for (int r = 0; r < ST; r++) {
-                    const int q = tj * ST + r;
-                    rows.push_back(q < rb ? P.B[x][q / nf] * nf + q % nf : -1);
-                }
-            }
-    }
-    T.n_tiles = (int)(rows.size() / (2 * ST));
-    std::vector<int> sub_of(n_ant, -1), pos_in(n_ant, -1);
-    for (size_t x = 0; x < P.A.size(); x++)
-        for (size_t i = 0; i < P.A[x].size(); i++) {
-            sub_of[P.A[x][i]] = (int)x;
-            pos_in[P.A[x][i]] = (int)i;
-        }
-    loc.resize((size_t)n_pair * nf * nf * 2);
-    for (int u = 0; u < n_pair; u++) {
-        const int x = sub_of[pair_a[u]];
-        const auto &B = P.B[x];
-        const int ib = (int)(std::lower_bound(B.begin(), B.end(), pair_b[u]) - B.begin());
-        for (int p = 0; p < nf; p++)
-            for (int q = 0; q < nf; q++) {
-                const int r = pos_in[pair_a[u]] * nf + p, col = ib * nf + q;
-                const size_t e = (((size_t)u * nf + p) * nf + q) * 2;
-                loc[e] = base[x] + (r / ST) * ntc[x] + col / ST;
-                loc[e + 1] = (r % ST) * ST + col % ST;
-            }
-    }
-    return T;
-}
-
-// The rows that some pair uses, in order, in blocks of 16; the 16 x 16 tiles that hold a
-// pair, by column block; bundles of tiles as they come, closed when the next tile would
-// exceed a workgroup's tiles or staged blocks.
-PairTiles pair_bundles(const int32_t *pair_a, const int32_t *pair_b, int n_pair, int nf) {
-    PairTiles T;
-    std::map<int32_t, int32_t> pos;  // antenna -> place among the used ones
-    for (int u = 0; u < n_pair; u++) pos[pair_a[u]] = pos[pair_b[u]] = 0;
-    std::vector<int32_t> used;
-    for (auto &kv : pos) {
-        kv.second = (int32_t)used.size();
-        used.push_back(kv.first);
-    }
-    const int n_rows = (int)used.size() * nf, B = kPairTile;
-    std::map<std::pair<int32_t, int32_t>, int32_t> tile;  // (column block, row block) -> index
-    auto each = [&](auto f) {
-        for (int u = 0; u < n_pair; u++)
-            for (int p = 0; p < nf; p++)
-                for (int q = 0; q < nf; q++)
-                    f(((size_t)u * nf + p) * nf + q, pos[pair_a[u]] * nf + p, pos[pair_b[u]] * nf + q);
-    };
-    each([&](size_t, int32_t r, int32_t c) { tile[{c / B, r / B}] = 0; });
-    std::vector<int32_t> blocks;  // of the open bundle
-    auto slot = [&](int32_t b) {
-        return (int32_t)(std::find(blocks.begin(), blocks.end(), b) - blocks.begin());
-    };
-    PairBundle bd{0, 0, 0, 0};
-    auto close = [&]() {
-        bd.n_rows = (int32_t)blocks.size() * B;
-        bd.n_tiles = T.n_tiles - bd.tile0;
-        T.bundles.push_back(bd);
-        for (int32_t b : blocks)
-            for (int i = 0; i < B; i++) {
-                const int r = b * B + i;
-                T.rows.push_back(r < n_rows ? used[r / nf] * nf + r % nf : -1);
-            }
-        bd = PairBundle{(int32_t)T.rows.size(), 0, T.n_tiles, 0};
-        blocks.clear();
-    };
-    for (auto &kv : tile) {
-        const int32_t J = kv.first.first, I = kv.first.second;
-        const int fresh = (slot(I) == (int)blocks.size()) + (J != I && slot(J) == (int)blocks.size());
-        if ((int)blocks.size() + fresh > kPairBlocks || T.n_tiles - bd.tile0 == kPairTiles) close();
-        for (int32_t b : {J, I})
-            if (slot(b) == (int)blocks.size()) blocks.push_back(b);
-        T.tiles.push_back(slot(I) | slot(J) << 8);
-        kv.second = T.n_tiles++;
-    }
-    close();
-    T.loc.resize((size_t)n_pair * nf * nf * 2);
-    each([&](size_t e, int32_t r, int32_t c) {
-        T.loc[2 * e] = tile[{c / B, r / B}];
-        T.loc[2 * e + 1] = (r % B) * B + c % B;
-    });
-    return T;
-}
 
 // Enqueue the whole simulate sequence on stream s (no host waits).
 matvis_status enqueue_simulate(matvis_ctx *c, const double *antpos, const int32_t *beam_idx, const double *freqs,
@@ -634,9 +779,20 @@ matvis_status enqueue_simulate(matvis_ctx *c, const double *antpos, const int32_
                 ha.n_bal = c->n_bal;
                 ha.min_cols = kMinSplitCols;
                 ha.grid = c->herk_grid;
-                if (!pairs) STEP(c, MATVIS_STEP_OTHER, s, launch_worklist(prec, ha, c->fused ? 1 : 0, s));
+                if (!pairs && !c->full.n_bundle)
+                    STEP(c, MATVIS_STEP_OTHER, s, launch_worklist(prec, ha, c->fused ? 1 : 0, s));
 
-                if (c->fused && !pairs) {
+                int n_split = c->max_splits;  // of the tiles
+                if (c->full.n_bundle && !pairs) {
+                    // a batch of fewer instances than the buffers hold leaves room for more splits
+                    n_split = tile_splits(c, c->full, bt.n_inst, c->pair_splits,
+                                          (int64_t)c->max_splits * B_cap / bt.n_inst);
+                    TileArgs ta = tile_args(c, c->full, bt, freqs, n_split);
+                    ta.part = c->part;
+                    ta.part_stride = (int64_t)c->Np * c->Np;
+                    ta.ld = c->Np;
+                    STEP(c, MATVIS_STEP_HERK, s, launch_tiles(prec, ta, s));
+                } else if (c->fused && !pairs) {
                     FusedArgs fa{};
                     fa.antc = c->antc;
                     fa.bidx = c->bidx;
@@ -700,29 +856,12 @@ matvis_status enqueue_simulate(matvis_ctx *c, const double *antpos, const int32_
                 }
                 if (pairs) {
                     // App. A: only the planned sub-matrices, then the requested pairs
-                    if (c->pr_nbundle) {
-                        PairArgs pa{};
-                        pa.rows = c->pr_rows;
-                        pa.tiles = c->pr_tile_list;
-                        pa.bundles = c->pr_bundles;
-                        pa.n_tiles = c->pr_tiles;
-                        pa.n_bundle = c->pr_nbundle;
-                        pa.count = c->count;
-                        pa.n_ax = g.n_ax;
-                        pa.n_feed = g.n_feed;
-                        pa.n_beam = g.n_beam;
-                        pa.nfb = nfb;
-                        pa.n_inst = bt.n_inst;
-                        pa.f0 = f0;
-                        pa.n_split = c->pr_splits;
-                        pa.antc = c->antc;
-                        pa.bidx = c->bidx;
-                        pa.freqs = freqs;
-                        pa.s_hat = c->s_hat;
-                        pa.B = c->A;
-                        pa.ld_src = c->chunk;
-                        pa.part = c->pr_part;
-                        STEP(c, MATVIS_STEP_HERK, s, launch_pair_tiles(prec, pa, s));
+                    if (c->pr_list.n_bundle) {
+                        TileArgs ta = tile_args(c, c->pr_list, bt, freqs, c->pr_splits);
+                        ta.part = c->pr_part;
+                        ta.part_stride = (int64_t)c->pr_tiles * kTile * kTile;
+                        ta.ld = kTile;
+                        STEP(c, MATVIS_STEP_HERK, s, launch_tiles(prec, ta, s));
                     } else {
                         SubmatArgs sa{};
                         sa.Z = c->fused ? c->pr_Z : c->Z;
@@ -744,7 +883,7 @@ matvis_status enqueue_simulate(matvis_ctx *c, const double *antpos, const int32_
                     sr.part = c->pr_part;
                     sr.n_tiles = c->pr_tiles;
                     sr.max_splits = c->pr_splits;
-                    sr.st = c->pr_nbundle ? kPairTile : kSubmatTile;
+                    sr.st = c->pr_list.n_bundle ? kTile : kSubmatTile;
                     sr.loc = c->pr_loc;
                     sr.n_pair = c->pr_n;
                     sr.n_feed = g.n_feed;
@@ -752,7 +891,7 @@ matvis_status enqueue_simulate(matvis_ctx *c, const double *antpos, const int32_
                     sr.n_ax = g.n_ax;
                     sr.nfb = nfb;
                     sr.n_inst = bt.n_inst;
-                    sr.ksplit = c->pr_nbundle ? 0 : c->ksplit;
+                    sr.ksplit = c->pr_list.n_bundle ? 0 : c->ksplit;
                     sr.vacc = c->pr_vacc;
                     sr.first = ch == 0;
                     sr.last = ch == n_chunks - 1;
@@ -767,13 +906,13 @@ matvis_status enqueue_simulate(matvis_ctx *c, const double *antpos, const int32_
                 ra.part = c->part;
                 ra.n_rows = c->N;
                 ra.n_rows_pad = c->Np;
-                ra.max_splits = c->max_splits;
+                ra.max_splits = n_split;
                 ra.count = c->count;
-                ra.n_ax = g.n_ax;
+                ra.n_ax = c->full.coherent ? 1 : g.n_ax;
                 ra.nfb = nfb;
                 ra.n_inst = bt.n_inst;
-                ra.ksplit = c->ksplit;
-                ra.nsplit = ha.nsplit;
+                ra.ksplit = c->full.n_bundle ? 0 : c->ksplit;
+                ra.nsplit = c->full.n_bundle ? nullptr : ha.nsplit;
                 ra.vacc = c->vacc;
                 ra.first = ch == 0;
                 ra.last = ch == n_chunks - 1;
@@ -889,29 +1028,20 @@ matvis_status matvis_set_pairs(matvis_ctx *c, const int32_t *pair_a, const int32
     const int nf = g.n_feed;
     const bool in_lds = c->fused && g.precision != P64;  // else Z in device memory
     int64_t size = 0;
-    PairTiles T;
+    Tiles T;
     try {
         const red::Plan P = red::plan(pair_a, pair_b, n_pair, g.n_ant, n_sub);
         for (size_t x = 0; x < P.A.size(); x++) size += (int64_t)P.A[x].size() * P.B[x].size();
-        T = in_lds ? pair_bundles(pair_a, pair_b, n_pair, nf)
+        T = in_lds ? pair_tiles(pair_a, pair_b, n_pair, nf)
                    : pair_submatrices(P, pair_a, pair_b, n_pair, g.n_ant, nf);
     } catch (const std::bad_alloc &) {
         return fail(c, MATVIS_ENOMEM, "host memory for the pair plan");
     }
-    const int ST = in_lds ? kPairTile : kSubmatTile;
+    const int ST = in_lds ? kTile : kSubmatTile;
     const int B_cap = c->ntb * c->nfb;
     const auto &rows = T.rows;
     const auto &loc = T.loc;
     const int n_tiles = T.n_tiles;
-    int splits = c->pair_splits;
-    if (in_lds) {
-        // A workgroup has a CU to itself: as many k-splits as fill whole rounds of the
-        // CUs, none above the context's columns per split nor of fewer than 8 stages.
-        const int64_t per_split = (int64_t)B_cap * (int64_t)T.bundles.size();
-        const int64_t rounds = (per_split * splits + c->n_cu - 1) / c->n_cu;
-        const int64_t most = std::max<int64_t>(1, c->ldz / 128);
-        splits = (int)std::max<int64_t>(splits, std::min(most, rounds * c->n_cu / per_split));
-    }
     HIPCHK(c, hipSetDevice(c->device));
     HIPCHK(c, hipDeviceSynchronize());
     // graphs captured with an earlier plan hold its buffers
@@ -919,7 +1049,8 @@ matvis_status matvis_set_pairs(matvis_ctx *c, const int32_t *pair_a, const int32
     c->graphs.clear();
     c->graph_order.clear();
     for (void *q : {(void *)c->pr_rows, (void *)c->pr_loc, c->pr_part, (void *)c->pr_vacc, c->pr_Z,
-                    (void *)c->pr_bundles, (void *)c->pr_tile_list}) {
+                    (void *)c->pr_list.rows, (void *)c->pr_list.tiles, (void *)c->pr_list.dst,
+                    (void *)c->pr_list.bundles}) {
         if (!q) continue;
         auto it = std::find(c->allocs.begin(), c->allocs.end(), q);
         if (it != c->allocs.end()) c->allocs.erase(it);
@@ -929,12 +1060,17 @@ matvis_status matvis_set_pairs(matvis_ctx *c, const int32_t *pair_a, const int32
     c->pr_part = nullptr;
     c->pr_vacc = nullptr;
     c->pr_Z = nullptr;
-    c->pr_bundles = nullptr;
-    c->pr_tile_list = nullptr;
-    c->pr_nbundle = 0;
+    c->pr_list = DevTiles{};
     c->pr_set = false;
     matvis_status st;
-    if ((st = dalloc(c, &c->pr_rows, sizeof(int32_t) * rows.size())) != MATVIS_OK) return st;
+    int splits = c->pair_splits;
+    if (in_lds) {
+        if ((st = upload_tiles(c, T, c->pr_list)) != MATVIS_OK) return st;
+        splits = tile_splits(c, c->pr_list, B_cap, splits, INT32_MAX);
+    } else {
+        if ((st = dalloc(c, &c->pr_rows, sizeof(int32_t) * rows.size())) != MATVIS_OK) return st;
+        HIPCHK(c, hipMemcpy(c->pr_rows, rows.data(), sizeof(int32_t) * rows.size(), hipMemcpyHostToDevice));
+    }
     if ((st = dalloc(c, &c->pr_loc, sizeof(int32_t) * loc.size())) != MATVIS_OK) return st;
     if ((st = dalloc(c, &c->pr_part, cbytes(g.precision) * (size_t)B_cap * splits * n_tiles * ST * ST)) !=
         MATVIS_OK)
@@ -943,19 +1079,10 @@ matvis_status matvis_set_pairs(matvis_ctx *c, const int32_t *pair_a, const int32
     if (c->fused && g.precision == P64) {  // its batch is sized for a Z
         if ((st = dalloc(c, &c->pr_Z, cbytes(g.precision) * (size_t)B_cap * c->Np * c->ldz)) != MATVIS_OK) return st;
     }
-    if (in_lds) {
-        if ((st = dalloc(c, &c->pr_bundles, sizeof(PairBundle) * T.bundles.size())) != MATVIS_OK) return st;
-        if ((st = dalloc(c, &c->pr_tile_list, sizeof(int32_t) * T.tiles.size())) != MATVIS_OK) return st;
-        HIPCHK(c, hipMemcpy(c->pr_bundles, T.bundles.data(), sizeof(PairBundle) * T.bundles.size(),
-                            hipMemcpyHostToDevice));
-        HIPCHK(c, hipMemcpy(c->pr_tile_list, T.tiles.data(), sizeof(int32_t) * T.tiles.size(), hipMemcpyHostToDevice));
-    }
-    HIPCHK(c, hipMemcpy(c->pr_rows, rows.data(), sizeof(int32_t) * rows.size(), hipMemcpyHostToDevice));
     HIPCHK(c, hipMemcpy(c->pr_loc, loc.data(), sizeof(int32_t) * loc.size(), hipMemcpyHostToDevice));
     c->pr_n = n_pair;
     c->pr_tiles = n_tiles;
     c->pr_splits = splits;
-    c->pr_nbundle = (int32_t)T.bundles.size();
     c->pr_size = size;
     c->pr_set = true;
     if (size_out) *size_out = size;
@@ -1108,8 +1235,8 @@ matvis_status matvis_step_herk(matvis_ctx *c, const void *Zin, int32_t n_row, in
     ha.n_ax = 1;
     ha.nfb = 1;
     ha.n_inst = 1;
-    ha.ksplit = c->ksplit;
-    ha.max_splits = c->max_splits;
+    ha.ksplit = c->step_ksplit;
+    ha.max_splits = c->step_splits;
     ha.part = c->part;
     ha.work = c->work;
     ha.nsplit = c->work + c->ntb * c->nfb + 1;
@@ -1122,13 +1249,13 @@ matvis_status matvis_step_herk(matvis_ctx *c, const void *Zin, int32_t n_row, in
     ra.part = c->part;
     ra.n_rows = n_row;
     ra.n_rows_pad = np;
-    ra.max_splits = c->max_splits;
+    ra.max_splits = c->step_splits;
     ra.count = nullptr;
     ra.fixed_k = n_col;
     ra.n_ax = 1;
     ra.nfb = 1;
     ra.n_inst = 1;
-    ra.ksplit = c->ksplit;
+    ra.ksplit = c->step_ksplit;
     ra.vacc = nullptr;
     ra.first = 1;
     ra.last = 1;
