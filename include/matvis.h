@@ -185,9 +185,9 @@ matvis_status matvis_submatrix_plan(const int32_t *pair_a, const int32_t *pair_b
 /* Plan the sub-matrix product for the pairs (pair_a[u], pair_b[u]) (host
  * arrays, antennas in [0, n_ant); any pairs, usually the representatives of
  * matvis_redundant_groups) with n_sub sub-matrices, and upload the plan to
- * the context's device.  Any precision: with Z in device memory (FP64, or
- * MATVIS_FLAG_UNFUSED) the sub-matrix rows are gathered from it; otherwise
- * (FP32 / BF16X3) they are formed in the product's stages from the beam and
+ * the context's device.  Any precision: with Z in device memory
+ * (MATVIS_FLAG_UNFUSED) the sub-matrix rows are gathered from it; otherwise the
+ * 16 x 16 tiles that hold a pair are multiplied from rows formed in LDS from the beam and
  * the fringe phase, as the full product forms Z.  Allocates the plan's
  * scratch (so call it outside graph capture); replaces an earlier plan.  *size_out (may be NULL) receives the total sub-matrix size
  * sum_x |A_x| |B_x| in antenna pairs. */
@@ -367,10 +367,11 @@ matvis_status matvis_profile_read(matvis_ctx *ctx, double *ms, int64_t *launches
 
 /* Which kernel forms the product of Eq. zz for this context (fixed at init):
  *   MATVIS_PATH_Z_IN_HBM   Z is written to device memory by its own step and
- *                          V = Z Z^H reads it (FP64, or MATVIS_FLAG_UNFUSED).
- *                          Reported for every FP64 context, also where matvis_simulate
- *                          takes the axis sum per source first and forms Z inside the
- *                          product (2 feeds x 2 axes, one shared beam, without
+ *                          V = Z Z^H reads it (MATVIS_FLAG_UNFUSED).
+ *                          Reported for every FP64 context, also where
+ *                          matvis_simulate forms Z inside the product (over
+ *                          sources for 2 feeds x 2 axes with one shared beam, in
+ *                          16 x 16 tiles for the other shapes; all without
  *                          MATVIS_FLAG_UNFUSED);
  *   MATVIS_PATH_FUSED      Z formed in LDS in blocks of 16 rows and multiplied in
  *                          16 x 16 tiles of the lower triangle (2 feeds x 2 axes

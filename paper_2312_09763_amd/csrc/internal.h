@@ -323,6 +323,12 @@ struct TileArgs {
 };
 int tile_waves(int n_rows, int n_tiles);
 hipError_t launch_tiles(int prec, const TileArgs &a, hipStream_t s);
+// The same in FP64 (kernels_herk_f64.hip; B and partials complex128): 8 waves with a CU's
+// LDS or 4 with half of it.
+constexpr int kWaveTiles64 = 8;
+__host__ __device__ constexpr int tile64_blocks(int waves) { return waves == 8 ? 16 : 7; }
+int tile64_waves(int n_rows, int n_tiles);
+hipError_t launch_tiles64(const TileArgs &a, hipStream_t s);
 // Columns of each of n k-splits of K columns, whole stages of 16 (the last ones may be short or empty)
 __host__ __device__ inline int64_t split_cols(int64_t K, int64_t n) { return ((K + n - 1) / n + 15) / 16 * 16; }
 struct SubmatReduceArgs {

@@ -1,4 +1,6 @@
-// FP64 product over sources (2 feeds x 2 axes, one shared beam).  The axis sum is taken per source first,
+// FP64 products with Z formed in LDS.
+//
+// Product over sources (2 feeds x 2 axes, one shared beam).  The axis sum is taken per source first,
 //   V[(a,p),(b,q)] = sum_m F_a(m) conj(F_b(m)) C_pq(m),  C_pq = sum_k B_pk conj(B_qk),
 // which halves the multiply-adds of Z Z^H, and the fringe rows F are formed in
 // LDS, so Z never goes through device memory.
@@ -339,6 +341,182 @@ __global__ void __launch_bounds__(512, 1) k_herk_coh64(FusedArgs a) {
     }
 }
 
+// ---------------------------------------------------------------------------
+// FP64 product over lists of 16 x 16 tiles with Z formed in LDS: scalar arrays, several
+// beams, and requested pairs.  Lists and bundles are those of kernels_tiles.hip:
+// a workgroup forms all rows of its bundle once per stage of 16 columns and multiplies up
+// to eight tiles a wave.  MFMA-bound (1024 cycles a tile and stage), forming beside it by the
+// other wave of the SIMD: 8 waves with a CU's LDS, or 4 with half of it.
+// Against Z written to memory and multiplied from there in blocks of 64 (with k-splits
+// that fill the chip), whole calls: 37 antennas, 2000 sources, 8 instances 83 -> 52 us; 30 / 100
+// antennas, 30 000 sources, 32 instances 434 / 1158 -> 171 / 600 us.
+// ---------------------------------------------------------------------------
+struct Col64 {
+    double x, y, z, pad;  // s_hat
+    double2 b[2];         // values of both feeds (one beam)
+};
+
+struct Row64 {
+    double x, y, z;     // x_a
+    int32_t bp, pad;    // beam n_feed + feed
+};
+
+template <int WAVES>
+__global__ void __launch_bounds__(64 * WAVES, 2) k_tiles64(TileArgs a) {
+    constexpr int ROWS = 16 * tile64_blocks(WAVES), BUF = ROWS * kRS64, NT = kWaveTiles64;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[2 * BUF];
+    __shared__ __attribute__((aligned(16))) Col64 col[2][kS64];
+    __shared__ Row64 row[ROWS];
+    __shared__ double2 turn[kTurn];  // (cos, -sin) of i / 256 turns
+    static_assert((2 * BUF + sizeof(col) + sizeof(row) + sizeof(turn)) * (8 / WAVES) <= 160 * 1024, "LDS");
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int l16 = lane & 15, lk = lane >> 4;
+    const int64_t item = blockIdx.x;
+    const int s = (int)(item % a.n_split);
+    const int bundle = (int)((item / a.n_split) % a.n_bundle);
+    const int inst = (int)(item / ((int64_t)a.n_split * a.n_bundle));
+    const int tslot = inst / a.nfb;
+    const int nx = a.n_ax, nf = a.n_feed;
+    const int64_t K = (int64_t)nx * a.count[tslot];
+    const int64_t kc = split_cols(K, a.n_split);
+    const int64_t kb = (int64_t)s * kc, ke = kb + kc < K ? kb + kc : K;
+    if (kb >= K) return;  // an empty k-split: the reduction leaves it out too
+    const TileBundle bd = a.bundles[bundle];
+    const int n_rows = bd.n_rows;
+    const double nu_c = a.freqs[a.f0 + inst % a.nfb] / kSpeedOfLight;
+    const double *sh = a.s_hat + (int64_t)tslot * 3 * a.ld_src;
+    const double2 *Bi = (const double2 *)a.B + (int64_t)inst * a.n_beam * nf * nx * a.ld_src;  // [beam][feed][axis][m]
+    const bool shared_beam = a.n_beam == 1;
+    for (int q = tid; q < n_rows; q += 64 * WAVES) {
+        const int z = a.rows[bd.row0 + q], ant = z < 0 ? 0 : z / nf;  // padding rows reach no stored output
+        row[q] = Row64{a.antc[3 * ant], a.antc[3 * ant + 1], a.antc[3 * ant + 2],
+                       a.bidx[ant] * nf + (z < 0 ? 0 : z % nf), 0};
+    }
+    for (int q = tid; q < kTurn; q += 64 * WAVES) {
+        double sn, cs;
+        sincospi(q * (2.0 / kTurn), &sn, &cs);
+        turn[q] = make_double2(cs, -sn);
+    }
+    const int n_stage = (int)((ke - kb + kS64 - 1) / kS64);
+
+    // the columns of a stage, one per lane of the first 16
+    const bool fetcher = tid < kS64;
+    Col64 fc;
+    auto fetch = [&](int stage) {
+        const int64_t c = kb + (int64_t)stage * kS64 + tid;
+        fc.x = fc.y = fc.z = fc.pad = 0.0;
+        fc.b[0] = fc.b[1] = make_double2(0.0, 0.0);
+        if (c < ke) {
+            const int64_t m = c / nx;
+            fc.x = sh[m];
+            fc.y = sh[a.ld_src + m];
+            fc.z = sh[2 * a.ld_src + m];
+            if (shared_beam) {
+                fc.b[0] = Bi[(c % nx) * a.ld_src + m];
+                if (nf == 2) fc.b[1] = Bi[(nx + c % nx) * a.ld_src + m];
+            }
+        }
+    };
+    // one column (fs) of rows fr + 4 WAVES k
+    const int fs = tid % kS64, fr = tid / kS64;
+    auto produce = [&](unsigned char *buf, int stage) __attribute__((always_inline)) {
+        const Col64 &c = col[stage & 1][fs];
+        const double x = c.x, y = c.y, z = c.z;
+        const int64_t cg = kb + (int64_t)stage * kS64 + fs;
+#pragma unroll 1
+        for (int r = fr; r < n_rows; r += 4 * WAVES) {
+            const Row64 e = row[r];
+            double2 b;
+            if (shared_beam)
+                b = c.b[e.bp];
+            else
+                b = cg < ke ? Bi[(e.bp * nx + cg % nx) * a.ld_src + cg / nx] : make_double2(0.0, 0.0);
+            const double2 f = fringe64(nu_c * (e.x * x + e.y * y + e.z * z), turn);
+            *(double2 *)(buf + r * kRS64 + fs * 16) =
+                make_double2(b.x * f.x - b.y * f.y, b.x * f.y + b.y * f.x);
+        }
+    };
+
+    if (fetcher) {
+        fetch(0);
+        col[0][tid] = fc;
+        fetch(1);
+        col[1][tid] = fc;
+    }
+    // this wave's tiles, sorted by column block: LDS offsets of their row and column blocks
+    // (`fresh`: bit t set where the column block is not that of tile t - 1)
+    const int t0 = bd.n_tiles * wave / WAVES, nt = bd.n_tiles * (wave + 1) / WAVES - t0;
+    uint32_t ro[NT], co[NT], fresh = 0;
+#pragma unroll
+    for (int t = 0; t < NT; t++) {
+        const int32_t e = a.tiles[bd.tile0 + (t < nt ? t0 + t : 0)];
+        ro[t] = __builtin_amdgcn_readfirstlane((e & 255) * 16 * kRS64);
+        co[t] = __builtin_amdgcn_readfirstlane((e >> 8) * 16 * kRS64);
+        if (t == 0 || co[t] != co[t - 1]) fresh |= 1u << t;
+    }
+    __syncthreads();
+    produce(lds, 0);
+    __syncthreads();
+
+    auto stages = [&](auto first) __attribute__((always_inline)) {
+        f64x4 re[NT], im[NT];
+#pragma unroll
+        for (int t = 0; t < NT; t++) re[t] = im[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+        auto consume = [&](const unsigned char *buf) __attribute__((always_inline)) {
+            const unsigned char *p = buf + l16 * kRS64 + lk * 16;
+            double2 b[4];
+            int n = nt;
+            uint32_t fr_ = fresh;
+            asm volatile("" : "+s"(n), "+s"(fr_));  // tested here: no condition is kept across the stages
+#pragma unroll
+            for (int t = 0; t < NT; t++) {
+                if (t < n) {
+                    if (fr_ >> t & 1)
+#pragma unroll
+                        for (int q = 0; q < 4; q++) b[q] = *(const double2 *)(p + co[t] + q * 64);
+                    double2 r[4];
+#pragma unroll
+                    for (int q = 0; q < 4; q++) r[q] = *(const double2 *)(p + ro[t] + q * 64);
+#pragma unroll
+                    for (int q = 0; q < 4; q++) mfma64(r[q].x, r[q].y, b[q], re[t], im[t]);
+                }
+            }
+        };
+        for (int stg = 0; stg < n_stage; stg++) {
+            unsigned char *cur = lds + (stg & 1) * BUF;
+            unsigned char *nxt = lds + ((stg + 1) & 1) * BUF;
+            const bool more = stg + 1 < n_stage;
+            if constexpr (decltype(first)::value) {
+                consume(cur);
+                // the columns of stage stg + 2 replace those of stage stg, last read a stage ago
+                if (fetcher && stg + 2 < n_stage) fetch(stg + 2);
+                if (more) produce(nxt, stg + 1);
+                if (fetcher && stg + 2 < n_stage) col[stg & 1][tid] = fc;
+            } else {
+                if (more) produce(nxt, stg + 1);
+                consume(cur);
+            }
+            __syncthreads();
+        }
+        // the write-out's addresses are formed here rather than kept live across the stages
+        int r4 = lk, c = l16, ld = a.ld;
+        asm volatile("" : "+v"(r4), "+v"(c), "+v"(ld));
+        double2 *P = (double2 *)a.part + ((int64_t)inst * a.n_split + s) * a.part_stride;
+        const int32_t *dst = a.dst + bd.tile0 + t0;
+#pragma unroll
+        for (int t = 0; t < NT; t++)
+            if (t < nt)
+#pragma unroll
+                for (int e = 0; e < 4; e++)
+                    P[(int64_t)dst[t] + (4 * e + r4) * ld + c] = make_double2(re[t][e], im[t][e]);
+    };
+    if (wave < WAVES / 2)
+        stages(std::true_type{});
+    else
+        stages(std::false_type{});
+}
+
 }  // namespace
 
 bool f64_over_sources(int n_feed, int n_ax, int n_beam) { return n_feed == 2 && n_ax == 2 && n_beam == 1; }
@@ -351,6 +529,23 @@ int f64_items(int n_ant) {
 hipError_t launch_herk_f64(const FusedArgs &a, hipStream_t s) {
     if (a.n_inst <= 0) return hipSuccess;
     k_herk_coh64<<<a.grid, 512, 0, s>>>(a);
+    return hipGetLastError();
+}
+
+int tile64_waves(int n_rows, int n_tiles) {
+    return n_rows <= 16 * tile64_blocks(4) && n_tiles <= 4 * kWaveTiles64 ? 4 : 8;
+}
+
+hipError_t launch_tiles64(const TileArgs &a, hipStream_t s) {
+    const int64_t items = (int64_t)a.n_inst * a.n_bundle * a.n_split;
+    if (items <= 0) return hipSuccess;
+    if (items > 0x7fffffff || a.n_feed > 2 || a.n_ax > 2 || a.coherent) return hipErrorInvalidValue;
+    if (a.waves == 4)
+        k_tiles64<4><<<(unsigned)items, 256, 0, s>>>(a);
+    else if (a.waves == 8)
+        k_tiles64<8><<<(unsigned)items, 512, 0, s>>>(a);
+    else
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

@@ -41,8 +41,9 @@ struct GraphKey {
 struct DevTiles {
     int32_t n_bundle = 0;  // 0: none
     int32_t waves = 16, coherent = 0;
-    int32_t *rows = nullptr, *tiles = nullptr, *dst = nullptr;
-    TileBundle *bundles = nullptr;
+    int32_t per_cu = 1;    // workgroups that run on a CU at once
+    TileBundle *bundles = nullptr;  // the allocation, then the other lists
+    int32_t *tiles = nullptr, *dst = nullptr, *rows = nullptr;
 };
 
 struct matvis_ctx {
@@ -102,7 +103,6 @@ struct matvis_ctx {
     int32_t *pr_rows = nullptr;  // [tiles][2][ST] Z rows (Z in device memory)
     int32_t *pr_loc = nullptr;   // [n_pair][nf][nf][2]
     void *pr_part = nullptr;     // [B_cap][pr_splits][tiles][ST][ST]
-    void *pr_Z = nullptr;        // fused FP64 contexts: Z of a batch for the pairs
     int pr_splits = 1;
     DevTiles pr_list;            // Z formed in LDS: the pairs' tiles
     DevTiles full;               // the tiles of V, where the product takes them (path FUSED)
@@ -287,8 +287,9 @@ Tiles pair_submatrices(const red::Plan &P, const int32_t *pair_a, const int32_t 
 // numbers of tiles, closed early when the next tile would exceed the staged blocks;
 // row(b, i) is the Z row of row i of block b, or -1.
 template <typename Row>
-void bundle_tiles(Tiles &T, const std::vector<std::pair<int32_t, int32_t>> &list, Row row) {
-    const int n = (int)list.size(), cap = 16 * kWaveTiles;
+void bundle_tiles(Tiles &T, int prec, const std::vector<std::pair<int32_t, int32_t>> &list, Row row) {
+    const int n = (int)list.size(), cap = prec == P64 ? 8 * kWaveTiles64 : 16 * kWaveTiles;
+    const int max_blocks = prec == P64 ? tile64_blocks(8) : tile_blocks(16);
     const int target = n > 0 ? (n + (n + cap - 1) / cap - 1) / ((n + cap - 1) / cap) : 0;
     std::vector<int32_t> blocks;  // of the open bundle
     auto slot = [&](int32_t b) { return (int32_t)(std::find(blocks.begin(), blocks.end(), b) - blocks.begin()); };
@@ -305,7 +306,7 @@ void bundle_tiles(Tiles &T, const std::vector<std::pair<int32_t, int32_t>> &list
     for (const auto &t : list) {
         const int32_t I = t.first, J = t.second;
         const int fresh = (slot(I) == (int)blocks.size()) + (J != I && slot(J) == (int)blocks.size());
-        if ((int)blocks.size() + fresh > tile_blocks(16) || T.n_tiles - bd.tile0 == target) close();
+        if ((int)blocks.size() + fresh > max_blocks || T.n_tiles - bd.tile0 == target) close();
         for (int32_t b : {J, I})
             if (slot(b) == (int)blocks.size()) blocks.push_back(b);
         T.tiles.push_back(slot(I) | slot(J) << 8);
@@ -316,7 +317,7 @@ void bundle_tiles(Tiles &T, const std::vector<std::pair<int32_t, int32_t>> &list
 
 // The rows that some pair uses, in order, in blocks of 16, and the tiles that hold a pair,
 // by column block.
-Tiles pair_tiles(const int32_t *pair_a, const int32_t *pair_b, int n_pair, int nf) {
+Tiles pair_tiles(int prec, const int32_t *pair_a, const int32_t *pair_b, int n_pair, int nf) {
     Tiles T;
     std::map<int32_t, int32_t> pos;  // antenna -> place among the used ones
     for (int u = 0; u < n_pair; u++) pos[pair_a[u]] = pos[pair_b[u]] = 0;
@@ -340,7 +341,7 @@ Tiles pair_tiles(const int32_t *pair_a, const int32_t *pair_b, int n_pair, int n
         T.dst.push_back((int32_t)list.size() * B * B);
         list.push_back({kv.first.second, kv.first.first});
     }
-    bundle_tiles(T, list, [&](int32_t b, int i) {
+    bundle_tiles(T, prec, list, [&](int32_t b, int i) {
         const int r = b * B + i;
         return r < n_rows ? used[r / nf] * nf + r % nf : -1;
     });
@@ -352,11 +353,11 @@ Tiles pair_tiles(const int32_t *pair_a, const int32_t *pair_b, int n_pair, int n
     return T;
 }
 
-// The lower triangle of V in partials of Np columns.  Up to 16 blocks the tiles go column
-// by column (one or two bundles); more blocks in rectangles of 12 x 8, which fill a
-// workgroup with 20 blocks.  coherent: planes 0, 1, 2 (P0, P1, L) of antenna block b are
+// The lower triangle of V in partials of Np columns.  Up to 16 blocks (FP64: 10, one bundle)
+// the tiles go column by column; more blocks in rectangles of 12 x 8, which fill a
+// workgroup with 20 blocks (FP64: 8 x 8 with 16).  coherent: planes 0, 1, 2 (P0, P1, L) of antenna block b are
 // blocks 3 b, 3 b + 1, 3 b + 2.
-Tiles full_tiles(int n_ant, int nf, int Np, bool coherent) {
+Tiles full_tiles(int prec, int n_ant, int nf, int Np, bool coherent) {
     Tiles T;
     std::vector<std::pair<int32_t, int32_t>> list;
     if (coherent) {
@@ -367,14 +368,15 @@ Tiles full_tiles(int n_ant, int nf, int Np, bool coherent) {
                     list.push_back({3 * I + (pq == 0 ? 0 : pq == 3 ? 1 : 2), 3 * J + (pq == 3 ? 1 : 0)});
                     T.dst.push_back(I | J << 8 | pq << 16);
                 }
-        bundle_tiles(T, list, [&](int32_t b, int i) {
+        bundle_tiles(T, prec, list, [&](int32_t b, int i) {
             const int ant = b / 3 * kTile + i;
             return ant < n_ant ? 3 * ant + b % 3 : -1;
         });
         return T;
     }
     const int N = n_ant * nf, nb = (N + kTile - 1) / kTile;
-    const int rj = nb <= 16 ? nb : 8, ri = nb <= 16 ? nb : 12;
+    const bool f64 = prec == P64, whole = nb <= (f64 ? 10 : 16);
+    const int rj = whole ? nb : 8, ri = whole ? nb : f64 ? 8 : 12;
     for (int J0 = 0; J0 < nb; J0 += rj)
         for (int I0 = J0 / ri * ri; I0 < nb; I0 += ri)
             for (int J = J0; J < std::min(J0 + rj, nb); J++)
@@ -382,7 +384,7 @@ Tiles full_tiles(int n_ant, int nf, int Np, bool coherent) {
                     list.push_back({I, J});
                     T.dst.push_back((I * Np + J) * kTile);
                 }
-    bundle_tiles(T, list, [&](int32_t b, int i) { return b * kTile + i < N ? b * kTile + i : -1; });
+    bundle_tiles(T, prec, list, [&](int32_t b, int i) { return b * kTile + i < N ? b * kTile + i : -1; });
     return T;
 }
 
@@ -390,7 +392,7 @@ Tiles full_tiles(int n_ant, int nf, int Np, bool coherent) {
 // least), more while they fill whole rounds of the workgroups that run at once, none of
 // fewer than 8 stages of the context's columns, at most `most`.
 int tile_splits(const matvis_ctx *c, const DevTiles &t, int n_inst, int64_t base, int64_t most) {
-    const int64_t slots = (int64_t)c->n_cu * (16 / t.waves), per_split = (int64_t)n_inst * t.n_bundle;
+    const int64_t slots = (int64_t)c->n_cu * t.per_cu, per_split = (int64_t)n_inst * t.n_bundle;
     const int64_t rounds = (per_split * base + slots - 1) / slots;
     // (the split sum is a chain of its own, so their number grows as the root of the columns)
     const int64_t fill = std::min({rounds * slots / per_split, c->ldz / 128, (int64_t)std::sqrt((double)c->ldz)});
@@ -424,26 +426,31 @@ TileArgs tile_args(const matvis_ctx *c, const DevTiles &t, const Batch &bt, cons
     return a;
 }
 
-void set_launch(const Tiles &T, DevTiles &d) {
+void set_launch(int prec, const Tiles &T, DevTiles &d) {
     int rows = 0, tiles = 0;
     for (const TileBundle &b : T.bundles) rows = std::max(rows, b.n_rows), tiles = std::max(tiles, b.n_tiles);
-    d.waves = tile_waves(rows, tiles);
+    d.waves = prec == P64 ? tile64_waves(rows, tiles) : tile_waves(rows, tiles);
+    d.per_cu = (prec == P64 ? 8 : 16) / d.waves;
     d.n_bundle = (int32_t)T.bundles.size();
 }
 
-// A tile list's device copy.
+// A tile list's device copy, in one allocation and one transfer.
 matvis_status upload_tiles(matvis_ctx *c, const Tiles &T, DevTiles &d) {
-    auto put = [&](auto **p, const auto &v) -> matvis_status {
-        matvis_status st = dalloc(c, p, sizeof(v[0]) * v.size());
-        if (st != MATVIS_OK) return st;
-        HIPCHK(c, hipMemcpy(*p, v.data(), sizeof(v[0]) * v.size(), hipMemcpyHostToDevice));
-        return MATVIS_OK;
-    };
-    matvis_status st;
-    if ((st = put(&d.rows, T.rows)) != MATVIS_OK || (st = put(&d.tiles, T.tiles)) != MATVIS_OK ||
-        (st = put(&d.dst, T.dst)) != MATVIS_OK || (st = put(&d.bundles, T.bundles)) != MATVIS_OK)
-        return st;
-    set_launch(T, d);
+    static_assert(sizeof(TileBundle) == 4 * sizeof(int32_t), "bundles are stored as four words");
+    std::vector<int32_t> all;
+    for (const TileBundle &b : T.bundles) all.insert(all.end(), {b.row0, b.n_rows, b.tile0, b.n_tiles});
+    all.insert(all.end(), T.tiles.begin(), T.tiles.end());
+    all.insert(all.end(), T.dst.begin(), T.dst.end());
+    all.insert(all.end(), T.rows.begin(), T.rows.end());
+    int32_t *p = nullptr;
+    matvis_status st = dalloc(c, &p, sizeof(int32_t) * all.size());
+    if (st != MATVIS_OK) return st;
+    d.bundles = (TileBundle *)p;
+    HIPCHK(c, hipMemcpy(p, all.data(), sizeof(int32_t) * all.size(), hipMemcpyHostToDevice));
+    d.tiles = p + 4 * T.bundles.size();
+    d.dst = d.tiles + T.tiles.size();
+    d.rows = d.dst + T.dst.size();
+    set_launch(c->cfg.precision == MATVIS_FP64 ? P64 : P32, T, d);
     return MATVIS_OK;
 }
 
@@ -508,9 +515,8 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
     // reduction (on the 3.1M-pixel polarised sky one chunk instead of twelve was
     // 79.5 -> 71.7 ms per call of 8 instances).
     const bool over64 = prec == P64 && f64_over_sources(cfg->n_feed, cfg->n_ax, cfg->n_beam);
-    c->fused = (prec != P64 || over64) && !(cfg->flags & MATVIS_FLAG_UNFUSED);
-    // (FP64 keeps the chunk and the batch of a Z in device memory, which its
-    // sub-matrix product still writes.)
+    c->fused = !(cfg->flags & MATVIS_FLAG_UNFUSED);
+    // (FP64 keeps the chunk and the batch of a Z in device memory.)
     c->chunk = cfg->src_chunk > 0 ? std::min<int64_t>(cfg->src_chunk, cfg->max_src)
                                   : std::min<int64_t>(cfg->max_src, (int64_t)1 << (c->fused && prec != P64 ? 22 : 18));
     c->ldz = round_up((int64_t)cfg->n_ax * c->chunk, kColPad);
@@ -539,17 +545,17 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
     const bool over_sources = path == MATVIS_PATH_SOURCES, three_blocks = path == MATVIS_PATH_FUSED_BLOCKS;
     if (over_sources) c->Np = (int)round_up(c->N, 2 * c->st);  // whole blocks of 128 antennas x 2 feeds
     // the lower triangle's 16 x 16 tiles
-    const bool tiled = path == MATVIS_PATH_FUSED;
+    const bool tiled = path == MATVIS_PATH_FUSED || (c->fused && prec == P64 && !over64);
     Tiles tiles;
     if (tiled) {
-        c->full.coherent = cfg->n_feed == 2 && cfg->n_ax == 2 && cfg->n_beam == 1;
+        c->full.coherent = prec != P64 && cfg->n_feed == 2 && cfg->n_ax == 2 && cfg->n_beam == 1;
         try {
-            tiles = full_tiles(cfg->n_ant, cfg->n_feed, c->Np, c->full.coherent != 0);
+            tiles = full_tiles(prec, cfg->n_ant, cfg->n_feed, c->Np, c->full.coherent != 0);
         } catch (const std::bad_alloc &) {
             matvis_destroy(c);
             return MATVIS_ENOMEM;
         }
-        set_launch(tiles, c->full);
+        set_launch(prec, tiles, c->full);
     }
     c->ksplit = cfg->ksplit > 0 ? cfg->ksplit : default_ksplit(prec, path);
     c->max_splits = c->pair_splits = (int)((c->ldz + c->ksplit - 1) / c->ksplit);
@@ -791,7 +797,7 @@ matvis_status enqueue_simulate(matvis_ctx *c, const double *antpos, const int32_
                     ta.part = c->part;
                     ta.part_stride = (int64_t)c->Np * c->Np;
                     ta.ld = c->Np;
-                    STEP(c, MATVIS_STEP_HERK, s, launch_tiles(prec, ta, s));
+                    STEP(c, MATVIS_STEP_HERK, s, prec == P64 ? launch_tiles64(ta, s) : launch_tiles(prec, ta, s));
                 } else if (c->fused && !pairs) {
                     FusedArgs fa{};
                     fa.antc = c->antc;
@@ -848,11 +854,6 @@ matvis_status enqueue_simulate(matvis_ctx *c, const double *antpos, const int32_
                 if (!c->fused) {
                     STEP(c, MATVIS_STEP_ZFORM, s, launch_zform(prec, za, bt, s));
                     if (!pairs) STEP(c, MATVIS_STEP_HERK, s, launch_herk(prec, ha, s));
-                } else if (pairs && c->pr_Z) {
-                    // the pairs of a fused FP64 context (B already carries the sky)
-                    za.flux = nullptr;
-                    za.Z = c->pr_Z;
-                    STEP(c, MATVIS_STEP_ZFORM, s, launch_zform(prec, za, bt, s));
                 }
                 if (pairs) {
                     // App. A: only the planned sub-matrices, then the requested pairs
@@ -861,10 +862,10 @@ matvis_status enqueue_simulate(matvis_ctx *c, const double *antpos, const int32_
                         ta.part = c->pr_part;
                         ta.part_stride = (int64_t)c->pr_tiles * kTile * kTile;
                         ta.ld = kTile;
-                        STEP(c, MATVIS_STEP_HERK, s, launch_tiles(prec, ta, s));
+                        STEP(c, MATVIS_STEP_HERK, s, prec == P64 ? launch_tiles64(ta, s) : launch_tiles(prec, ta, s));
                     } else {
                         SubmatArgs sa{};
-                        sa.Z = c->fused ? c->pr_Z : c->Z;
+                        sa.Z = c->Z;
                         sa.Z_lo = c->Z_lo;
                         sa.ldz = c->ldz;
                         sa.inst_stride = (int64_t)c->Np * c->ldz;
@@ -1026,13 +1027,14 @@ matvis_status matvis_set_pairs(matvis_ctx *c, const int32_t *pair_a, const int32
         if (pair_a[u] < 0 || pair_a[u] >= g.n_ant || pair_b[u] < 0 || pair_b[u] >= g.n_ant)
             return fail(c, MATVIS_EINVAL, "pair antenna outside [0, n_ant)");
     const int nf = g.n_feed;
-    const bool in_lds = c->fused && g.precision != P64;  // else Z in device memory
+    const bool in_lds = c->fused;  // Z formed there, else in device memory
+    const int prec = g.precision == MATVIS_FP64 ? P64 : g.precision == MATVIS_FP32 ? P32 : PB3;
     int64_t size = 0;
     Tiles T;
     try {
         const red::Plan P = red::plan(pair_a, pair_b, n_pair, g.n_ant, n_sub);
         for (size_t x = 0; x < P.A.size(); x++) size += (int64_t)P.A[x].size() * P.B[x].size();
-        T = in_lds ? pair_tiles(pair_a, pair_b, n_pair, nf)
+        T = in_lds ? pair_tiles(prec, pair_a, pair_b, n_pair, nf)
                    : pair_submatrices(P, pair_a, pair_b, n_pair, g.n_ant, nf);
     } catch (const std::bad_alloc &) {
         return fail(c, MATVIS_ENOMEM, "host memory for the pair plan");
@@ -1048,8 +1050,7 @@ matvis_status matvis_set_pairs(matvis_ctx *c, const int32_t *pair_a, const int32
     for (auto &kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
     c->graphs.clear();
     c->graph_order.clear();
-    for (void *q : {(void *)c->pr_rows, (void *)c->pr_loc, c->pr_part, (void *)c->pr_vacc, c->pr_Z,
-                    (void *)c->pr_list.rows, (void *)c->pr_list.tiles, (void *)c->pr_list.dst,
+    for (void *q : {(void *)c->pr_rows, (void *)c->pr_loc, c->pr_part, (void *)c->pr_vacc,
                     (void *)c->pr_list.bundles}) {
         if (!q) continue;
         auto it = std::find(c->allocs.begin(), c->allocs.end(), q);
@@ -1059,7 +1060,6 @@ matvis_status matvis_set_pairs(matvis_ctx *c, const int32_t *pair_a, const int32
     c->pr_rows = c->pr_loc = nullptr;
     c->pr_part = nullptr;
     c->pr_vacc = nullptr;
-    c->pr_Z = nullptr;
     c->pr_list = DevTiles{};
     c->pr_set = false;
     matvis_status st;
@@ -1076,9 +1076,6 @@ matvis_status matvis_set_pairs(matvis_ctx *c, const int32_t *pair_a, const int32
         MATVIS_OK)
         return st;
     if ((st = dalloc(c, &c->pr_vacc, sizeof(double) * 2 * (size_t)B_cap * n_pair * nf * nf)) != MATVIS_OK) return st;
-    if (c->fused && g.precision == P64) {  // its batch is sized for a Z
-        if ((st = dalloc(c, &c->pr_Z, cbytes(g.precision) * (size_t)B_cap * c->Np * c->ldz)) != MATVIS_OK) return st;
-    }
     HIPCHK(c, hipMemcpy(c->pr_loc, loc.data(), sizeof(int32_t) * loc.size(), hipMemcpyHostToDevice));
     c->pr_n = n_pair;
     c->pr_tiles = n_tiles;

@@ -56,3 +56,21 @@ def test_scalar_fp32_bundles(n_ant, n_beam):
     say(f"scalar fp32, {n_ant} antennas: err_F={ef:.3e} err_CS={ec:.3e}")
     assert ef <= 2e-6 and ec <= 2e-6
     assert np.array_equal(V, np.conj(np.transpose(V, (0, 2, 1, 4, 3))))
+
+
+@pytest.mark.parametrize("workload,n_ant,n_beam,n_src", [
+    (1, 1, 1, 40), (1, 16, 1, 31), (1, 17, 1, 33), (1, 112, 1, 90), (1, 113, 1, 64), (1, 160, 2, 100), (1, 161, 1, 70),
+    (1, 256, 1, 120), (1, 300, 1, 90), (2, 8, 3, 100), (2, 41, 5, 40), (2, 100, 2, 60)])
+def test_fp64_tiles(workload, n_ant, n_beam, n_src):
+    import torch
+    wl = synth.workload(workload, n_ant=n_ant, n_src=n_src, n_time=2, n_freq=2)
+    say(f"tile lists fp64: workload {workload}, {n_ant} antennas, {n_beam} beams, {n_src} sources")
+    wl.beam = np.concatenate([wl.beam * (1 - 0.05 * b) * np.exp(0.3j * b) for b in range(n_beam)])
+    bidx = (np.arange(n_ant) * 7 % n_beam).astype(np.int32)
+    ref = oracle.simulate(wl.antpos, wl.freqs, wl.lsts, wl.ra, wl.dec, wl.flux, wl.beam, wl.latitude, wl.dza, wl.daz,
+                          wl.interp, beam_idx=bidx)
+    for kw in ({}, {"src_chunk": 64}):
+        V = gpu_simulate(wl, "fp64", beam_idx=torch.from_numpy(bidx).cuda(), **kw)
+        ef, ec = errors(V, ref)
+        say(f"  {kw}: err_F={ef:.3e} err_CS={ec:.3e}")
+        assert ef <= 1e-10 and ec <= 1e-10
