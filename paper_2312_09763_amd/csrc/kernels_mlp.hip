@@ -7,8 +7,8 @@
 // gradient, column sums for bias gradients, and Adam.
 //
 // Inference (k_mlp_infer) is one persistent launch: every workgroup holds
-// the bf16 hidden weights in LDS and each wave runs the whole network on 64
-// points at a time with the activations in registers, so only the inputs and
+// the bf16 hidden weights in LDS and each wave runs the whole network on 32
+// (or 16) points at a time with the activations in registers, so only the inputs and
 // the outputs touch HBM.  In the simulator it replaces beam interpolation:
 // it reads the visible sources' (za, az) of one time, evaluates the network
 // once, and writes B = sqrt(I) J of every channel of the batch (the
@@ -260,8 +260,8 @@ constexpr int kImgLayerBlocks = (kHid / 16) * (kHid / 32);   // 32 per layer 2..
 static_assert((int64_t)(kImgW1Blocks + 3 * kImgLayerBlocks) * kBlk == mlp::kWbElems, "image covers W1..W4");
 constexpr int kImgW5Blocks = (kNet / 16) * (kHid / 32) * 2;  // 32: (row tile, k block, hi / lo)
 static_assert((int64_t)kImgW5Blocks * kBlk == mlp::kW5Elems, "image covers W5 hi and lo");
-constexpr int kIPts = 64;    // points per wave task
-constexpr int kIWaves = 8;   // waves per workgroup (two per SIMD)
+// waves per workgroup: two per SIMD, four where a task's registers allow
+__host__ __device__ constexpr int infer_waves(int pt) { return pt == 1 ? 16 : 8; }
 
 // column of W (row 16 h + l16) at element e of lane (l16, lk) in k block kb
 __device__ __host__ inline int image_col(bool first, int kb, int lk, int e) {
@@ -311,16 +311,17 @@ __device__ inline bf16x8 lds_block(const __bf16 *img, int blk, int loff) {
 }
 
 // Hidden layer 2..4 (image blocks from blk0): out = SiLU(W in + b) as B operands.
-__device__ inline void hidden_layer(const __bf16 *img, int blk0, const float *__restrict__ b, const bf16x8 (&in)[4][4],
-                                    bf16x8 (&out)[4][4], int loff, int lk) {
+template <int PT>
+__device__ inline void hidden_layer(const __bf16 *img, int blk0, const float *__restrict__ b,
+                                    const bf16x8 (&in)[4][PT], bf16x8 (&out)[4][PT], int loff, int lk) {
 #pragma unroll
     for (int hh = 0; hh < 2; hh++) {
-        f32x4 acc[4][4];
+        f32x4 acc[4][PT];
 #pragma unroll
         for (int i = 0; i < 4; i++) {
             const f32x4 bv = *(const f32x4 *)(b + 16 * (4 * hh + i) + 4 * lk);
 #pragma unroll
-            for (int pt = 0; pt < 4; pt++) acc[i][pt] = bv;
+            for (int pt = 0; pt < PT; pt++) acc[i][pt] = bv;
         }
 #pragma unroll
         for (int kb = 0; kb < 4; kb++)
@@ -328,13 +329,13 @@ __device__ inline void hidden_layer(const __bf16 *img, int blk0, const float *__
             for (int i = 0; i < 4; i++) {
                 const bf16x8 w = lds_block(img, blk0 + (4 * hh + i) * 4 + kb, loff);
 #pragma unroll
-                for (int pt = 0; pt < 4; pt++)
+                for (int pt = 0; pt < PT; pt++)
                     acc[i][pt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, in[kb][pt], acc[i][pt], 0, 0, 0);
             }
 #pragma unroll
         for (int i = 0; i < 4; i++)
 #pragma unroll
-            for (int pt = 0; pt < 4; pt++)
+            for (int pt = 0; pt < PT; pt++)
 #pragma unroll
                 for (int e = 0; e < 4; e++) out[2 * hh + i / 2][pt][4 * (i % 2) + e] = (__bf16)silu_fast(acc[i][pt][e]);
     }
@@ -344,7 +345,7 @@ struct InferArgs {
     const float *P;        // FP32 parameters (Fourier matrix, biases)
     const __bf16 *Wb;      // image: bf16 W1..W4 (copied to LDS), then W5 hi / lo
     double nu0, nu1;
-    int64_t n_tasks;       // 64-point tasks
+    int64_t n_tasks;
     int64_t tiles;         // simulator mode: tasks per time of the batch
     // plain mode: x [n][3] normalised inputs, out [n][8]
     const float *x;
@@ -367,7 +368,8 @@ struct InferArgs {
 
 // J[p][0], J[p][1] (re, im each; p = lk, valid in lanes lk < 2) of point 16 pt + l16
 // from the head accumulators and this lane's four basis values Tl[e] = T_{4 (lk & 1) + e}.
-__device__ inline f32x4 basis_sum(const f32x4 (&D)[4][2], int pt, const float (&Tl)[4], int lk) {
+template <int HJ>
+__device__ inline f32x4 basis_sum(const f32x4 (&D)[4][HJ], int pt, const float (&Tl)[4], int lk) {
     float s[4];
 #pragma unroll
     for (int rt = 0; rt < 4; rt++) {
@@ -380,27 +382,29 @@ __device__ inline f32x4 basis_sum(const f32x4 (&D)[4][2], int pt, const float (&
     return f32x4{a, __shfl_xor(a, 32), b, __shfl_xor(b, 32)};
 }
 
-template <bool SIM>
-__global__ void __launch_bounds__(kIWaves * kWave) k_mlp_infer(InferArgs a) {
+// PT point tiles of 16 per task.
+template <bool SIM, int PT>
+__global__ void __launch_bounds__(infer_waves(PT) * kWave) k_mlp_infer(InferArgs a) {
     __shared__ __attribute__((aligned(16))) __bf16 img[mlp::kWbElems];
     const int tid = threadIdx.x, lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int l16 = lane & 15, lk = lane >> 4;
-    for (int i = tid; i < (int)(mlp::kWbElems / 8); i += kIWaves * kWave)
+    for (int i = tid; i < (int)(mlp::kWbElems / 8); i += infer_waves(PT) * kWave)
         ((u32x4 *)img)[i] = ((const u32x4 *)a.Wb)[i];
     __syncthreads();
-    const int64_t nw = (int64_t)gridDim.x * kIWaves;
+    constexpr int IPTS = 16 * PT, HJ = PT < 2 ? 1 : 2;  // points of a task, point tiles of the head at a time
+    const int64_t nw = (int64_t)gridDim.x * infer_waves(PT);
 #pragma unroll 1
-    for (int64_t t = (int64_t)blockIdx.x * kIWaves + wave; t < a.n_tasks; t += nw) {
+    for (int64_t t = (int64_t)wave * gridDim.x + blockIdx.x; t < a.n_tasks; t += nw) {
         int slot = 0;
         int64_t m0, nrow;
-        if (SIM) {  // 64 visible sources of one time of the batch, every channel
+        if (SIM) {  // visible sources of one time of the batch, every channel
             slot = (int)(t / a.tiles);
-            m0 = (t % a.tiles) * kIPts;
+            m0 = (t % a.tiles) * IPTS;
             nrow = a.count[slot];
             if (m0 >= nrow) continue;
         } else {
-            m0 = t * kIPts;
+            m0 = t * IPTS;
             nrow = a.n;
         }
         // Parameters are re-read per task through L1: hoisted out of the loop
@@ -413,10 +417,10 @@ __global__ void __launch_bounds__(kIWaves * kWave) k_mlp_infer(InferArgs a) {
         asm volatile("" : "+v"(loff));
         const __bf16 *w5 = a.Wb + mlp::kWbElems;
         asm volatile("" : "+s"(w5));
-        // inputs of this lane's four points (16 pt + l16)
-        float xu[4], xv[4], xw[4];
+        // inputs of this lane's points (16 pt + l16)
+        float xu[PT], xv[PT], xw[PT];
 #pragma unroll
-        for (int pt = 0; pt < 4; pt++) {
+        for (int pt = 0; pt < PT; pt++) {
             const int64_t m = m0 + 16 * pt + l16;
             xu[pt] = xv[pt] = xw[pt] = 0.f;
             if (m < nrow) {
@@ -433,12 +437,12 @@ __global__ void __launch_bounds__(kIWaves * kWave) k_mlp_infer(InferArgs a) {
             }
         }
         // layer 1: features formed per k block (sin in kb, cos in kb + 4)
-        f32x4 acc1[8][4];
+        f32x4 acc1[8][PT];
 #pragma unroll
         for (int h = 0; h < 8; h++) {
             const f32x4 bv = *(const f32x4 *)(P + kOffB1 + 16 * h + 4 * lk);
 #pragma unroll
-            for (int pt = 0; pt < 4; pt++) acc1[h][pt] = bv;
+            for (int pt = 0; pt < PT; pt++) acc1[h][pt] = bv;
         }
 #pragma unroll 1
         for (int kb = 0; kb < 4; kb++) {
@@ -452,9 +456,9 @@ __global__ void __launch_bounds__(kIWaves * kWave) k_mlp_infer(InferArgs a) {
                 bf[4 * q + 2] = v[2];
                 bf[4 * q + 3] = v[3];
             }
-            bf16x8 S[4], C[4];
+            bf16x8 S[PT], C[PT];
 #pragma unroll
-            for (int pt = 0; pt < 4; pt++)
+            for (int pt = 0; pt < PT; pt++)
 #pragma unroll
                 for (int e = 0; e < 8; e++) {
                     float s, c;
@@ -466,32 +470,32 @@ __global__ void __launch_bounds__(kIWaves * kWave) k_mlp_infer(InferArgs a) {
             for (int h = 0; h < 8; h++) {
                 const bf16x8 ws = lds_block(img, h * 8 + kb, loff), wc = lds_block(img, h * 8 + kb + 4, loff);
 #pragma unroll
-                for (int pt = 0; pt < 4; pt++) {
+                for (int pt = 0; pt < PT; pt++) {
                     acc1[h][pt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ws, S[pt], acc1[h][pt], 0, 0, 0);
                     acc1[h][pt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wc, C[pt], acc1[h][pt], 0, 0, 0);
                 }
             }
         }
-        bf16x8 hA[4][4], hB[4][4];
+        bf16x8 hA[4][PT], hB[4][PT];
 #pragma unroll
         for (int h = 0; h < 8; h++)
 #pragma unroll
-            for (int pt = 0; pt < 4; pt++)
+            for (int pt = 0; pt < PT; pt++)
 #pragma unroll
                 for (int e = 0; e < 4; e++) hA[h / 2][pt][4 * (h % 2) + e] = (__bf16)silu_fast(acc1[h][pt][e]);
         hidden_layer(img, kImgW1Blocks, P + kOffB2, hA, hB, loff, lk);
         hidden_layer(img, kImgW1Blocks + kImgLayerBlocks, P + kOffB3, hB, hA, loff, lk);
-        // Layer 4, the head and the outputs for two point tiles at a time (points
-        // 16 (2 pp + j) + l16, j < 2), which keeps the head's accumulators in registers.
+        // Layer 4, the head and the outputs for HJ point tiles at a time (points
+        // 16 (HJ pp + j) + l16, j < HJ), which keeps the head's accumulators in registers.
         const int blk4 = kImgW1Blocks + 2 * kImgLayerBlocks;
 #pragma unroll
-        for (int pp = 0; pp < 2; pp++) {
-            f32x4 acc[8][2];
+        for (int pp = 0; pp < PT / HJ; pp++) {
+            f32x4 acc[8][HJ];
 #pragma unroll
             for (int i = 0; i < 8; i++) {
                 const f32x4 bv = *(const f32x4 *)(P + kOffB4 + 16 * i + 4 * lk);
 #pragma unroll
-                for (int j = 0; j < 2; j++) acc[i][j] = bv;
+                for (int j = 0; j < HJ; j++) acc[i][j] = bv;
             }
 #pragma unroll
             for (int kb = 0; kb < 4; kb++)
@@ -499,21 +503,21 @@ __global__ void __launch_bounds__(kIWaves * kWave) k_mlp_infer(InferArgs a) {
                 for (int i = 0; i < 8; i++) {
                     const bf16x8 w = lds_block(img, blk4 + i * 4 + kb, loff);
 #pragma unroll
-                    for (int j = 0; j < 2; j++)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, hA[kb][2 * pp + j], acc[i][j], 0, 0, 0);
+                    for (int j = 0; j < HJ; j++)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, hA[kb][HJ * pp + j], acc[i][j], 0, 0, 0);
                 }
-            f32x4 D[4][2];
+            f32x4 D[4][HJ];
 #pragma unroll
             for (int rt = 0; rt < 4; rt++) {
                 const f32x4 b5 = *(const f32x4 *)(P + kOffB5 + 16 * rt + 4 * lk);
 #pragma unroll
-                for (int j = 0; j < 2; j++) D[rt][j] = b5;
+                for (int j = 0; j < HJ; j++) D[rt][j] = b5;
             }
 #pragma unroll
             for (int kb = 0; kb < 4; kb++) {  // head k block kb: unit tiles 2 kb, 2 kb + 1 after SiLU
-                bf16x8 sh[2], sl[2];
+                bf16x8 sh[HJ], sl[HJ];
 #pragma unroll
-                for (int j = 0; j < 2; j++)
+                for (int j = 0; j < HJ; j++)
 #pragma unroll
                     for (int e = 0; e < 8; e++) {
                         const float v = silu_fast(acc[2 * kb + e / 4][j][e % 4]);
@@ -526,7 +530,7 @@ __global__ void __launch_bounds__(kIWaves * kWave) k_mlp_infer(InferArgs a) {
                     const bf16x8 wh = *(const bf16x8 *)(w5 + ((rt * 4 + kb) * 2) * kBlk + lane * 8);
                     const bf16x8 wl = *(const bf16x8 *)(w5 + ((rt * 4 + kb) * 2 + 1) * kBlk + lane * 8);
 #pragma unroll
-                    for (int j = 0; j < 2; j++) {
+                    for (int j = 0; j < HJ; j++) {
                         D[rt][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wh, sh[j], D[rt][j], 0, 0, 0);
                         D[rt][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wh, sl[j], D[rt][j], 0, 0, 0);
                         D[rt][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wl, sh[j], D[rt][j], 0, 0, 0);
@@ -536,10 +540,10 @@ __global__ void __launch_bounds__(kIWaves * kWave) k_mlp_infer(InferArgs a) {
             if (!SIM) {
                 // each point at its own frequency
 #pragma unroll
-                for (int j = 0; j < 2; j++) {
-                    const int pt = 2 * pp + j;
+                for (int j = 0; j < HJ; j++) {
+                    const int pt = HJ * pp + j;
                     float T[kBasis], Tl[4];
-                    chebyshev(2.0f * xw[2 * pp + j] - 1.0f, T);
+                    chebyshev(2.0f * xw[HJ * pp + j] - 1.0f, T);
 #pragma unroll
                     for (int e = 0; e < 4; e++) Tl[e] = (lk & 1) ? T[4 + e] : T[e];
                     const f32x4 J = basis_sum(D, j, Tl, lk);
@@ -557,9 +561,9 @@ __global__ void __launch_bounds__(kIWaves * kWave) k_mlp_infer(InferArgs a) {
 #pragma unroll
                 for (int e = 0; e < 4; e++) Tl[e] = (lk & 1) ? T[4 + e] : T[e];
 #pragma unroll
-                for (int j = 0; j < 2; j++) {
+                for (int j = 0; j < HJ; j++) {
                     f32x4 J = basis_sum(D, j, Tl, lk);  // (re, im) of J[lk][0], J[lk][1]
-                    const int64_t m = m0 + 16 * (2 * pp + j) + l16;
+                    const int64_t m = m0 + 16 * (HJ * pp + j) + l16;
                     if (lk >= 2 || m >= nrow) continue;
                     float sq = 1.0f;
                     if (a.idx) {
@@ -590,7 +594,7 @@ __global__ void __launch_bounds__(kIWaves * kWave) k_mlp_infer(InferArgs a) {
     }
 }
 
-int infer_grid(int64_t n_tasks) {
+int infer_cus() {
     static int n_cu = 0;
     if (n_cu == 0) {
         int dev = 0;
@@ -598,7 +602,25 @@ int infer_grid(int64_t n_tasks) {
             hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
             n_cu = 256;
     }
-    return (int)std::min<int64_t>(n_cu, (n_tasks + kIWaves - 1) / kIWaves);
+    return n_cu;
+}
+
+// Point tiles per task.  A task is a serial chain (about 15 us for 16 points, 20 for 32, 33
+// for 64, alone on its SIMD), and waves side by side hide it better than longer tasks do:
+// calls of 1000 / 32 768 / 100 000 / 200 000 points take 36 / 40 / 58 / 85 us on 16-point tasks
+// with four waves a SIMD, 42 / 44 / 63 / 85 on 32-point ones with two and 56 / 56 / 65 / 99
+// on 64-point ones; past that the weights, read from LDS once per task, count: 111 / 305 us
+// at 300 000 / 1 000 000 points against 114 / 292 and 109 / 306.
+int infer_tiles(int64_t points) { return points <= (1 << 18) ? 1 : 2; }
+
+template <bool SIM>
+hipError_t launch_infer(const InferArgs &a, int pt, hipStream_t s) {
+    const int grid = (int)std::min<int64_t>(infer_cus(), a.n_tasks);  // a task on every CU before a second on one
+    if (pt == 2)
+        k_mlp_infer<SIM, 2><<<grid, infer_waves(2) * kWave, 0, s>>>(a);
+    else
+        k_mlp_infer<SIM, 1><<<grid, infer_waves(1) * kWave, 0, s>>>(a);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -709,9 +731,9 @@ hipError_t infer_plain(const float *P, const __bf16 *Wb, const float *x, int64_t
     a.x = x;
     a.out = out;
     a.n = n;
-    a.n_tasks = (n + kIPts - 1) / kIPts;
-    k_mlp_infer<false><<<infer_grid(a.n_tasks), kIWaves * kWave, 0, s>>>(a);
-    return hipGetLastError();
+    const int pt = infer_tiles(n);
+    a.n_tasks = (n + 16 * pt - 1) / (16 * pt);
+    return launch_infer<false>(a, pt, s);
 }
 
 hipError_t infer_sim(const float *P, const __bf16 *Wb, double nu0, double nu1, const double *za_az,
@@ -740,10 +762,10 @@ hipError_t infer_sim(const float *P, const __bf16 *Wb, double nu0, double nu1, c
     a.beam = beam;
     a.n_beam = n_beam;
     a.bt = bt;
-    a.tiles = (max_m + kIPts - 1) / kIPts;
-    a.n_tasks = a.tiles * bt.ntb;  // one task per 64 sources of one time: every channel of the batch
-    k_mlp_infer<true><<<infer_grid(a.n_tasks), kIWaves * kWave, 0, s>>>(a);
-    return hipGetLastError();
+    const int pt = infer_tiles(max_m * bt.ntb);
+    a.tiles = (max_m + 16 * pt - 1) / (16 * pt);
+    a.n_tasks = a.tiles * bt.ntb;  // a task is some sources of one time: every channel of the batch
+    return launch_infer<true>(a, pt, s);
 }
 
 }  // namespace mlp

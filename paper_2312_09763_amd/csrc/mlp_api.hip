@@ -211,6 +211,47 @@ static hipError_t noalloc_scratch(float **p) {
     return hipSuccess;
 }
 
+// Weight images of forward calls in flight: a few static slots per device (module memory),
+// taken for the length of a call, which ends after its stream is done with them; a call
+// that finds none free allocates, which costs some 10 us more.
+constexpr int kImgSlots = 4;
+static __device__ __attribute__((aligned(16))) __bf16 forward_images[kImgSlots][mlp::kImgElems];
+static unsigned img_busy[kMaxDevices] = {};
+
+struct ForwardImage {
+    __bf16 *p = nullptr;
+    int dev = -1, slot = -1;
+    hipError_t take() {
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        if (dev >= 0 && dev < kMaxDevices) {
+            std::lock_guard<std::mutex> lock(noalloc_mu);
+            for (int i = 0; i < kImgSlots && slot < 0; i++)
+                if (!(img_busy[dev] >> i & 1)) slot = i;
+            if (slot >= 0) {
+                void *q = nullptr;
+                e = hipGetSymbolAddress(&q, HIP_SYMBOL(forward_images));
+                if (e != hipSuccess) {
+                    slot = -1;
+                    return e;
+                }
+                img_busy[dev] |= 1u << slot;
+                p = (__bf16 *)q + (size_t)slot * mlp::kImgElems;
+                return hipSuccess;
+            }
+        }
+        return hipMalloc(&p, sizeof(__bf16) * mlp::kImgElems);
+    }
+    ~ForwardImage() {
+        if (slot < 0) {
+            if (p) (void)hipFree(p);
+            return;
+        }
+        std::lock_guard<std::mutex> lock(noalloc_mu);
+        img_busy[dev] &= ~(1u << slot);
+    }
+};
+
 extern "C" {
 
 matvis_status matvis_mlp_forward(const float *params, const float *x, int64_t n, float *out, void *stream) {
@@ -218,13 +259,13 @@ matvis_status matvis_mlp_forward(const float *params, const float *x, int64_t n,
     if ((uintptr_t)params % 16 || (uintptr_t)out % 16) return MATVIS_EINVAL;  // read / written as float4
     if (n == 0) return MATVIS_OK;
     hipStream_t s = (hipStream_t)stream;
-    __bf16 *wb = nullptr;
-    CK(hipMalloc(&wb, sizeof(__bf16) * mlp::kImgElems));
-    hipError_t e = mlp::pack_weights(params, wb, s);
-    if (e == hipSuccess) e = mlp::infer_plain(params, wb, x, n, out, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    (void)hipFree(wb);
+    ForwardImage img;
+    CK(img.take());
+    hipError_t e = mlp::pack_weights(params, img.p, s);
+    if (e == hipSuccess) e = mlp::infer_plain(params, img.p, x, n, out, s);
+    const hipError_t sync = hipStreamSynchronize(s);  // the image is given back after this, also on an error
     CK(e);
+    CK(sync);
     return MATVIS_OK;
 }
 
