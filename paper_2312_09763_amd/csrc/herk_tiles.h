@@ -1,5 +1,5 @@
 // Tile geometry shared by the product kernels that form Z in LDS
-// (kernels_herk_fused.hip, kernels_herk_x6.hip, kernels_pairs.hip).
+// (kernels_herk_fused.hip, kernels_herk_x6.hip, kernels_tiles.hip).
 #pragma once
 
 #include "internal.h"

@@ -1,4 +1,4 @@
-"""The requested pairs' tiles formed in LDS (kernels_pairs.hip) at their edges: one pair, rows around a
+"""The requested pairs' tiles formed in LDS (kernels_tiles.hip) at their edges: one pair, rows around a
 block of 16, more tiles than one workgroup takes, more blocks than it stages, either order of a pair,
 autocorrelations, one and two feeds, beams per antenna, columns around a stage, and fewer columns
 than k-splits."""
