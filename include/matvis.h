@@ -385,7 +385,8 @@ matvis_status matvis_profile_read(matvis_ctx *ctx, double *ms, int64_t *launches
  *                          first, V[(a,p),(b,q)] = sum_m F_a conj(F_b) C_pq(m),
  *                          so the product runs over sources, not over the
  *                          (source, axis) columns of Z -- half the
- *                          multiply-adds for the same V;
+ *                          multiply-adds for the same V (FP32 up to 80
+ *                          antennas: in the 16 x 16 tiles of _FUSED);
  *   MATVIS_PATH_FUSED_BLOCKS one feed, one axis, one shared beam, 257..384
  *                          antennas (BF16X3 or FP32): three items per
  *                          (instance, k-split), each a diagonal triangle with

@@ -544,8 +544,13 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
                          : MATVIS_PATH_Z_IN_HBM;
     const bool over_sources = path == MATVIS_PATH_SOURCES, three_blocks = path == MATVIS_PATH_FUSED_BLOCKS;
     if (over_sources) c->Np = (int)round_up(c->N, 2 * c->st);  // whole blocks of 128 antennas x 2 feeds
-    // the lower triangle's 16 x 16 tiles
-    const bool tiled = path == MATVIS_PATH_FUSED || (c->fused && prec == P64 && !over64);
+    // The lower triangle's 16 x 16 tiles.  Over sources they are also the better for FP32 up
+    // to five blocks of antennas, where whole tile rows of the 96 or 128 antennas of the
+    // larger kernels would be padding: 66 / 80 / 96 antennas, 100 000 sources, 32 instances
+    // 1.17 / 1.20 / 1.52 ms in tiles, 1.34 / 1.35 / 1.38 ms in blocks (BF16X3 0.95 against
+    // 0.79 ms at 66).
+    const bool tiled = path == MATVIS_PATH_FUSED || (c->fused && prec == P64 && !over64) ||
+                       (over_sources && prec == P32 && cfg->n_ant <= 80);
     Tiles tiles;
     if (tiled) {
         c->full.coherent = prec != P64 && cfg->n_feed == 2 && cfg->n_ax == 2 && cfg->n_beam == 1;
