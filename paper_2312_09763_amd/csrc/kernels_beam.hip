@@ -3,7 +3,10 @@
 // beam_interp.h.  One thread per (visible source, instance); the taps are read
 // through the L2 / MALL (a 0.5 deg polarised channel is 4.2 MB in complex64).
 // When the product forms Z itself, the output is B = sqrt(I) A.
+#include <algorithm>
+
 #include "beam_interp.h"
+#include "launch_rules.h"
 
 namespace mv {
 
@@ -168,14 +171,6 @@ __global__ void __launch_bounds__(256) k_stencil(InterpArgs a, Batch bt) {
     }
 }
 
-// Beams that one block of k_interp_tf evaluates its sources on.
-constexpr int kBeamGroup = 4;
-
-// Blocks of `spb` sources that one XCD may have to do of a slot with up to max_m.
-__host__ __device__ inline int64_t tf_blocks_per_xcd(int64_t max_m, int spb) {
-    return ((max_m + spb - 1) / spb + 7) / 8;
-}
-
 // A group of LPS lanes per (visible source, time slot of the batch, FG channels
 // of the batch): a tap's interleaved run T[b][j][k][f .. f + FG - 1][0 .. ncomp) is
 // FG ncomp complex values, and lane l of the group reads its l-th 16-byte piece
@@ -192,26 +187,25 @@ __host__ __device__ inline int64_t tf_blocks_per_xcd(int64_t max_m, int spb) {
 // groups of 4 beams (16: 1.11, 8: 1.03, 2: 1.05), which is 4.1 GB at 4.0 TB/s.  More
 // waves in flight (fewer registers, by launch bounds) were slower: 1.71 against 1.45 ms.
 template <typename R, int MODE, int NCOMP, bool ST, int FG>
-__global__ void __launch_bounds__(256) k_interp_tf(InterpArgs a, Batch bt) {
+__global__ void __launch_bounds__(256) k_interp_tf(InterpArgs a, Batch bt, uint32_t z0) {
     typedef typename CplxOf<R>::T C;
     constexpr int PER = 16 / sizeof(C);              // complex values per lane (16 bytes)
     constexpr int LPS = FG * NCOMP / PER;            // lanes per source
-    // XCD-aware block order: workgroups go to the 8 XCDs round-robin by linear id,
-    // and each XCD is given one contiguous eighth of every slot's visible sources;
+    // XCD-aware block order: workgroups go to the 8 XCDs round-robin by linear id (gridDim.x
+    // is a multiple of 8), and each XCD is given one contiguous eighth of every slot's visible sources;
     // neighbouring (sky-cell ordered) sources then share one L2 and the grid lines
     // they have in common are fetched into it once, and the XCDs have equal work
     // however many of the sources are up.  Groups of beams go outermost, so that the
     // slots read a beam's grid from the MALL after its first.
     const uint32_t i = blockIdx.x / 8, xcd = blockIdx.x % 8;
-    const uint32_t per = (uint32_t)tf_blocks_per_xcd(a.max_m, blockDim.x / LPS);
-    const int slot = (int)(i / per % (uint32_t)bt.ntb);
-    const uint32_t j = i / per / (uint32_t)bt.ntb;
+    const int slot = blockIdx.y;
+    const uint32_t j = z0 + blockIdx.z;
     const uint32_t ngf = (uint32_t)(bt.nfb + FG - 1) / FG;
     const int fg = (int)(j % ngf) * FG;  // first channel of the group, relative to the batch
     const int b0 = (int)(j / ngf) * kBeamGroup, b1 = b0 + kBeamGroup < a.n_beam ? b0 + kBeamGroup : a.n_beam;
     const int64_t M = a.count ? a.count[slot] : a.fixed_count;
     const int64_t nb = (M + blockDim.x / LPS - 1) / (blockDim.x / LPS);  // blocks of this slot
-    const int64_t bx = nb * xcd / 8 + i % per;
+    const int64_t bx = nb * xcd / 8 + i;
     if (bx >= nb * (xcd + 1) / 8) return;
     const int l = threadIdx.x % LPS;
     const int64_t m = bx * (blockDim.x / LPS) + threadIdx.x / LPS;
@@ -327,15 +321,16 @@ template <typename R, int MODE, bool ST, int FG>
 void launch_tf_fg(const InterpArgs &a, const Batch &bt, hipStream_t s) {
     const int ncomp = a.n_feed * a.n_ax;
     const int lps = FG * ncomp * (int)sizeof(typename CplxOf<R>::T) / 16;  // lanes per source
-    const int sources_per_block = 256 / lps;
-    const dim3 g((unsigned)(8 * tf_blocks_per_xcd(a.max_m, sources_per_block) * bt.ntb * ((bt.nfb + FG - 1) / FG) *
-                          ((a.n_beam + kBeamGroup - 1) / kBeamGroup)));
-    if (ncomp == 4)
-        k_interp_tf<R, MODE, 4, ST, FG><<<g, 256, 0, s>>>(a, bt);
-    else if (ncomp == 2)
-        k_interp_tf<R, MODE, 2, ST, FG><<<g, 256, 0, s>>>(a, bt);
-    else
-        k_interp_tf<R, MODE, 1, ST, FG><<<g, 256, 0, s>>>(a, bt);
+    const TfGrid n = tf_grid(a.max_m, 256 / lps, bt.ntb, bt.nfb, FG, a.n_beam);
+    for (int64_t z0 = 0; z0 < n.z; z0 += kMaxGridYZ) {
+        const dim3 g((unsigned)n.x, (unsigned)n.y, (unsigned)std::min(n.z - z0, kMaxGridYZ));
+        if (ncomp == 4)
+            k_interp_tf<R, MODE, 4, ST, FG><<<g, 256, 0, s>>>(a, bt, (uint32_t)z0);
+        else if (ncomp == 2)
+            k_interp_tf<R, MODE, 2, ST, FG><<<g, 256, 0, s>>>(a, bt, (uint32_t)z0);
+        else
+            k_interp_tf<R, MODE, 1, ST, FG><<<g, 256, 0, s>>>(a, bt, (uint32_t)z0);
+    }
 }
 
 template <typename R, int MODE>

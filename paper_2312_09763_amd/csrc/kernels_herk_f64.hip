@@ -25,8 +25,10 @@
 // MFMAs busy 65 % at 2.16 GHz) where writing Z took 2.1 ms and Z Z^H 4.3 ms; 4 antennas
 // 351 against 656 us for the whole call, 33 antennas 649 against 1929 us, 200 antennas
 // and 3000 sources 320 against 488 us, so every such context takes it.
-#include "internal.h"
 #include <type_traits>
+
+#include "internal.h"
+#include "launch_rules.h"
 
 namespace mv {
 
@@ -539,7 +541,7 @@ int tile64_waves(int n_rows, int n_tiles) {
 hipError_t launch_tiles64(const TileArgs &a, hipStream_t s) {
     const int64_t items = (int64_t)a.n_inst * a.n_bundle * a.n_split;
     if (items <= 0) return hipSuccess;
-    if (items > 0x7fffffff || a.n_feed > 2 || a.n_ax > 2 || a.coherent) return hipErrorInvalidValue;
+    if (items * 64 * a.waves >= kMaxThreadsX || a.n_feed > 2 || a.n_ax > 2 || a.coherent) return hipErrorInvalidValue;
     if (a.waves == 4)
         k_tiles64<4><<<(unsigned)items, 256, 0, s>>>(a);
     else if (a.waves == 8)

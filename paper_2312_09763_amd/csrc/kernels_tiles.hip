@@ -40,6 +40,7 @@
 #include <type_traits>
 
 #include "herk_tiles.h"
+#include "launch_rules.h"
 #include "matvis.h"
 
 namespace mv {
@@ -341,7 +342,7 @@ int tile_waves(int n_rows, int n_tiles) {
 hipError_t launch_tiles(int prec, const TileArgs &a, hipStream_t s) {
     const int64_t items = (int64_t)a.n_inst * a.n_bundle * a.n_split;
     if (items <= 0) return hipSuccess;
-    if (items > 0x7fffffff || a.n_feed > 2 || a.n_ax > 2) return hipErrorInvalidValue;
+    if (items * 64 * a.waves >= kMaxThreadsX || a.n_feed > 2 || a.n_ax > 2) return hipErrorInvalidValue;
     if (a.coherent && (a.n_feed != 2 || a.n_ax != 2 || a.n_beam != 1)) return hipErrorInvalidValue;
     auto launch = [&](auto waves) {
         constexpr int W = decltype(waves)::value;
