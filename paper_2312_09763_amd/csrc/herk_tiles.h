@@ -8,7 +8,7 @@ namespace mv {
 
 namespace {
 
-constexpr int kST = 128;  // antennas (or rows) per block
+constexpr int kST = kAntBlock;  // antennas (or rows) per block
 constexpr int kTI = 4;    // 16 x 16 tiles per side of a square wave tile
 
 __device__ inline int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }

@@ -8,6 +8,8 @@
 #include <cstdint>
 #include <vector>
 
+#include "launch_rules.h"
+
 namespace mv {
 
 constexpr double kSpeedOfLight = 299792458.0;  // m/s
@@ -213,15 +215,14 @@ struct HerkArgs {
     int32_t *work;           // [n_inst + 1] item prefix
     int32_t *nsplit;         // [n_inst] k-splits of each instance (built with work)
     int32_t *kcols;          // [n_inst] columns per k-split of each instance (a multiple of 64)
-    int32_t balance_grid;    // > 0: add k-splits so the items fill whole waves of this many workgroups
-    int32_t n_bal;           // items per k-split of the launch that is balanced
-    int32_t min_cols;        // columns that a k-split keeps at least when splits are added
+    SplitRule rule;          // of the k-splits that are added (grid 0: none)
     int32_t grid;            // persistent grid size (multiple of 8)
 };
 int herk_super_tile(int prec);
 int herk_occupancy(int prec);  // resident workgroups per CU
 // Item prefix over the batch (k_worklist), then the persistent product kernel.
-// unit != 0 counts k-splits only (the fused product multiplies by its item kinds).
+// unit != 0 counts k-splits only (the fused product multiplies by its item kinds).  Of
+// a.rule, ksplit, max_splits and n_st are set from a.
 // Instance i gets nsplit[i] k-splits of kcols[i] <= ksplit columns (the last
 // one partial); without balancing that is ceil(K_i / ksplit) of ksplit.
 hipError_t launch_worklist(int prec, const HerkArgs &a, int unit, hipStream_t s);

@@ -72,61 +72,78 @@ __device__ inline int64_t inst_k(const int32_t *count, int64_t fixed_k, int n_ax
     return count ? (int64_t)n_ax * count[i / nfb] : fixed_k;
 }
 
-// k-splits per instance and the item prefix.  nsplit_i starts at
-// ceil(K_i / ksplit); with balancing, extra splits are spread over the
-// instances until the items of the launch (n_bal per split) fill whole waves of
-// the persistent grid (capped by max_splits and by min_cols columns per split),
-// and each instance's splits are made equal:
-// kcols_i = 64 ceil(K_i / (64 nsplit_i)).  Every workgroup then takes the same
-// number of items of nearly the same size, and a call of few or small instances
-// still reaches every CU: 15 instances of 20 000 columns at 91 antennas made 75
-// items for 256 CUs and took 711 us on FP32, 255 items take 241 us; 8 instances
-// of 1000 columns on FP64 made 8 items of 63 serial stages, 134 us, and as 128
-// items take 29 us; 16 instances of 50 000 columns and 256 rows on FP64 filled
-// 2.2 of 3 waves of the grid, 6.26 ms, and fill 3 of 3 in 4.34 ms.  With several launches of different item counts
-// per split (unit mode, n_st = 1) the splits themselves are rounded once there
-// is a grid's worth of them, which suits every launch.
-__global__ void __launch_bounds__(1024) k_worklist(const int32_t *count, int64_t fixed_k, int n_ax, int nfb, int n_inst,
-                                                   int64_t ksplit, int n_st, int balance_grid, int n_bal, int min_cols,
-                                                   int max_splits, int32_t *work, int32_t *nsplit, int32_t *kcols) {
-    __shared__ int wtot[1024 / kWave];
-    __shared__ int carry_s, total_s;
-    if (threadIdx.x == 0) {
-        carry_s = 0;
-        total_s = 0;
+// A wave as plan_splits wants it.  Reductions by DPP, within rows of 16 and then from row to
+// row, into lane 63: a sixth of the time of shuffles through LDS, which count in a kernel of
+// a few microseconds.
+struct WaveGroup {
+    int id;
+    static constexpr int size = kWave;
+    template <int CTRL, int ROWS, typename F>
+    static __device__ int64_t step(int64_t v, int64_t none, F f) {
+        const int lo = __builtin_amdgcn_update_dpp((int)none, (int)v, CTRL, ROWS, 0xf, false);
+        const int hi = __builtin_amdgcn_update_dpp((int)(none >> 32), (int)(v >> 32), CTRL, ROWS, 0xf, false);
+        return f(v, (int64_t)((uint64_t)(uint32_t)hi << 32 | (uint32_t)lo));
     }
+    template <typename F>
+    static __device__ int64_t reduce(int64_t v, int64_t none, F f) {
+        v = step<0x111, 0xf>(v, none, f);  // row_shr:1, 2, 4, 8
+        v = step<0x112, 0xf>(v, none, f);
+        v = step<0x114, 0xf>(v, none, f);
+        v = step<0x118, 0xf>(v, none, f);
+        v = step<0x142, 0xa>(v, none, f);  // row_bcast:15 into rows 1 and 3
+        v = step<0x143, 0xc>(v, none, f);  // row_bcast:31 into rows 2 and 3
+        const uint32_t lo = __builtin_amdgcn_readlane((int)v, kWave - 1);
+        const uint32_t hi = __builtin_amdgcn_readlane((int)(v >> 32), kWave - 1);
+        return (int64_t)((uint64_t)hi << 32 | lo);
+    }
+    __device__ int64_t sum(int64_t v) {
+        return reduce(v, 0, [](int64_t a, int64_t b) { return a + b; });
+    }
+    __device__ int64_t max(int64_t v) {
+        return reduce(v, 0, [](int64_t a, int64_t b) { return a > b ? a : b; });
+    }
+    __device__ int64_t min(int64_t v) {
+        return reduce(v, INT64_MAX, [](int64_t a, int64_t b) { return a < b ? a : b; });
+    }
+};
+
+// k-splits per instance (the rule is plan_splits) and the item prefix.  Every workgroup
+// then takes the same number of items of nearly the same size, and a call of few or
+// small instances still reaches every CU: 15 instances of 20 000 columns at 91 antennas
+// made 75 items for 256 CUs and took 711 us on FP32, 255 items take 241 us; 16 instances of
+// 50 000 columns and 256 rows on FP64 with Z in memory filled 2.2 of 3 waves of the grid,
+// 6.26 ms, and fill 3 of 3 in 4.34 ms.
+__global__ void __launch_bounds__(1024) k_worklist(const int32_t *count, int64_t fixed_k, int n_ax, int nfb, int n_inst,
+                                                   SplitRule rule, int32_t *work, int32_t *nsplit, int32_t *kcols) {
+    __shared__ int wtot[1024 / kWave];
+    __shared__ int carry_s;
+    constexpr int kSlots = 256;
+    __shared__ int32_t seen[kSlots];  // visible counts, where the slots fit
+    __shared__ SplitPlan plan_s;
+    const int n_slot = n_inst / nfb;
+    const bool local = count && n_slot <= kSlots;
+    if (threadIdx.x == 0) carry_s = 0;
+    if (local && (int)threadIdx.x < n_slot) seen[threadIdx.x] = count[threadIdx.x];
     __syncthreads();
     const int lane = lane_id(), w = threadIdx.x / kWave;
-    int extra_all = 0;
-    if (balance_grid > 0) {
-        int part = 0;
-        for (int i = threadIdx.x; i < n_inst; i += 1024) {
-            const int64_t k = inst_k(count, fixed_k, n_ax, nfb, i);
-            part += (int)((k + ksplit - 1) / ksplit);
-        }
-        atomicAdd(&total_s, part);
-        __syncthreads();
-        const int t = total_s;
-        const int64_t n = n_st == 1 && t >= balance_grid ? 1 : n_bal;
-        const int64_t waves = (t * n + balance_grid - 1) / balance_grid;
-        extra_all = (int)max<int64_t>(waves * balance_grid / n - t, 0);
+    auto cols = [&](int slot) {
+        return local ? (int64_t)n_ax * seen[slot] : inst_k(count, fixed_k, n_ax, 1, slot);
+    };
+    if (w == 0) {
+        WaveGroup group{lane};
+        const SplitPlan p = plan_splits(rule, n_slot, nfb, cols, group);
+        if (lane == 0) plan_s = p;
     }
+    __syncthreads();
+    const SplitPlan plan = plan_s;
     for (int base = 0; base < n_inst; base += 1024) {
         int i = base + threadIdx.x;
         int v = 0;
         if (i < n_inst) {
-            const int64_t k = inst_k(count, fixed_k, n_ax, nfb, i);
-            int n = (int)((k + ksplit - 1) / ksplit);
-            int64_t kc = ksplit;
-            if (balance_grid > 0 && k > 0) {
-                const int extra = extra_all / n_inst + (i < extra_all % n_inst ? 1 : 0);
-                n = (int)max<int64_t>(min<int64_t>(min<int64_t>(n + extra, max_splits), (k + min_cols - 1) / min_cols), n);
-                kc = ((k + n - 1) / n + 63) / 64 * 64;
-                n = (int)((k + kc - 1) / kc);
-            }
-            nsplit[i] = n;
-            kcols[i] = (int32_t)kc;
-            v = n * n_st;
+            const Split sp = split_of(rule, plan, cols(i / nfb), i);
+            nsplit[i] = sp.n;
+            kcols[i] = (int32_t)sp.kc;
+            v = sp.n * rule.n_st;
         }
         int x = v;
         for (int d = 1; d < kWave; d <<= 1) {
@@ -639,10 +656,12 @@ hipError_t launch_worklist(int prec, const HerkArgs &a, int unit, hipStream_t s)
     if (a.n_inst <= 0) return hipSuccess;
     const int st = herk_super_tile(prec);
     const int nb = a.n_rows_pad / st;
-    const int n_st = unit ? 1 : nb * (nb + 1) / 2;
-    k_worklist<<<1, 1024, 0, s>>>(a.count, a.fixed_k, a.n_ax, a.nfb, a.n_inst, a.ksplit, n_st, a.balance_grid,
-                                  a.n_bal < 1 ? 1 : a.n_bal, a.min_cols < 64 ? 64 : a.min_cols, a.max_splits, a.work,
-                                  a.nsplit, a.kcols);
+    SplitRule r = a.rule;
+    r.ksplit = a.ksplit;
+    r.max_splits = a.max_splits;
+    r.n_st = unit ? 1 : nb * (nb + 1) / 2;
+    if (r.n_bal < 1) r.n_bal = 1;
+    k_worklist<<<1, 1024, 0, s>>>(a.count, a.fixed_k, a.n_ax, a.nfb, a.n_inst, r, a.work, a.nsplit, a.kcols);
     return hipGetLastError();
 }
 

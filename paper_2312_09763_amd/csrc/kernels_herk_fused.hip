@@ -434,7 +434,7 @@ __global__ void __launch_bounds__(512, 1) k_herk_coh(FusedArgs a) {
     // the triangle waves the row sets of TriSet6; its square waves form 64
     // antennas and its triangle waves 32.  The other launch skips that block.
     constexpr bool short_blk = SHORT;
-    const bool has_short = !OFF && a.n_ant - (nb - 1) * kST <= 96;
+    const bool has_short = !OFF && short_last_block(a.n_ant, nb);
     const int n_kind = OFF ? nb * (nb - 1) : SHORT ? 1 : has_short ? nb - 1 : nb;
     const int total = a.work[a.n_inst] * n_kind;
     const int per_xcd = a.grid / 8;
@@ -1358,7 +1358,7 @@ hipError_t launch_herk_fused(int prec, const FusedArgs &a, hipStream_t s, int wh
         if (first) {
             // the full diagonal blocks, then a short last block (at most 96 antennas)
             const int nb = a.n_rows_pad / (2 * kST);
-            const bool has_short = a.n_ant - (nb - 1) * kST <= 96;
+            const bool has_short = short_last_block(a.n_ant, nb);
             if (prec == PB3) {
                 if (nb > 1 || !has_short) {
                     if (split == 2)

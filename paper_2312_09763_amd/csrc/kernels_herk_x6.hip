@@ -268,7 +268,7 @@ __global__ void __launch_bounds__(512, 1) k_coh_x6(FusedArgs a) {
     const int l16 = lane & 15, lk = lane >> 4;
     const int Np = a.n_rows_pad;
     const int nb = Np / (2 * kST);
-    const bool has_short = a.n_ant - (nb - 1) * kST <= 96;
+    const bool has_short = short_last_block(a.n_ant, nb);
     const int n_kind = SHORT ? 1 : has_short ? nb - 1 : nb;
     const int total = a.work[a.n_inst] * n_kind;
     const int per_xcd = a.grid / 8;
@@ -807,7 +807,7 @@ __global__ void __launch_bounds__(512, 1) k_blk3_x6(FusedArgs a) {
 
 hipError_t launch_coh_x6(const FusedArgs &a, hipStream_t s) {
     const int nb = a.n_rows_pad / (2 * kST);
-    const bool has_short = a.n_ant - (nb - 1) * kST <= 96;
+    const bool has_short = short_last_block(a.n_ant, nb);
     if (nb > 1 || !has_short) {
         if ((a.tile & 15) == 2)
             k_coh_x6<64, false><<<a.grid, 512, 0, s>>>(a);

@@ -61,7 +61,7 @@ struct matvis_ctx {
     int64_t step_ksplit = 4096;  // of matvis_step_herk, whose FP32 accumulators take every MFMA update
     int step_splits = 1;
     int pair_splits = 1;  // k-splits of ksplit columns (the sub-matrix product, which is not balanced)
-    int n_bal = 1;        // items per k-split of the product launch that the splits are balanced for
+    SplitRule split_rule{};  // of the k-splits that k_worklist adds
     int64_t nblk_cap = 1;
     bool fused = false;  // Z formed inside the product (FP32, BF16X3, or FP64 over sources)
 
@@ -166,10 +166,6 @@ matvis_status dalloc(matvis_ctx *c, T **p, size_t bytes) {
     *p = (T *)q;
     return MATVIS_OK;
 }
-
-// Columns that a k-split keeps at least when k_worklist adds splits (four stages
-// of the product kernels; below that an item's fill and write-out outweigh it).
-constexpr int kMinSplitCols = 64;
 
 int64_t round_up(int64_t x, int64_t m) { return ((x + m - 1) / m) * m; }
 
@@ -593,18 +589,25 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
     } else {
         const int nb = c->Np / c->st;
         const int grid = c->fused ? c->fused_grid : c->herk_grid;
-        c->n_bal = !c->fused ? nb * (nb + 1) / 2
-                   : prec == P64 ? f64_items(cfg->n_ant)
-                   : over_sources ? c->Np / (2 * c->st)
-                   : three_blocks ? 3
-                   : prec == PB3 && nb == 2 ? 1  // one item holds both row blocks
-                                            : nb;
-        const int64_t per = std::max(1, grid / c->n_bal);
+        SplitRule &r = c->split_rule;
+        r.grid = grid;
+        r.plain_splits = c->pair_splits;
+        // one launch of so many items a split, or the several launches over sources; FUSED_ROWS has
+        // one item, which holds both row blocks
+        r.n_st = 1;
+        r.n_bal = !c->fused ? nb * (nb + 1) / 2 : prec == P64 ? f64_items(cfg->n_ant) : three_blocks ? 3 : 1;
+        if (over_sources) sources_launches(cfg->n_ant, c->Np, r);
+        const int64_t per = std::max(1, grid / r.n_bal);
         const size_t one = (size_t)B * c->Np * c->Np * cbytes(prec);
         int64_t most = c->max_splits + (per + B - 1) / B;
         most = std::min(most, (c->ldz + kMinSplitCols - 1) / kMinSplitCols);
         most = std::min<int64_t>(most, (int64_t)(((size_t)1 << 30) / one));
         c->max_splits = std::max<int64_t>(c->max_splits, most);
+        if (r.n_launch > 1) {  // no more room than the plan of this batch makes use of
+            r.ksplit = c->ksplit;
+            r.max_splits = c->max_splits;
+            c->max_splits = std::max(c->pair_splits, splits_wanted(r, c->ntb, c->nfb, c->ldz));
+        }
     }
     // Z scratch: a whole batch when Z goes through device memory, else one
     // instance (used only by matvis_step_herk)
@@ -786,9 +789,7 @@ matvis_status enqueue_simulate(matvis_ctx *c, const double *antpos, const int32_
                 ha.work = c->work;
                 ha.nsplit = c->work + B_cap + 1;
                 ha.kcols = c->work + 2 * B_cap + 1;
-                ha.balance_grid = c->fused ? c->fused_grid : c->herk_grid;
-                ha.n_bal = c->n_bal;
-                ha.min_cols = kMinSplitCols;
+                ha.rule = c->split_rule;
                 ha.grid = c->herk_grid;
                 if (!pairs && !c->full.n_bundle)
                     STEP(c, MATVIS_STEP_OTHER, s, launch_worklist(prec, ha, c->fused ? 1 : 0, s));
@@ -1243,7 +1244,6 @@ matvis_status matvis_step_herk(matvis_ctx *c, const void *Zin, int32_t n_row, in
     ha.work = c->work;
     ha.nsplit = c->work + c->ntb * c->nfb + 1;
     ha.kcols = c->work + 2 * c->ntb * c->nfb + 1;
-    ha.balance_grid = 0;
     ha.grid = c->herk_grid;
     HIPCHK(c, launch_worklist(prec, ha, 0, s));
     HIPCHK(c, launch_herk(prec, ha, s));
