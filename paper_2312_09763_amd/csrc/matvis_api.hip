@@ -430,25 +430,55 @@ void set_launch(int prec, const Tiles &T, DevTiles &d) {
     d.n_bundle = (int32_t)T.bundles.size();
 }
 
-// A tile list's device copy, in one allocation and one transfer.
-matvis_status upload_tiles(matvis_ctx *c, const Tiles &T, DevTiles &d) {
+// A tile list as it lies on the device: bundles, tiles, destinations, rows.
+std::vector<int32_t> pack_tiles(const Tiles &T) {
     static_assert(sizeof(TileBundle) == 4 * sizeof(int32_t), "bundles are stored as four words");
     std::vector<int32_t> all;
+    all.reserve(4 * T.bundles.size() + T.tiles.size() + T.dst.size() + T.rows.size());
     for (const TileBundle &b : T.bundles) all.insert(all.end(), {b.row0, b.n_rows, b.tile0, b.n_tiles});
     all.insert(all.end(), T.tiles.begin(), T.tiles.end());
     all.insert(all.end(), T.dst.begin(), T.dst.end());
     all.insert(all.end(), T.rows.begin(), T.rows.end());
-    int32_t *p = nullptr;
-    matvis_status st = dalloc(c, &p, sizeof(int32_t) * all.size());
-    if (st != MATVIS_OK) return st;
-    d.bundles = (TileBundle *)p;
-    HIPCHK(c, hipMemcpy(p, all.data(), sizeof(int32_t) * all.size(), hipMemcpyHostToDevice));
-    d.tiles = p + 4 * T.bundles.size();
+    return all;
+}
+// (its device copy lies at `at`)
+void bind_tiles(int prec, const Tiles &T, int32_t *at, DevTiles &d) {
+    d.bundles = (TileBundle *)at;
+    d.tiles = at + 4 * T.bundles.size();
     d.dst = d.tiles + T.tiles.size();
     d.rows = d.dst + T.dst.size();
-    set_launch(c->cfg.precision == MATVIS_FP64 ? P64 : P32, T, d);
-    return MATVIS_OK;
+    set_launch(prec, T, d);
 }
+
+// Buffers asked for one by one and allocated in one piece: an allocation of its own costs each
+// large one 10 to 20 us.
+struct Arena {
+    struct Piece {
+        void *where;  // the pointer to set
+        size_t offset;
+    };
+    static constexpr int kMost = 32;
+    Piece pieces[kMost];
+    int n = 0;
+    size_t total = 0;
+    template <typename T>
+    void add(T **p, size_t bytes) {
+        const size_t align = bytes >= (size_t)2 << 20 ? (size_t)2 << 20 : 256;
+        total = (total + align - 1) / align * align;
+        pieces[n++] = {p, total};
+        total += std::max<size_t>(bytes, 256);
+    }
+    matvis_status alloc(matvis_ctx *c) {
+        char *base = nullptr;
+        const matvis_status st = dalloc(c, &base, total);
+        if (st != MATVIS_OK) return st;
+        for (int i = 0; i < n; i++) {
+            void *p = base + pieces[i].offset;
+            std::memcpy(pieces[i].where, &p, sizeof(p));
+        }
+        return MATVIS_OK;
+    }
+};
 
 }  // namespace
 
@@ -548,10 +578,12 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
     const bool tiled = path == MATVIS_PATH_FUSED || (c->fused && prec == P64 && !over64) ||
                        (over_sources && prec == P32 && cfg->n_ant <= 80);
     Tiles tiles;
+    std::vector<int32_t> tiles_h;
     if (tiled) {
         c->full.coherent = prec != P64 && cfg->n_feed == 2 && cfg->n_ax == 2 && cfg->n_beam == 1;
         try {
             tiles = full_tiles(prec, cfg->n_ant, cfg->n_feed, c->Np, c->full.coherent != 0);
+            tiles_h = pack_tiles(tiles);
         } catch (const std::bad_alloc &) {
             matvis_destroy(c);
             return MATVIS_ENOMEM;
@@ -614,29 +646,17 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
     const int zinst_n = c->fused ? 1 : B;
 
     const size_t ncomp = (size_t)cfg->n_beam * cfg->n_feed * cfg->n_ax;
-#define ALLOC(ptr, bytes)                              \
-    do {                                               \
-        matvis_status _s = dalloc(c, &(ptr), (bytes)); \
-        if (_s != MATVIS_OK) {                         \
-            fprintf(stderr, "matvis_init: %s\n", c->err.c_str()); \
-            matvis_destroy(c);                         \
-            return _s;                                 \
-        }                                              \
-    } while (0)
+    const size_t zbytes = (prec == PB3 ? (size_t)4 : cbytes(prec)) * zinst_n * c->Np * c->ldz;
+    Arena arena;
+    int32_t *tiles_d = nullptr;
+#define ALLOC(ptr, bytes) arena.add(&(ptr), (bytes))
     ALLOC(c->xeq, sizeof(double) * 3 * cfg->max_src);
     ALLOC(c->xeq_in, sizeof(double) * 3 * cfg->max_src);
     ALLOC(c->cell, sizeof(int16_t) * cfg->max_src);
     ALLOC(c->cell_hist, sizeof(int32_t) * sort_hist_entries(cfg->max_src));
     ALLOC(c->perm, sizeof(int32_t) * cfg->max_src);
     ALLOC(c->rot, sizeof(double) * 9 * cfg->max_time);
-    if (tiled) {
-        st = upload_tiles(c, tiles, c->full);
-        if (st != MATVIS_OK) {
-            fprintf(stderr, "matvis_init: %s\n", c->err.c_str());
-            matvis_destroy(c);
-            return st;
-        }
-    }
+    if (tiled) ALLOC(tiles_d, sizeof(int32_t) * tiles_h.size());
     ALLOC(c->antc, sizeof(double) * 3 * cfg->n_ant);
     ALLOC(c->bidx, sizeof(int32_t) * cfg->n_ant);
     ALLOC(c->flags, sizeof(int32_t) * 4);
@@ -647,7 +667,6 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
     ALLOC(c->s_hat, sizeof(double) * 3 * c->ntb * c->chunk);
     ALLOC(c->za_az, sizeof(double) * 2 * c->ntb * c->chunk);
     ALLOC(c->A, cbytes(prec) * ncomp * B * c->chunk);
-    const size_t zbytes = (prec == PB3 ? (size_t)4 : cbytes(prec)) * zinst_n * c->Np * c->ldz;
     ALLOC(c->Z, zbytes);
     if (prec == PB3) ALLOC(c->Z_lo, zbytes);
     ALLOC(c->part, cbytes(prec) * std::max((size_t)B * c->max_splits, (size_t)c->step_splits) * c->Np * c->Np);
@@ -663,9 +682,21 @@ matvis_status matvis_init(const matvis_config *cfg, matvis_ctx **out) {
         ALLOC(c->sur_Wb, sizeof(__bf16) * mlp::kImgElems * cfg->n_beam);
     }
 #undef ALLOC
-    // Rows N..Np-1 of Z are never written by the kernels and must read as zero.
-    hipError_t e = hipMemset(c->Z, 0, zbytes);
-    if (e == hipSuccess && c->Z_lo) e = hipMemset(c->Z_lo, 0, zbytes);
+    st = arena.alloc(c);
+    if (st != MATVIS_OK) {
+        fprintf(stderr, "matvis_init: %s\n", c->err.c_str());
+        matvis_destroy(c);
+        return st;
+    }
+    hipError_t e = hipSuccess;
+    if (tiled) {  // (the list outlives the copy: hipDeviceSynchronize below)
+        bind_tiles(prec == P64 ? P64 : P32, tiles, tiles_d, c->full);
+        e = hipMemcpyAsync(tiles_d, tiles_h.data(), sizeof(int32_t) * tiles_h.size(), hipMemcpyHostToDevice, nullptr);
+    }
+    // Rows N..Np-1 of a batch's Z are never written by the kernels and must read as zero.
+    // (matvis_step_herk, the only user of a fused context's Z, clears its padding itself.)
+    if (e == hipSuccess && !c->fused) e = hipMemset(c->Z, 0, zbytes);
+    if (e == hipSuccess && !c->fused && c->Z_lo) e = hipMemset(c->Z_lo, 0, zbytes);
     if (e == hipSuccess) e = hipMemset(c->flags, 0, sizeof(int32_t) * 4);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -1037,11 +1068,13 @@ matvis_status matvis_set_pairs(matvis_ctx *c, const int32_t *pair_a, const int32
     const int prec = g.precision == MATVIS_FP64 ? P64 : g.precision == MATVIS_FP32 ? P32 : PB3;
     int64_t size = 0;
     Tiles T;
+    std::vector<int32_t> list;
     try {
         const red::Plan P = red::plan(pair_a, pair_b, n_pair, g.n_ant, n_sub);
         for (size_t x = 0; x < P.A.size(); x++) size += (int64_t)P.A[x].size() * P.B[x].size();
         T = in_lds ? pair_tiles(prec, pair_a, pair_b, n_pair, nf)
                    : pair_submatrices(P, pair_a, pair_b, n_pair, g.n_ant, nf);
+        if (in_lds) list = pack_tiles(T);
     } catch (const std::bad_alloc &) {
         return fail(c, MATVIS_ENOMEM, "host memory for the pair plan");
     }
@@ -1071,7 +1104,10 @@ matvis_status matvis_set_pairs(matvis_ctx *c, const int32_t *pair_a, const int32
     matvis_status st;
     int splits = c->pair_splits;
     if (in_lds) {
-        if ((st = upload_tiles(c, T, c->pr_list)) != MATVIS_OK) return st;
+        int32_t *at = nullptr;
+        if ((st = dalloc(c, &at, sizeof(int32_t) * list.size())) != MATVIS_OK) return st;
+        bind_tiles(prec == P64 ? P64 : P32, T, at, c->pr_list);
+        HIPCHK(c, hipMemcpy(at, list.data(), sizeof(int32_t) * list.size(), hipMemcpyHostToDevice));
         splits = tile_splits(c, c->pr_list, B_cap, splits, INT32_MAX);
     } else {
         if ((st = dalloc(c, &c->pr_rows, sizeof(int32_t) * rows.size())) != MATVIS_OK) return st;
