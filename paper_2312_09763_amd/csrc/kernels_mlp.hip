@@ -607,11 +607,21 @@ int infer_cus() {
 
 // Point tiles per task.  A task is a serial chain (about 15 us for 16 points, 20 for 32, 33
 // for 64, alone on its SIMD), and waves side by side hide it better than longer tasks do:
-// calls of 1000 / 32 768 / 100 000 / 200 000 points take 36 / 40 / 58 / 85 us on 16-point tasks
-// with four waves a SIMD, 42 / 44 / 63 / 85 on 32-point ones with two and 56 / 56 / 65 / 99
-// on 64-point ones; past that the weights, read from LDS once per task, count: 111 / 305 us
-// at 300 000 / 1 000 000 points against 114 / 292 and 109 / 306.
-int infer_tiles(int64_t points) { return points <= (1 << 18) ? 1 : 2; }
+// calls of 32 768 / 65 536 / 98 304 / 110 000 points take 39 / 46 / 54 / 58 us on 16-point tasks with
+// four waves a SIMD, 42 / 47 / 55 / 63 on 32-point ones with two and 54 / 55 / 63 / 64 on 64-point
+// ones.  From some 115 000 points on the weights, read from LDS once per task, count as
+// much as the steps in which a call's time grows, a task on every SIMD: 16 384 points in
+// 16-point tasks, 32 768 in 32-point ones, which are the better where they fill their last
+// step (120 000 / 131 072 / 150 000 / 262 144 points 62.7 / 63.1 / 68.8 / 96.8 against 63.8 / 64.3 /
+// 70.8 / 100.9) and not where they do not (180 000 / 230 000: 80 / 96 against 76 / 93).  Past 2^18
+// points 32-point tasks are 2 % slower to 6 % faster (300 000: 114 against 112, 360 000: 121
+// against 128, 1 000 000: 292 against 310).  Calls on the visible sources know only how many
+// these are at most.
+int infer_tiles(int64_t points, bool at_most) {
+    if (points > (1 << 18)) return 2;
+    const int64_t step = 16 * 4 * (int64_t)infer_cus(), n = (points + step - 1) / step;
+    return !at_most && n > 7 && n % 2 == 0 ? 2 : 1;
+}
 
 template <bool SIM>
 hipError_t launch_infer(const InferArgs &a, int pt, hipStream_t s) {
@@ -731,7 +741,7 @@ hipError_t infer_plain(const float *P, const __bf16 *Wb, const float *x, int64_t
     a.x = x;
     a.out = out;
     a.n = n;
-    const int pt = infer_tiles(n);
+    const int pt = infer_tiles(n, false);
     a.n_tasks = (n + 16 * pt - 1) / (16 * pt);
     return launch_infer<false>(a, pt, s);
 }
@@ -762,7 +772,7 @@ hipError_t infer_sim(const float *P, const __bf16 *Wb, double nu0, double nu1, c
     a.beam = beam;
     a.n_beam = n_beam;
     a.bt = bt;
-    const int pt = infer_tiles(max_m * bt.ntb);
+    const int pt = infer_tiles(max_m * bt.ntb, true);
     a.tiles = (max_m + 16 * pt - 1) / (16 * pt);
     a.n_tasks = a.tiles * bt.ntb;  // a task is some sources of one time: every channel of the batch
     return launch_infer<true>(a, pt, s);
