@@ -247,6 +247,9 @@ struct Pads {
         const float4 f = *(const float4 *)at(st, m, 2);
         return Src{xy.x, xy.y, *(const double *)at(st, m, 1), f.x, f.y, f.z, f.w};
     }
+    // a factor more, of the other block's rows
+    __device__ void put_factor(int st, int m, float g) const { *(float *)(at(st, m, 1) + 8) = g; }
+    __device__ float factor(int st, int m) const { return *(const float *)(at(st, m, 1) + 8); }
 };
 
 // ---------------------------------------------------------------------------
@@ -450,8 +453,8 @@ __global__ void __launch_bounds__(512, 1) k_coh_x6(FusedArgs a) {
 
 // ---------------------------------------------------------------------------
 // Block pairs I > J of the product over sources, two kinds of item per pair as in
-// k_herk_pairs: rows w0 F_I, w1 F_I against the plain columns F_J with (w0, w1) =
-// (C_00, C_11) or (C_10, conj C_10).  Waves s and s + 4 (one SIMD) take the two
+// k_herk_pairs: rows w0 F_I, w1 F_I against the columns g F_J with (w0, w1) = (C_00, C_11)
+// or (C_10, conj C_10), over g (see stash).  Waves s and s + 4 (one SIMD) take the two
 // products with opposite row halves and the same column half; row tiles past a
 // short block I are neither formed nor multiplied.  (The columns are rotated in
 // registers: a fourth plane does not fit the LDS.)
@@ -517,25 +520,31 @@ __global__ void __launch_bounds__(512, 1) k_pairs_x6(FusedArgs a) {
                 for (int c = 0; c < 4; c++) fb[c] = Bm[(int64_t)c * a.ld_src + m];
             }
         };
-        // the two complex weights (f0, f1), (f2, f3): C_00 and C_11, or C_10 and its conjugate
+        // the two complex weights (f0, f1), (f2, f3): C_00 and C_11, or C_10 and its conjugate, over
+        // g = sqrt(max(C_00, C_11)), which the rows of block J take: both operands then stay of the
+        // size of B and their low terms within FP32's range wherever B's square is
         auto stash = [&](int stage) {
-            float w0, w1;
+            const float c00 = fb[0].x * fb[0].x + fb[0].y * fb[0].y + fb[1].x * fb[1].x + fb[1].y * fb[1].y;
+            const float c11 = fb[2].x * fb[2].x + fb[2].y * fb[2].y + fb[3].x * fb[3].x + fb[3].y * fb[3].y;
+            const float g = sqrtf(fmaxf(c00, c11)), r = g > 0.f ? 1.f / g : 0.f;
+            float w0 = c00, w1 = c11;
             if (kind_y) {
                 w0 = fb[2].x * fb[0].x + fb[2].y * fb[0].y + fb[3].x * fb[1].x + fb[3].y * fb[1].y;
                 w1 = fb[2].y * fb[0].x - fb[2].x * fb[0].y + fb[3].y * fb[1].x - fb[3].x * fb[1].y;
-            } else {
-                w0 = fb[0].x * fb[0].x + fb[0].y * fb[0].y + fb[1].x * fb[1].x + fb[1].y * fb[1].y;
-                w1 = fb[2].x * fb[2].x + fb[2].y * fb[2].y + fb[3].x * fb[3].x + fb[3].y * fb[3].y;
             }
+            w0 *= r;
+            w1 *= r;
             pads.put_src(stage & 1, tid,
                          Src{fx, fy, fz, w0, kind_y ? w1 : 0.f, kind_y ? w0 : w1, kind_y ? -w1 : 0.f});
+            pads.put_factor(stage & 1, tid, g);
         };
-        // Weighted rows of block I or plain rows of block J for this thread's two
+        // Weighted rows of block I or the rows of block J for this thread's two
         // sources; a source past the split has zero weights.
         auto produce = [&](unsigned char *buf, int stage) __attribute__((always_inline)) {
             Src w[2];
             w[0] = pads.src(stage & 1, 2 * mp);
             w[1] = pads.src(stage & 1, 2 * mp + 1);
+            const float g[2] = {pads.factor(stage & 1, 2 * mp), pads.factor(stage & 1, 2 * mp + 1)};
 #pragma unroll
             for (int k = 0; k < 4; k++) {
                 const int as = a0 + 64 * k;
@@ -546,7 +555,9 @@ __global__ void __launch_bounds__(512, 1) k_pairs_x6(FusedArgs a) {
 #pragma unroll
                 for (int s = 0; s < 2; s++) fringe(ux * w[s].x + uy * w[s].y + uz * w[s].z, fr[s], fi[s]);
                 if (k >= 2) {
-                    store_row(buf, kST + as, mp, fr, fi);  // plane 2: row as - kST of block J
+#pragma unroll
+                    for (int s = 0; s < 2; s++) vr[s] = g[s] * fr[s], vi[s] = g[s] * fi[s];
+                    store_row(buf, kST + as, mp, vr, vi);  // plane 2: row as - kST of block J
                     continue;
                 }
 #pragma unroll
