@@ -192,7 +192,9 @@ extern "C" matvis_status matvis_autotune(const matvis_config *base, const double
     const bool over_sources = path0 == MATVIS_PATH_SOURCES, three_blocks = path0 == MATVIS_PATH_FUSED_BLOCKS;
     const int64_t kdef = mv::default_ksplit(prec, path0);
     std::vector<long long> tiles = {0};  // forming split, bits 0-3
-    if (over_sources) tiles.push_back(2);
+    // (it is the full diagonal blocks': a short block alone and the 16 x 16 tiles of small FP32
+    // arrays have one form)
+    if (over_sources && base->n_ant > mv::kShortAnts) tiles.push_back(2);
     if (three_blocks) tiles.insert(tiles.end(), {2, 4});
     std::vector<long long> pair_kernels = {0};  // block-pair kernel, bit 4 (BF16X3, more than one block)
     if (over_sources && prec == mv::PB3 && base->n_ant > 128) pair_kernels.push_back(16);
