@@ -545,9 +545,9 @@ def workloads_section(args):
 
 def redundancy_section(args):
     """Full product V = Z Z^H against the sub-matrix product of App. A for the unique
-    baselines of a redundant 350-antenna hexagon (the diffuse-sky array), BF16X3,
-    FP32 and FP64 with Z in device memory, and BF16X3 and FP32 with Z formed in the
-    product's stages; per-step device times from the profiled pass."""
+    baselines of a redundant 350-antenna hexagon (the diffuse-sky array), BF16X3
+    and FP32 with Z in device memory, and BF16X3, FP32 (the _fused rows) and FP64 with Z
+    formed in LDS; per-step device times from the profiled pass."""
     import torch
     from paper_2312_09763_amd import matvis as mv
     from paper_2312_09763_amd import synth

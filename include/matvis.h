@@ -92,6 +92,7 @@ typedef struct {
     int32_t flags;        /* MATVIS_FLAG_* bits */
     int64_t ksplit;       /* Z columns summed by one product work item before its partial
                              is stored at most (a multiple of 64); 0 = automatic.
+                             Small batches get shorter splits, which fill the device.
                              FP32 accumulators see up to ksplit / 2 sequential
                              updates, so this bounds their rounding; the partials are
                              summed in FP64. */
@@ -350,12 +351,12 @@ matvis_status matvis_autotune(const matvis_config *base, const double *antpos, c
  * arrays of MATVIS_N_STEPS entries.
  * ------------------------------------------------------------------------- */
 typedef enum {
-    MATVIS_STEP_SKY = 0,    /* rotation + compaction (count, scan, scatter) */
+    MATVIS_STEP_SKY = 0,    /* input preparation and checks, sky-cell order, rotation + compaction */
     MATVIS_STEP_BEAM = 1,   /* beam interpolation */
     MATVIS_STEP_ZFORM = 2,  /* phase + Z formation */
     MATVIS_STEP_HERK = 3,   /* the Z Z^H product kernel alone */
     MATVIS_STEP_REDUCE = 4, /* k-split reduction + Hermitian fill */
-    MATVIS_STEP_OTHER = 5,  /* input preparation and the work-list prefix */
+    MATVIS_STEP_OTHER = 5,  /* the work-list prefix (k-splits of the persistent products) */
     MATVIS_STEP_HERK_PAIRS = 6, /* the product's second launch, where it has one: the
                                    off-diagonal antenna-block pairs (path SOURCES); the
                                    product's time is HERK + HERK_PAIRS */

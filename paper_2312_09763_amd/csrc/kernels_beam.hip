@@ -184,8 +184,9 @@ __global__ void __launch_bounds__(256) k_stencil(InterpArgs a, Batch bt) {
 // sources, 4 times of 2 channels: 2.50 ms with 4 channels a group (half the lanes
 // idle) and an eighth of all slots' source range to each XCD (half of it below the
 // horizon, so half the XCDs idle), 1.45 ms without these two faults, 1.02 ms in
-// groups of 4 beams (16: 1.11, 8: 1.03, 2: 1.05), which is 4.1 GB at 4.0 TB/s.  More
-// waves in flight (fewer registers, by launch bounds) were slower: 1.71 against 1.45 ms.
+// groups of 4 beams (16: 1.11, 8: 1.03, 2: 1.05): 36 million reads past L2, of 64 or 128
+// bytes each (2.3 to 4.6 GB), and 0.8 GB written.  More waves in flight (fewer registers,
+// by launch bounds) were slower: 1.71 against 1.45 ms.
 template <typename R, int MODE, int NCOMP, bool ST, int FG>
 __global__ void __launch_bounds__(256) k_interp_tf(InterpArgs a, Batch bt, uint32_t z0) {
     typedef typename CplxOf<R>::T C;

@@ -22,7 +22,7 @@
 // so the two waves of a SIMD overlap matrix and vector work.
 //
 // 128 antennas, 50 000 sources, 4 x 4 instances: 2.2 ms (43 useful TFLOP/s, 48 executed;
-// MFMAs busy 65 % at 2.16 GHz) where writing Z took 2.1 ms and Z Z^H 4.3 ms; 4 antennas
+// MFMAs busy 70 % at 2.18 GHz) where writing Z took 2.1 ms and Z Z^H 4.3 ms; 4 antennas
 // 351 against 656 us for the whole call, 33 antennas 649 against 1929 us, 200 antennas
 // and 3000 sources 320 against 488 us, so every such context takes it.
 #include <type_traits>

@@ -14,9 +14,9 @@
 // 2.1e-6), 5.2e-7 -> 1.5e-7 on 350 antennas and 786 432 pixels.
 //
 // Bound by MFMAs and vector instructions together (2.4 per MFMA: splitting, column
-// rotations, the additions); MFMAs are busy 60 % at 2.09 GHz.  Product of the first
-// case above 53.3 -> 31.7 ms; 350 polarised antennas, 1 x 4 instances, whole call
-// 28.2 -> 18.7 ms; 350 scalar antennas, 1 x 8, 14.4 -> 9.0 ms.
+// rotations, the additions); MFMAs are busy 61 % at 2.05 GHz (59 % in the block pairs).
+// Product of the first case above 53.3 -> 31.7 ms; 350 polarised antennas, 1 x 4
+// instances, whole call 28.3 -> 14.9 ms; 350 scalar antennas, 1 x 8, 14.4 -> 9.0 ms.
 //
 // The kernels are the FP32 forms of the product over sources (k_coh_x6 for the
 // diagonal blocks, k_pairs_x6 for the block pairs) and of the three-block scalar

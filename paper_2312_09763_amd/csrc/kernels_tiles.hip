@@ -11,8 +11,8 @@
 // written nor gathered, and nothing is done for padding beyond 16 rows: as blocks of 128
 // rows, 12, 37 and 61 polarised antennas all took the time of 64.
 //
-// A polarised array of up to 64 antennas with one beam (COHERENT) stages, as the product
-// over sources of larger ones does, the planes P0 = s0 F, P1 = s1 F and L = l F, with
+// A polarised array with one beam (COHERENT; up to 64 antennas, on FP32 up to 80) stages, as the
+// product over sources of larger ones does, the planes P0 = s0 F, P1 = s1 F and L = l F, with
 // s_p = sqrt(C_pp) and l = C10 / s0 of the source's 2 x 2 coherency C = B B^H:
 // V^00 = P0 P0^H, V^11 = P1 P1^H (lower triangles), V^10 = L P0^H: half the columns of Z.
 //
@@ -25,9 +25,9 @@
 // whichever is the least that holds its bundle: a CU always has 16 waves, and small
 // bundles have other workgroups to fill the waits at their barriers.
 //
-// Bound by vector instructions (63 % of the cycles: forming, rotation of columns, the
-// additions), LDS (54 %) and MFMAs (45 %) together; half of the waves multiply before
-// they form the next stage and half after.  Requested pairs of 350 antennas, 49 152
+// Bound by vector instructions (66 % of the cycles, 4.4 per MFMA: forming, rotation of
+// columns, the additions) and MFMAs (47 %) together, with LDS bank conflicts in 23 %; half of
+// the waves multiply before they form the next stage and half after.  Requested pairs of 350 antennas, 49 152
 // sources, 4 times of 8 channels, FP32: forming Z and multiplying went from 1.08 + 2.29
 // to 0.80 ms, the error against 64 bits from 1.3e-6 to 2.2e-7.  16 waves of 6 tiles
 // rather than 8 of 12 (with operands loaded a tile ahead) took 0.82 against 0.92 ms, rows
@@ -35,8 +35,11 @@
 // Whole calls of 100 000 sources, 4 times of 8 channels against blocks of 128 rows: FP32, 12
 // / 37 / 61 polarised antennas 2.19 / 2.22 / 2.23 -> 0.31 / 0.60 / 0.98 ms, 30 / 100 / 200
 // scalar ones 1.37 / 1.38 / 4.62 -> 0.23 / 0.60 / 1.41 ms; BF16X3, 12 / 37 / 61 polarised 0.83 /
-// 0.85 / 0.86 -> 0.30 / 0.56 / 0.79 ms, 30 / 100 scalar 0.61 / 0.61 -> 0.22 / 0.50 ms; errors a
-// quarter of what they were.
+// 0.85 / 0.86 -> 0.30 / 0.56 / 0.79 ms, 30 / 100 scalar 0.61 / 0.61 -> 0.22 / 0.50 ms.  The gain is
+// least where the blocks had least padding: 113 / 128 scalar antennas on BF16X3 594 / 595 ->
+// 544 / 557 us, 64 polarised ones 860 -> 784 us.  Errors against 64 bits: FP32 a quarter of what
+// they were; BF16X3, set by its two-term split, 2.2e-6 -> 1.2e-6 at 100 to 128 scalar antennas
+// and 100 000 sources, 1.9e-6 -> 5.1e-7 at 64 polarised ones.
 #include <type_traits>
 
 #include "herk_tiles.h"

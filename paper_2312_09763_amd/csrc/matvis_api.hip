@@ -6,8 +6,8 @@
 // x (source chunk) and enqueues, per step of Alg. 2:
 //   sky     : rotation + ordered horizon compaction of the chunk, per time;
 //   interp  : beam at the visible sources, per (t, f) instance;
-//   zform   : Z of Eq. (littlez), per instance;
-//   herk    : V partials of Eq. (zz) over a device-built work list;
+//   herk    : V partials of Eq. (zz), Z of Eq. (littlez) formed in LDS, over tile lists or
+//             a device-built work list (MATVIS_FLAG_UNFUSED: zform writes Z first);
 //   reduce  : fixed-order sum over k-splits and chunks, Hermitian fill.
 // Nothing in the sequence waits on the host, so the whole call is captured
 // once into a hipGraph (keyed by its arguments) and replayed afterwards.
@@ -63,7 +63,7 @@ struct matvis_ctx {
     int pair_splits = 1;  // k-splits of ksplit columns (the sub-matrix product, which is not balanced)
     SplitRule split_rule{};  // of the k-splits that k_worklist adds
     int64_t nblk_cap = 1;
-    bool fused = false;  // Z formed inside the product (FP32, BF16X3, or FP64 over sources)
+    bool fused = false;  // Z formed inside the product (without MATVIS_FLAG_UNFUSED)
 
     // device scratch
     double *xeq = nullptr, *rot = nullptr, *antc = nullptr, *s_hat = nullptr, *za_az = nullptr, *vacc = nullptr;

@@ -149,7 +149,7 @@ class Config:
     batch_time: int = 0
     batch_freq: int = 0
     use_graph: bool = True
-    unfused: bool = False  # FP32 / BF16X3: separate Z-formation step (Z in device memory)
+    unfused: bool = False  # separate Z-formation step (Z in device memory)
     ksplit: int = 0        # columns per product work item (multiple of 64); 0 = automatic
     polarised_sky: bool = False  # src_flux is [4][n_freq][n_src] (I, Q, U, V); needs n_ax = 2
     tile: int = 0          # product kernel variant (bits 0-3: forming split in 32-antenna units); 0 = automatic
