@@ -313,37 +313,40 @@ void bundle_tiles(Tiles &T, int prec, const std::vector<std::pair<int32_t, int32
 
 // The rows that some pair uses, in order, in blocks of 16, and the tiles that hold a pair,
 // by column block.
-Tiles pair_tiles(int prec, const int32_t *pair_a, const int32_t *pair_b, int n_pair, int nf) {
+Tiles pair_tiles(int prec, const int32_t *pair_a, const int32_t *pair_b, int n_pair, int n_ant, int nf) {
     Tiles T;
-    std::map<int32_t, int32_t> pos;  // antenna -> place among the used ones
+    std::vector<int32_t> pos(n_ant, -1), used;  // antenna -> place among the used ones
     for (int u = 0; u < n_pair; u++) pos[pair_a[u]] = pos[pair_b[u]] = 0;
-    std::vector<int32_t> used;
-    for (auto &kv : pos) {
-        kv.second = (int32_t)used.size();
-        used.push_back(kv.first);
-    }
-    const int n_rows = (int)used.size() * nf, B = kTile;
-    std::map<std::pair<int32_t, int32_t>, int32_t> tile;  // (column block, row block) -> index
+    for (int a = 0; a < n_ant; a++)
+        if (pos[a] == 0) {
+            pos[a] = (int32_t)used.size();
+            used.push_back(a);
+        }
+    const int n_rows = (int)used.size() * nf, B = kTile, nb = (n_rows + B - 1) / B;
+    // index of the tile (row block, column block) at column block * nb + row block
+    std::vector<int32_t> tile((size_t)nb * nb, -1);
     auto each = [&](auto f) {
         for (int u = 0; u < n_pair; u++)
             for (int p = 0; p < nf; p++)
                 for (int q = 0; q < nf; q++)
                     f(((size_t)u * nf + p) * nf + q, pos[pair_a[u]] * nf + p, pos[pair_b[u]] * nf + q);
     };
-    each([&](size_t, int32_t r, int32_t c) { tile[{c / B, r / B}] = 0; });
+    each([&](size_t, int32_t r, int32_t c) { tile[(size_t)(c / B) * nb + r / B] = 0; });
     std::vector<std::pair<int32_t, int32_t>> list;
-    for (auto &kv : tile) {
-        kv.second = (int32_t)list.size();
-        T.dst.push_back((int32_t)list.size() * B * B);
-        list.push_back({kv.first.second, kv.first.first});
-    }
+    for (int J = 0; J < nb; J++)
+        for (int I = 0; I < nb; I++)
+            if (tile[(size_t)J * nb + I] == 0) {
+                tile[(size_t)J * nb + I] = (int32_t)list.size();
+                T.dst.push_back((int32_t)list.size() * B * B);
+                list.push_back({I, J});
+            }
     bundle_tiles(T, prec, list, [&](int32_t b, int i) {
         const int r = b * B + i;
         return r < n_rows ? used[r / nf] * nf + r % nf : -1;
     });
     T.loc.resize((size_t)n_pair * nf * nf * 2);
     each([&](size_t e, int32_t r, int32_t c) {
-        T.loc[2 * e] = tile[{c / B, r / B}];
+        T.loc[2 * e] = tile[(size_t)(c / B) * nb + r / B];
         T.loc[2 * e + 1] = (r % B) * B + c % B;
     });
     return T;
@@ -1072,7 +1075,7 @@ matvis_status matvis_set_pairs(matvis_ctx *c, const int32_t *pair_a, const int32
     try {
         const red::Plan P = red::plan(pair_a, pair_b, n_pair, g.n_ant, n_sub);
         for (size_t x = 0; x < P.A.size(); x++) size += (int64_t)P.A[x].size() * P.B[x].size();
-        T = in_lds ? pair_tiles(prec, pair_a, pair_b, n_pair, nf)
+        T = in_lds ? pair_tiles(prec, pair_a, pair_b, n_pair, g.n_ant, nf)
                    : pair_submatrices(P, pair_a, pair_b, n_pair, g.n_ant, nf);
         if (in_lds) list = pack_tiles(T);
     } catch (const std::bad_alloc &) {
